@@ -177,10 +177,10 @@ def measure(cfg, args, P, torch, tiles_trial: int) -> dict:
             from paper_1701_02005_amd import pmc_traffic
             ent = json.loads(tr_file.read_text()).get(f"{args.workload}/{cfg.precision}/{dom}")
             src = Path(ent["source"]).name if ent else None
-            cn_slab = bool(tiles and tiles.get("cnslab"))
+            cn_rows = cfg.precision == "mixed" or cfg.ny > 321 or bool(tiles and tiles.get("cnslab"))
             z_fused = bool(tiles) and tiles.get("thomas") == 0
             same_kernels = ent and tuple(ent.get("kernels", ())) == tuple(
-                pmc_traffic.class_kernels(dom, cn_slab, z_fused))
+                pmc_traffic.class_kernels(dom, z_fused=z_fused, cn_rows=cn_rows))
             if same_kernels and ent.get("source_sha256") == pmc_traffic.source_hash(src):
                 traffic = ent["bytes_per_launch"]
         except (ValueError, OSError, KeyError):

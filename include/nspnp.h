@@ -371,12 +371,13 @@ NSPNP_API int nspnp_ensemble_clock(nspnp_ensemble *e, int32_t member, double *t,
  * (arch, grid, precision, members) key.  Trials advance the members (the
  * launch shape does not change any result); on return every member has
  * advanced by the same number of substeps.  tiles_out (NULL or 8 ints per
- * class) receives the choice: explicit-kernel threads, CN threads (64 to
- * 256: tiles of 16 columns; 512: tiles of 32 columns), x and z
+ * class) receives the choice: explicit-kernel threads, threads of the CN lane
+ * scans (64 to 256: tiles of 16 columns; 512: tiles of 32 columns), x and z
  * transform points, modes per tile of the mode solves, correction threads,
- * explicit-kernel and correction slab rows, and the CN method (0: lane
- * scans over whole columns; 16 or 32: row slabs of that height, three
- * passes).
+ * explicit-kernel and correction slab rows, and the CN method (0: lane scans
+ * in FP64 up to 320 rows, else slabs of rows in registers, their height by
+ * the number of rows; 16: slabs of 16 rows; 32: of 24 up to 384 rows, else
+ * of 16).
  * Synchronises. */
 NSPNP_API int nspnp_ensemble_autotune(nspnp_ensemble *e, const char *cache_path, int32_t trial_substeps,
                                       int32_t *tiles_out);

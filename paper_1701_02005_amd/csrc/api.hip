@@ -101,7 +101,7 @@ Layout make_layout(const nspnp_config *c) {
     L.off_fac = o; o = align256(o + 2 * nspec * 16);  // [kind][mode][row] pivots
     L.off_cpv = o; o = align256(o + 2 * nspec * 8);   // [kind][row][mode] c' (fused y-march)
     L.off_mu = o; o = align256(o + 2 * 16);           // pinned-mode volume means
-    L.off_coef = o; o = align256(o + 3 * cn_stage_stride((int)M) * 8);  // 3 stages: rows, slab products, n products
+    L.off_coef = o; o = align256(o + 3 * cn_stage_stride((int)M) * 8);  // 3 stages
     L.off_clock = o; o = align256(o + kClockSlots * 8);
     L.off_phys = o; o = align256(o + sizeof(Phys));
     L.off_stats = o; o = align256(o + (3 * M + 2) * 8);
@@ -291,9 +291,8 @@ void setup_common(nspnp_state *s, const nspnp_config *cfg, int nmem, hipStream_t
     s->mstride = 0;
     s->planx = make_plan(cfg->nx);
     s->planz = make_plan(cfg->nz);
-    // the tuner's choices at 256 x 193 x 256 (the mixed form takes 32-column
-    // Crank-Nicolson tiles: whole 128-byte lines of FP32 per row)
-    s->tiles = Tiles{256, cfg->precision == NSPNP_PREC_FP64 ? 256 : 512, 512, 1024, 16, 128, 16, 0};
+    // the tuner's choices at 256 x 193 x 256
+    s->tiles = Tiles{256, 256, 512, 1024, 16, 128, 16, 0};
     {
         int dev = 0, lds = 0;
         if (hipGetDevice(&dev) == hipSuccess &&
@@ -733,7 +732,6 @@ int nspnp_set_clock(nspnp_state *s, double t, double dt, int32_t stage, int64_t 
     if (s->host_health) s->host_health[0] = s->host_health[1] = 0.0;
     s->substeps = substeps;
     s->cn_fresh = false;  // dt may have changed
-    s->cn_coef_at = -1;
     return NSPNP_OK;
 }
 
@@ -926,7 +924,6 @@ int nspnp_load(nspnp_state *s, const char *path) {
     HIP_TRY(hipStreamSynchronize(s->stream));
     s->substeps = h.substeps;
     s->cn_fresh = false;
-    s->cn_coef_at = -1;
     s->rstats_every = cs.every;
     if (s->host_health) {
         s->host_health[0] = h.clock[2];

@@ -279,29 +279,26 @@ struct PoissonBatch {
     const Phys *phys;   // member 0's constants (charge factor)
 };
 
-// Row-slab Crank-Nicolson method: the most slabs per column.
-constexpr int kCnMaxSlabs = 32;
 // Crank-Nicolson coefficients of one Runge-Kutta stage: [3 systems][g, m, n]
-// [M] rows, the slab products [3 systems][P, Phi, Nu][kCnMaxSlabs], then for
-// the row-slab method's fused first pass [3 systems][M] the products of n
-// from the slab's first row up to the row below.
-__host__ __device__ inline size_t cn_stage_stride(int M) {
-    return 12 * (size_t)M + 9 * (size_t)kCnMaxSlabs;
-}
+// [cn_rows(M)], zeros past the last row (the solve's last slab of rows may
+// reach past it).
+constexpr int kCnPad = 32;
+__host__ __device__ inline int cn_rows(int M) { return (M + kCnPad - 1) / kCnPad * kCnPad + kCnPad; }
+__host__ __device__ inline size_t cn_stage_stride(int M) { return 9 * (size_t)cn_rows(M); }
 
 // Launch shapes chosen by the autotuner.  None of them changes the
 // arithmetic done per cell, column, line or mode, so results are bitwise
 // independent of the choice.
 struct Tiles {
     int expl;     // threads per block of the explicit kernel (64..256)
-    int cn;       // threads per block (columns) of the Crank-Nicolson solve
+    int cn;       // threads per block of the Crank-Nicolson lane scans
     int fftx;     // complex points per block of the x transforms
     int fftz;     // complex points per block of the z transforms
     int thomas;   // modes per tile of the y solve of the elliptic problems (capped by LDS); 0: the z
                   // transforms and the y solve fused into two row marches
     int corr;     // threads per block of the projection correction
     int slab;     // rows marched by one block of the explicit kernel
-    int cnslab;   // Crank-Nicolson: 0 lane-scan method, 16 or 32 row-slab method with that many rows
+    int cnslab;   // Crank-Nicolson: 0 by type and rows; else rows per thread, 16, or (32) 24 up to 384 rows
 };
 
 constexpr int kTileInts = 8;  // Tiles as exported through the ABI
@@ -377,10 +374,8 @@ struct nspnp_state {
     double2 *fac;        // Thomas pivots (1/den, c') of both elliptic operators, [kind][mode][row]
     double *cpv;         // c' alone, [kind][row][mode], for the fused y-march (NULL: not kept)
     double2 *mu;         // volume mean of the pinned pressure mode, per problem (fused y-march)
-    double *cn_coef;     // Crank-Nicolson recurrence coefficients, 9 M per stage
+    double *cn_coef;     // Crank-Nicolson recurrence coefficients, cn_stage_stride(M) per stage
     bool cn_fresh = false;  // cn_coef matches the device dt of the current step
-    int cn_coef_slab = -1;  // slab rows the slab products in cn_coef were made for
-    int64_t cn_coef_at = -1;  // substep count at which cn_coef was last brought up to date
     double *clock;       // device [t, dt, health, max |dPhi|]
     double *host_health = nullptr;  // pinned host mirror of each member's [health, max |dPhi|]
     bool owns_host_health = false;

@@ -6,6 +6,8 @@
 // u lives on x-faces, w on z-faces, v on the bottom y-face of each row (row 0
 // is the wall), c+-, phi and p at cell centres.  T is the storage and stencil
 // type: double for the FP64 form, float for the mixed form.
+#include <type_traits>
+
 #include "internal.h"
 
 namespace nspnp {
@@ -52,12 +54,6 @@ struct ExplicitArgs {
     int slabs;      // row slabs per member
     int slab_rows;  // rows marched by one block
     int implicit_xz;  // 1: x/z diffusion goes to the implicit (alpha) part of r, not to H
-    // Row-slab Crank-Nicolson with its first pass fused (NULL: not fused):
-    // this stage's recurrence coefficients [3 systems][g, m, n][M] and the
-    // method's scratch [2][5 fields][slabs][plane]; the block's slab is the
-    // method's slab, and the kernel stores both exits of every column.
-    const double *cn_coef;
-    double *cn_scr;
 };
 
 __device__ __forceinline__ void shift_explicit(ExplicitArgs &a, unsigned mem) {
@@ -68,10 +64,6 @@ __device__ __forceinline__ void shift_explicit(ExplicitArgs &a, unsigned mem) {
     a.phi = member_ptr_at(a.phi, ms, mem); a.p = member_ptr_at(a.p, ms, mem);
     for (int f = 0; f < 5; ++f) { a.h[f] = member_ptr_at(a.h[f], ms, mem); a.r[f] = member_ptr_at(a.r[f], ms, mem); }
     a.clock = member_ptr_at(a.clock, ms, mem);
-    if (a.cn_coef) {
-        a.cn_coef = member_ptr_at(a.cn_coef, ms, mem);
-        a.cn_scr = member_ptr_at(a.cn_scr, ms, mem);
-    }
 }
 
 // Convection, horizontal diffusion, Coulomb force and ion transport at one
@@ -168,13 +160,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves
     const bool use_old = (a.st.k > 0) && mode == 0;
     const bool keep = (a.st.k < 2) && mode == 0;
     const bool imp = a.implicit_xz != 0;  // x/z diffusion: implicit part of r instead of H
-    // Fused first pass of the row-slab Crank-Nicolson solve: along the slab,
-    // the local forward sweep l_j = g_j r_j + m_j l_{j-1} (l = 0 below the
-    // slab) of each field's right-hand side, and its local backward sweep
-    // taken at the slab's first row, k = sum_j (prod_{i<j} n_i) l_j (the
-    // products are column-independent: a table per system, u, w / v / ions).
-    const bool fuse = (mode == 0) && a.cn_coef != nullptr;
-    double cl[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, ck[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     const int e = active ? k * nx + i : 0;
     const unsigned ueb = (unsigned)e * (unsigned)sizeof(T);  // own column, bytes
     const int ip = (i + 1 >= nx) ? 0 : i + 1;
@@ -247,13 +232,6 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves
                 const T rv = dt * (gam * hval + zet * hold_c[f] - alp * gp + alp * nu_ly);
                 st_once(byte_at((T *)a.r[f], qb), rv);
                 if (keep) st_once(byte_at((T *)a.h[f], qb), hval);
-                if (fuse) {
-                    const int sys = (f == 1) ? 1 : (f >= 3 ? 2 : 0);
-                    const double *cf = a.cn_coef + (size_t)sys * 3 * M;
-                    const double *np = a.cn_coef + 9 * (size_t)M + 9 * kCnMaxSlabs + (size_t)sys * M;
-                    cl[f] = uniform_load(cf, j) * (double)rv + uniform_load(cf + M, j) * cl[f];
-                    ck[f] += uniform_load(np, j) * cl[f];
-                }
             };
 
             // ---------------- u on the x-face ----------------
@@ -400,31 +378,16 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves
         if (pre) store_rows(sc, rn);
         __syncthreads();
     }
-    if (fuse && active) {  // both exits of this column's slab (zero inputs)
-        const unsigned S = slabs;
-#pragma unroll
-        for (int f = 0; f < 5; ++f) {
-            a.cn_scr[((size_t)f * S + slab) * (size_t)pl + (unsigned)e] = cl[f];
-            a.cn_scr[((size_t)(5 + f) * S + slab) * (size_t)pl + (unsigned)e] = ck[f];
-        }
-    }
 }
 
 struct CnArgs {
     Dims d;
-    const Phys *phys;
     size_t ms;
-    Tables tb;
     Stage st;
     void *q[5];
-    const void *r[5];  // right-hand sides, state type
-    const double *clock;
-    double *coef;  // per stage: [3 systems][g, m, n][M], then [3 systems][P, Phi, Nu][kCnMaxSlabs]
-    double *scr;   // row-slab method: per member [2][5 fields][slabs][plane] FP64 scratch
-    int slab_rows; // row-slab method: rows per slab (0: lane-scan method)
-    int slabs;
-    int out_r;     // lane-scan method: write the solution back into r (a factor of the
-                   // three-direction factorisation) instead of q += solution
+    void *r[5];          // right-hand sides, state type
+    const double *coef;  // per stage: [3 systems][g, m, n][cn_rows(M)]
+    int out_r;           // 1: the solution replaces r (a factor of the three-direction factorisation)
 };
 
 // Row coefficients of the Crank-Nicolson matrix (I - beta L_y) of system
@@ -458,98 +421,72 @@ __device__ __forceinline__ void cn_row(const double *lo_tab, const double *up_ta
 // reduces to two linear recurrences with column-independent coefficients:
 //   d'_j = g_j r_j + m_j d'_{j-1},   x_j = d'_j + n_j x_{j+1}
 // with g = 1/den, m = -A/den, n = -c' (den, c' of the Thomas forward pass).
-// One block per member and Runge-Kutta stage (blockIdx.y): the L_y tables are
-// staged in LDS, one thread per system runs the (serial) forward pass from
-// LDS with one reciprocal per row, and the block stores the 9 M coefficients
-// of its stage with coalesced writes.  Launched once per Runge-Kutta step
-// (dt changes only at the first stage).
+// One block per member, Runge-Kutta stage (blockIdx.y) and system
+// (blockIdx.x): the matrix rows are formed by all threads into LDS, one
+// thread runs the (serial) forward pass from LDS, and the block stores its
+// 3 cn_rows(M) coefficients with coalesced writes, zeros past the last row
+// and, for the nodes, in row 0 (the wall: no unknown).  Launched once per
+// Runge-Kutta step (dt changes only at the first stage).
 struct CnStages {
     double alp[3];
 };
 
-// Row-slab form of the same recurrences (used when the rows are split into
-// slabs of L rows, one thread per column and slab): for slab [a, b) the
-// column-independent quantities are P = prod m_j, Nu = prod n_j and Phi = the
-// local backward sweep (zero input at b) of p_j = prod_{i=a..j} m_i, taken at
-// row a.  A column's exact solution on the slab is then
-//   x_j = kappa_j + phi_j D + nu_j X
-// with D = d'_{a-1}, X = x_b and kappa the local backward sweep of the local
-// forward sweep of r; D and X follow from scans across the slabs.
-
 __global__ void __launch_bounds__(256) k_cn_coef(Dims d, Tables tb, const Phys *phys, const double *clock,
-                                                 double *coef, CnStages stages, int slab_rows, size_t ms) {
-    __shared__ double s_tab[4][kMaxRows];      // lyc_lo, lyc_up, lyn_lo, lyn_up
-    __shared__ double s_out[9][kMaxRows];      // [sys][g, m, n][row]
+                                                 double *coef, CnStages stages, size_t ms) {
+    __shared__ double s_a[kMaxRows + kCnPad], s_b[kMaxRows + kCnPad], s_c[kMaxRows + kCnPad];
     phys = member_ptr(phys, ms);
     clock = member_ptr(clock, ms);
-    const int M = d.M;
-    const int stage = blockIdx.y;
-    coef = member_ptr(coef, ms) + (size_t)stage * cn_stage_stride(M);
-    for (int j = threadIdx.x; j < M; j += blockDim.x) {
-        s_tab[0][j] = tb.lyc_lo[j];
-        s_tab[1][j] = tb.lyc_up[j];
-        s_tab[2][j] = tb.lyn_lo[j];
-        s_tab[3][j] = tb.lyn_up[j];
+    const int M = d.M, Mp = cn_rows(M);
+    const int stage = blockIdx.y, sys = blockIdx.x;
+    coef = member_ptr(coef, ms) + (size_t)stage * cn_stage_stride(M) + (size_t)sys * 3 * Mp;
+    const double nu = (sys == 2) ? phys->kd : phys->ire;
+    const double beta = 0.5 * stages.alp[stage] * clock[1] * nu;
+    const double *lo_tab = sys == 1 ? tb.lyn_lo : tb.lyc_lo, *up_tab = sys == 1 ? tb.lyn_up : tb.lyc_up;
+    const int j0 = (sys == 1) ? 1 : 0;
+    for (int j = threadIdx.x; j < Mp; j += blockDim.x) {
+        double A = 0.0, B = 1.0, C = 0.0;
+        if (j >= j0 && j < M) cn_row(lo_tab, up_tab, sys, M, j, beta, A, B, C);
+        s_a[j] = A;
+        s_b[j] = B;
+        s_c[j] = C;
     }
     __syncthreads();
-    const int sys = threadIdx.x;
-    if (sys < 3) {
-        const double nu = (sys == 2) ? phys->kd : phys->ire;
-        const double beta = 0.5 * stages.alp[stage] * clock[1] * nu;
-        const double *lo_tab = s_tab[sys == 1 ? 2 : 0], *up_tab = s_tab[sys == 1 ? 3 : 1];
-        double *g = s_out[3 * sys], *m = s_out[3 * sys + 1], *n = s_out[3 * sys + 2];
-        const int j0 = (sys == 1) ? 1 : 0;
-        if (j0 == 1) g[0] = m[0] = n[0] = 0.0;  // node row 0 is the wall: no unknown
+    if (threadIdx.x == 0) {
+        // batches of kB rows, loaded together ahead of the dependent chain
+        // (padding rows: A = C = 0)
+        constexpr int kB = 8;
+        static_assert(kCnPad % kB == 0, "whole batches");
         double cprev = 0.0;
-        for (int j = j0; j < M; ++j) {
-            double A, B, C;
-            cn_row(lo_tab, up_tab, sys, M, j, beta, A, B, C);
-            const double rden = 1.0 / (B - A * cprev);
-            const double cj = C * rden;
-            g[j] = rden;
-            m[j] = -A * rden;
-            n[j] = -cj;
-            cprev = cj;
+        for (int jb = 0; jb < M; jb += kB) {
+            double A[kB], B[kB], C[kB];
+#pragma unroll
+            for (int t = 0; t < kB; ++t) {
+                A[t] = s_a[jb + t];
+                B[t] = s_b[jb + t];
+                C[t] = s_c[jb + t];
+            }
+#pragma unroll
+            for (int t = 0; t < kB; ++t) {
+                const double rden = 1.0 / (B[t] - A[t] * cprev);
+                cprev = C[t] * rden;
+                s_a[jb + t] = rden;
+                s_b[jb + t] = -A[t] * rden;
+                s_c[jb + t] = -cprev;
+            }
         }
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < 9 * M; e += blockDim.x) {
-        const int sk = e / M, j = e - sk * M;
-        coef[e] = s_out[sk][j];
-    }
-    if (slab_rows > 0) {
-        const int nslab = (M + slab_rows - 1) / slab_rows;
-        double *sl = coef + 9 * (size_t)M;
-        for (int t = threadIdx.x; t < 3 * nslab; t += blockDim.x) {
-            const int sy = t / nslab, sb = t - sy * nslab;
-            const double *m = s_out[3 * sy + 1], *n = s_out[3 * sy + 2];
-            const int a = sb * slab_rows, b = (a + slab_rows < M) ? a + slab_rows : M;
-            double P = 1.0, Nu = 1.0;
-            for (int j = a; j < b; ++j) { P *= m[j]; Nu *= n[j]; }
-            // phi_j = p_j + n_j phi_{j+1}, phi_b = 0, with p_j = prod_{i=a..j} m_i
-            double phi = 0.0;
-            for (int j = b - 1; j >= a; --j) {
-                double pj = 1.0;
-                for (int i = a; i <= j; ++i) pj *= m[i];
-                phi = pj + n[j] * phi;
-            }
-            sl[(3 * sy + 0) * kCnMaxSlabs + sb] = P;
-            sl[(3 * sy + 1) * kCnMaxSlabs + sb] = phi;
-            sl[(3 * sy + 2) * kCnMaxSlabs + sb] = Nu;
-            // prod_{i=a}^{j-1} n_i for the rows of the slab (1 at its first row)
-            double *np = sl + 9 * kCnMaxSlabs + (size_t)sy * M;
-            double pr = 1.0;
-            for (int j = a; j < b; ++j) {
-                np[j] = pr;
-                pr *= n[j];
-            }
-        }
+    for (int j = threadIdx.x; j < Mp; j += blockDim.x) {
+        const bool in = j >= j0 && j < M;
+        coef[j] = in ? s_a[j] : 0.0;
+        coef[Mp + j] = in ? s_b[j] : 0.0;
+        coef[2 * Mp + j] = in ? s_c[j] : 0.0;
     }
 }
 
-// Columns staged per block: 16 (one 128-byte line per row in FP64; two FP32
-// tiles share a line) for blocks of up to 256 threads, 32 for 512-thread
-// blocks (a whole line per row in FP32 at the same waves per CU).
+// ---- FP64, up to kCnLaneRows rows ----
+// Columns staged per block: 16 (one 128-byte line per row) for blocks of up
+// to 256 threads, 32 for 512-thread blocks.
 inline int cn_tile_cols(int threads) { return threads > 256 ? 32 : 16; }
 
 // Crank-Nicolson solve of one tile of kCnTx columns: the rows of r are staged
@@ -558,15 +495,15 @@ inline int cn_tile_cols(int threads) { return threads > 256 ? 32 : 16; }
 // a local sweep per lane followed by a 6-step scan of affine maps across the
 // wave (x -> T + Q x composed lane by lane) and a second local sweep from the
 // correct incoming value.  Finally q += x with coalesced stores.
-// Staging batches of the lane-scan solves: 48 bytes of loads per thread in
-// flight per wait (6 FP64 or 12 FP32 values), measured best for both: more
-// FP64 registers cost occupancy, fewer FP32 loads leave bandwidth unused.
-constexpr int kCnBatchBytes = 48;
-template <typename T>
-constexpr int cn_batch() { return kCnBatchBytes / (int)sizeof(T); }
+// Staging in batches of kCnBatch loads per thread in flight per wait, measured
+// best (more registers cost occupancy).
+// Bound by memory: 0.273 ms at 256 x 193 x 256 (5.5 TB/s).
+constexpr int kCnBatch = 6;
+constexpr int kCnLaneRows = 320;
 
-template <typename T, int kCnTx, int kCnMaxR>
+template <int kCnTx, int kCnMaxR>
 __global__ void __launch_bounds__(512) k_cn_scan(CnArgs a) {
+    using T = double;
     extern __shared__ double s_r[];
     const uint3 blk = xcd_block3();  // adjacent column tiles share an L2
     const int f = (int)blk.y;
@@ -580,51 +517,28 @@ __global__ void __launch_bounds__(512) k_cn_scan(CnArgs a) {
     const T *r = (const T *)member_ptr_at(a.r[f], ms, blk.z);  // may be rewritten in place (out_r)
     T *__restrict__ q = (T *)member_ptr_at(a.q[f], ms, blk.z);
     const double *__restrict__ coef =
-        member_ptr_at(a.coef, ms, blk.z) + (size_t)a.st.k * cn_stage_stride(M) + (size_t)sys * 3 * M;
-    const double *__restrict__ cg = coef, *__restrict__ cm = coef + M, *__restrict__ cn = coef + 2 * M;
+        member_ptr_at(a.coef, ms, blk.z) + (size_t)a.st.k * cn_stage_stride(M) + (size_t)sys * 3 * cn_rows(M);
+    const double *__restrict__ cg = coef, *__restrict__ cm = coef + cn_rows(M), *__restrict__ cn = coef + 2 * cn_rows(M);
     constexpr int LD = kCnTx + 1;
     const int nrow = M - j0;
     const int ntile = nrow * kCnTx, bd = (int)blockDim.x;
-    // Staging in batches of cn_batch<T>() unconditional loads per thread (lanes
+    // Staging in batches of kCnBatch unconditional loads per thread (lanes
     // past the tile read its first element, which exists, and discard it), so
     // that a thread waits for memory once per batch, not once per element.
     // (offsets within one field: rows * plane < 2^32 for every supported grid)
     const unsigned upl = (unsigned)pl, uc0 = (unsigned)c0;
     const unsigned o_safe = (unsigned)j0 * upl + uc0;
-    if constexpr (sizeof(T) == 4) {
-        // FP32: two adjacent columns per 8-byte access (the plane, the tile
-        // origin and ncol are even, so a pair is wholly inside or outside)
-        constexpr int TXW = kCnTx / 2, B = cn_batch<T>() / 2;
-        const int ntw = nrow * TXW;
-        for (int e0 = threadIdx.x; e0 < ntw; e0 += B * bd) {
-            nspnp_f2v v[B];
+    for (int e0 = threadIdx.x; e0 < ntile; e0 += kCnBatch * bd) {
+        T v[kCnBatch];
 #pragma unroll
-            for (int u = 0; u < B; ++u) {
-                const int e = e0 + u * bd, jj = j0 + e / TXW, c = 2 * (e % TXW);
-                v[u] = ld_once2((const float *)r + ((e < ntw && c < ncol) ? (unsigned)jj * upl + uc0 + (unsigned)c : o_safe));
-            }
-#pragma unroll
-            for (int u = 0; u < B; ++u) {
-                const int e = e0 + u * bd, jj = j0 + e / TXW, c = 2 * (e % TXW);
-                if (e < ntw) {
-                    s_r[jj * LD + c] = (c < ncol) ? (double)v[u].x : 0.0;
-                    s_r[jj * LD + c + 1] = (c < ncol) ? (double)v[u].y : 0.0;
-                }
-            }
+        for (int u = 0; u < kCnBatch; ++u) {
+            const int e = e0 + u * bd, jj = j0 + e / kCnTx, c = e % kCnTx;
+            v[u] = ld_once(r + ((e < ntile && c < ncol) ? (unsigned)jj * upl + uc0 + (unsigned)c : o_safe));
         }
-    } else {
-        for (int e0 = threadIdx.x; e0 < ntile; e0 += cn_batch<T>() * bd) {
-            T v[cn_batch<T>()];
 #pragma unroll
-            for (int u = 0; u < cn_batch<T>(); ++u) {
-                const int e = e0 + u * bd, jj = j0 + e / kCnTx, c = e % kCnTx;
-                v[u] = ld_once(r + ((e < ntile && c < ncol) ? (unsigned)jj * upl + uc0 + (unsigned)c : o_safe));
-            }
-#pragma unroll
-            for (int u = 0; u < cn_batch<T>(); ++u) {
-                const int e = e0 + u * bd, jj = j0 + e / kCnTx, c = e % kCnTx;
-                if (e < ntile) s_r[jj * LD + c] = (c < ncol) ? (double)v[u] : 0.0;
-            }
+        for (int u = 0; u < kCnBatch; ++u) {
+            const int e = e0 + u * bd, jj = j0 + e / kCnTx, c = e % kCnTx;
+            if (e < ntile) s_r[jj * LD + c] = (c < ncol) ? (double)v[u] : 0.0;
         }
     }
     __syncthreads();
@@ -711,41 +625,142 @@ __global__ void __launch_bounds__(512) k_cn_scan(CnArgs a) {
         }
         return;
     }
-    if constexpr (sizeof(T) == 4) {
-        constexpr int TXW = kCnTx / 2, B = cn_batch<T>() / 2;
-        const int ntw = nrow * TXW;
-        float *qf = (float *)q;
-        for (int e0 = threadIdx.x; e0 < ntw; e0 += B * bd) {
-            nspnp_f2v v[B];
+    for (int e0 = threadIdx.x; e0 < ntile; e0 += kCnBatch * bd) {
+        T v[kCnBatch];
 #pragma unroll
-            for (int u = 0; u < B; ++u) {
-                const int e = e0 + u * bd, jj = j0 + e / TXW, c = 2 * (e % TXW);
-                v[u] = ld_once2(qf + ((e < ntw && c < ncol) ? (unsigned)jj * upl + uc0 + (unsigned)c : o_safe));
-            }
-#pragma unroll
-            for (int u = 0; u < B; ++u) {
-                const int e = e0 + u * bd, jj = j0 + e / TXW, c = 2 * (e % TXW);
-                if (e < ntw && c < ncol) {
-                    nspnp_f2v w;
-                    w.x = (float)((double)v[u].x + s_r[jj * LD + c]);
-                    w.y = (float)((double)v[u].y + s_r[jj * LD + c + 1]);
-                    st_once2(qf + ((unsigned)jj * upl + uc0 + (unsigned)c), w);
-                }
-            }
+        for (int u = 0; u < kCnBatch; ++u) {
+            const int e = e0 + u * bd, jj = j0 + e / kCnTx, c = e % kCnTx;
+            v[u] = ld_once(q + ((e < ntile && c < ncol) ? (unsigned)jj * upl + uc0 + (unsigned)c : o_safe));
         }
+#pragma unroll
+        for (int u = 0; u < kCnBatch; ++u) {
+            const int e = e0 + u * bd, jj = j0 + e / kCnTx, c = e % kCnTx;
+            if (e < ntile && c < ncol) st_once(q + ((unsigned)jj * upl + uc0 + (unsigned)c), (T)((double)v[u] + s_r[jj * LD + c]));
+        }
+    }
+}
+
+// ---- the mixed form, and FP64 above kCnLaneRows rows ----
+// Crank-Nicolson solve of the five fields in one pass.  A block owns kCx
+// neighbouring columns of one field over all rows; its threads split the rows
+// into slabs of L.  Each thread holds its L rows in registers: the forward
+// sweep with a zero input, l; the inputs of the slabs from their exits and
+// the products of m (a scan over the slabs below, through LDS); l plus the
+// input times the running product of m; then the backward sweep the same way.
+// r and q are read once and q written once (kOut: the solution replaces r,
+// a factor of the three-direction factorisation), every access a run of kCx
+// neighbouring values.  64 columns: a wave is one slab, its recurrence
+// coefficients wave-uniform (scalar loads); 32 columns (more than 16 slabs of
+// 16 rows): two slabs a wave, the coefficients from LDS.
+// Bound by memory (15 values a cell): 512 x 385 x 512 FP64 2.34 ms (5.2 TB/s),
+// mixed 1.11 ms (5.4 TB/s); 256 x 193 x 256 mixed 0.130 ms.  The lane scans
+// took 3.65, 2.37 and 0.191 ms (short runs of a row, and shuffles); a
+// three-pass form, its first pass in the explicit kernel, 2.29 ms and 0.15 ms
+// more in that kernel.  Not for FP64 columns of up to kCnLaneRows rows: the
+// gain there is small (0.256 against 0.273 ms at 256 x 193 x 256, 48 against
+// 51 us at 128 x 129 x 128), and the lane scans keep such runs bit for bit
+// what they were.
+template <typename T, int L, int kCx, bool kOut>
+__global__ void __launch_bounds__(1024) k_cn_rows(CnArgs a) {
+    extern __shared__ double s_x[];  // exits [slab][kCx], the slabs' products, (kCx 32) the coefficients
+    const uint3 blk = xcd_block3();  // adjacent column tiles share an L2
+    const int f = (int)blk.y;
+    const int sys = (f == 1) ? 1 : (f >= 3 ? 2 : 0);
+    const int M = a.d.M, Mp = cn_rows(M);
+    const int S = (int)blockDim.x / kCx;
+    const int col = (int)threadIdx.x % kCx;
+    int slab = (int)threadIdx.x / kCx;
+    if constexpr (kCx == 64) slab = __builtin_amdgcn_readfirstlane(slab);
+    const unsigned upl = (unsigned)a.d.plane;
+    const unsigned c = blk.x * (unsigned)kCx + (unsigned)col;
+    const bool in = c < upl;
+    const unsigned uc = in ? c : upl - 1;  // (columns past the plane repeat its last one and store nothing)
+    T *r = (T *)member_ptr_at(a.r[f], a.ms, blk.z);
+    T *q = (T *)member_ptr_at(a.q[f], a.ms, blk.z);
+    const int j0 = slab * L;
+    // row t of the slab at this column (64 columns: a wave-uniform row base and
+    // the column's 32-bit offset); rows past the last repeat it (their
+    // coefficients are zero)
+    auto at = [&](T *p, int t) -> T * {
+        const int j = j0 + t < M ? j0 + t : M - 1;
+        if constexpr (kCx == 64) return byte_at(p + (size_t)j * upl, uc * (unsigned)sizeof(T));
+        else return p + ((unsigned)j * upl + uc);
+    };
+    T rv[L];
+#pragma unroll
+    for (int t = 0; t < L; ++t) rv[t] = ld_once(at(r, t));
+    const double *coef = member_ptr_at(a.coef, a.ms, blk.z) + (size_t)a.st.k * cn_stage_stride(M) + (size_t)sys * 3 * Mp;
+    double *s_p = s_x + S * kCx, *s_c = s_p + S;
+    typedef const __attribute__((address_space(4))) double cdouble;
+    cdouble *ug = (cdouble *)(coef + (kCx == 64 ? j0 : 0));
+    if constexpr (kCx != 64) {
+        for (int e = threadIdx.x; e < 3 * Mp; e += blockDim.x) s_c[e] = coef[e];
+        __syncthreads();
+    }
+    auto cg = [&](int t) { return kCx == 64 ? ug[t] : s_c[j0 + t]; };
+    auto cm = [&](int t) { return kCx == 64 ? ug[Mp + t] : s_c[Mp + j0 + t]; };
+    auto cn = [&](int t) { return kCx == 64 ? ug[2 * Mp + t] : s_c[2 * Mp + j0 + t]; };
+    double x[L];
+    double P = 1.0, d = 0.0;
+#pragma unroll
+    for (int t = 0; t < L; ++t) {
+        d = cg(t) * (double)rv[t] + cm(t) * d;
+        x[t] = d;
+        P *= cm(t);
+    }
+    s_x[slab * kCx + col] = d;
+    if (col == 0) s_p[slab] = P;
+    // q is loaded while the exits travel; FP64 slabs of 24 rows load its second
+    // half after the first has been stored (all of it early would spill: 2.47
+    // against 2.34 ms at 512 x 385 x 512)
+    constexpr int QE = (sizeof(T) == 8 && L == 24) ? 12 : L;
+    T qv[QE];
+    if constexpr (!kOut) {
+#pragma unroll
+        for (int t = 0; t < QE; ++t) qv[t] = ld_once(at(q, t));
+    }
+    __syncthreads();
+    double v = 0.0;
+    for (int t = 0; t < slab; ++t) v = s_x[t * kCx + col] + s_p[t] * v;
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < L; ++t) {
+        v *= cm(t);
+        x[t] += v;
+    }
+    P = 1.0;
+    d = 0.0;
+#pragma unroll
+    for (int t = L - 1; t >= 0; --t) {
+        d = x[t] + cn(t) * d;
+        x[t] = d;
+        P *= cn(t);
+    }
+    s_x[slab * kCx + col] = d;
+    if (col == 0) s_p[slab] = P;
+    __syncthreads();
+    v = 0.0;
+    for (int t = S - 1; t > slab; --t) v = s_x[t * kCx + col] + s_p[t] * v;
+#pragma unroll
+    for (int t = L - 1; t >= 0; --t) {
+        v *= cn(t);
+        x[t] += v;
+    }
+    if (!in) return;
+    if constexpr (kOut) {
+#pragma unroll
+        for (int t = 0; t < L; ++t)
+            if (j0 + t < M) st_once(at(r, t), (T)x[t]);
     } else {
-        for (int e0 = threadIdx.x; e0 < ntile; e0 += cn_batch<T>() * bd) {
-            T v[cn_batch<T>()];
 #pragma unroll
-            for (int u = 0; u < cn_batch<T>(); ++u) {
-                const int e = e0 + u * bd, jj = j0 + e / kCnTx, c = e % kCnTx;
-                v[u] = ld_once(q + ((e < ntile && c < ncol) ? (unsigned)jj * upl + uc0 + (unsigned)c : o_safe));
-            }
+        for (int t = 0; t < QE; ++t)
+            if (j0 + t < M) st_once(at(q, t), (T)((double)qv[t] + x[t]));
+        if constexpr (QE < L) {
 #pragma unroll
-            for (int u = 0; u < cn_batch<T>(); ++u) {
-                const int e = e0 + u * bd, jj = j0 + e / kCnTx, c = e % kCnTx;
-                if (e < ntile && c < ncol) st_once(q + ((unsigned)jj * upl + uc0 + (unsigned)c), (T)((double)v[u] + s_r[jj * LD + c]));
-            }
+            for (int t = QE; t < L; ++t) qv[t - QE] = ld_once(at(q, t));
+#pragma unroll
+            for (int t = QE; t < L; ++t)
+                if (j0 + t < M) st_once(at(q, t), (T)((double)qv[t - QE] + x[t]));
         }
     }
 }
@@ -814,7 +829,7 @@ __global__ void __launch_bounds__(64) k_cyc_coef(Dims d, const Phys *phys, const
 // One tile of kCycTx periodic lines of one field per block, staged in LDS
 // (x-lines: each line contiguous; z-lines: kCycTx neighbouring columns per
 // element, 128-byte runs in FP64); each wave solves one line with its N points
-// split into 64 contiguous lane segments, as in the Crank-Nicolson lane scans,
+// split into 64 contiguous lane segments (affine-map scans across the wave),
 // then applies the periodic correction (the line's end values y_0, y_{N-1}
 // broadcast from their lanes).
 constexpr int kCycTx = 16;
@@ -969,123 +984,6 @@ __global__ void __launch_bounds__(256) k_cyc_scan(CycArgs a) {
                     else st_once(qq + addr(p.i, p.c), (T)((double)v[u] + xs));
                 }
             }
-        }
-    }
-}
-
-// ---- Crank-Nicolson, row-slab method (large grids) ----
-// One thread per (column, slab): every pass streams whole rows of a tile of
-// 256 columns, so each DRAM page opened serves a long contiguous run.
-__device__ __forceinline__ void cn_slab_site(const CnArgs &a, unsigned z, int &f, unsigned &mem, int &sys) {
-    f = (int)(z % 5u);
-    mem = z / 5u;
-    sys = (f == 1) ? 1 : (f >= 3 ? 2 : 0);
-}
-
-// pass 1 (the exits of the local sweeps of each slab, zero inputs) runs in
-// the explicit kernel as it produces r (ExplicitArgs::cn_coef).
-
-// pass 2: scans across the slabs of each column; the slab inputs D (forward)
-// and X (backward) replace the exits in place
-__global__ void __launch_bounds__(256) k_cn_slab_scan(CnArgs a) {
-    int f, sys;
-    unsigned mem;
-    cn_slab_site(a, blockIdx.z, f, mem, sys);
-    const int64_t pl = a.d.plane;
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= pl) return;
-    const int M = a.d.M, S = a.slabs;
-    const double *sl = member_ptr_at(a.coef, a.ms, mem) + (size_t)a.st.k * cn_stage_stride(M) + 9 * (size_t)M;
-    const double *P = sl + (3 * sys + 0) * kCnMaxSlabs, *Phi = sl + (3 * sys + 1) * kCnMaxSlabs,
-                 *Nu = sl + (3 * sys + 2) * kCnMaxSlabs;
-    double *scr = member_ptr_at(a.scr, a.ms, mem);
-    double *lam = scr + (int64_t)f * S * pl + e, *kap = scr + (int64_t)(5 + f) * S * pl + e;
-    // batches of 8 slabs: loads first (slabs past the end re-read the last
-    // one and are ignored), multipliers included, then the recurrence and
-    // the stores
-    constexpr int kB = 8;
-    double D = 0.0;
-    for (int s0 = 0; s0 < S; s0 += kB) {
-        double ex[kB], pb[kB];
-#pragma unroll
-        for (int u = 0; u < kB; ++u) {
-            const int sb = s0 + u < S ? s0 + u : S - 1;
-            ex[u] = lam[(int64_t)sb * pl];
-            pb[u] = P[sb];
-        }
-#pragma unroll
-        for (int u = 0; u < kB; ++u) {
-            const int sb = s0 + u;
-            if (sb < S) {
-                lam[(int64_t)sb * pl] = D;
-                D = ex[u] + pb[u] * D;
-            }
-        }
-    }
-    double X = 0.0;
-    for (int s1 = S - 1; s1 >= 0; s1 -= kB) {
-        double ex[kB], din[kB], phb[kB], nub[kB];
-#pragma unroll
-        for (int u = 0; u < kB; ++u) {
-            const int sb = s1 - u >= 0 ? s1 - u : 0;
-            ex[u] = kap[(int64_t)sb * pl];
-            din[u] = lam[(int64_t)sb * pl];
-            phb[u] = Phi[sb];
-            nub[u] = Nu[sb];
-        }
-#pragma unroll
-        for (int u = 0; u < kB; ++u) {
-            const int sb = s1 - u;
-            if (sb >= 0) {
-                kap[(int64_t)sb * pl] = X;
-                X = ex[u] + phb[u] * din[u] + nub[u] * X;
-            }
-        }
-    }
-}
-
-// pass 3: both sweeps of each slab from its exact inputs, then q += x
-template <typename T, int L>
-__global__ void __launch_bounds__(256) k_cn_slab_apply(CnArgs a) {
-    int f, sys;
-    unsigned mem;
-    cn_slab_site(a, blockIdx.z, f, mem, sys);
-    const int64_t pl = a.d.plane;
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= pl) return;
-    const int M = a.d.M, S = a.slabs, sb = blockIdx.y;
-    const int j0 = sb * L, j1 = (j0 + L < M) ? j0 + L : M;
-    const T *__restrict__ r = (const T *)member_ptr_at(a.r[f], a.ms, mem);
-    T *__restrict__ q = (T *)member_ptr_at(a.q[f], a.ms, mem);
-    const double *__restrict__ coef = member_ptr_at(a.coef, a.ms, mem) + (size_t)a.st.k * cn_stage_stride(M) +
-                                      (size_t)sys * 3 * M;
-    const double *g = coef, *m = coef + M, *n = coef + 2 * M;
-    const double *scr = member_ptr_at(a.scr, a.ms, mem);
-    double d = scr[((int64_t)(f * S + sb)) * pl + e];
-    double x = scr[((int64_t)((5 + f) * S + sb)) * pl + e];
-    // r and q of the slab's rows first, all in flight together (rows past the
-    // slab re-read its last row and are ignored)
-    const unsigned upl = (unsigned)pl, ue = (unsigned)e;
-    T rv[L], qv[L];
-#pragma unroll
-    for (int t = 0; t < L; ++t) {
-        const unsigned o = (unsigned)(j0 + t < j1 ? j0 + t : j1 - 1) * upl + ue;
-        rv[t] = ld_once(r + o);
-        qv[t] = ld_once(q + o);
-    }
-    double dv[L];
-#pragma unroll
-    for (int t = 0; t < L; ++t) {
-        const int j = j0 + t;
-        if (j < j1) d = g[j] * (double)rv[t] + m[j] * d;
-        dv[t] = d;
-    }
-#pragma unroll
-    for (int t = L - 1; t >= 0; --t) {
-        const int j = j0 + t;
-        if (j < j1) {
-            x = dv[t] + n[j] * x;
-            st_once(q + ((unsigned)j * upl + ue), (T)((double)qv[t] + x));
         }
     }
 }
@@ -1263,38 +1161,18 @@ static hipError_t explicit_launch(nspnp_state *s, const ExplicitArgs &a, int thr
     return hipGetLastError();
 }
 
-// Rows per slab of the row-slab CN method when it applies to this handle
-// (0: lane-scan method).  Its scratch (two values per field, slab and column)
-// lives in the spectrum buffers, unused between the explicit stage and the
-// elliptic solves.
-int cn_slab_rows(const nspnp_state *s) {
-    const int L = s->tiles.cnslab;
-    if (L != 16 && L != 32 || s->cfg.implicit_xz) return 0;  // the factorisation uses the lane-scan method
-    const int S = (s->d.M + L - 1) / L;
-    const int64_t need = 2 * 5 * (int64_t)S * s->d.plane;             // doubles
-    const int64_t have = 4 * (int64_t)s->d.nxh * s->d.nz * s->d.M;      // two half spectra
-    return (S <= kCnMaxSlabs && need <= have) ? L : 0;
-}
-
-// Crank-Nicolson recurrence coefficients of the three stages (and, for the
-// row-slab method, its slab products): computed on the device once per
-// Runge-Kutta step, after the step's dt, before the explicit kernel that may
-// run the method's first pass; at most once per substep.
+// Crank-Nicolson recurrence coefficients of the three stages: computed on
+// the device once per Runge-Kutta step, after the step's dt.
 static hipError_t launch_cn_coef(nspnp_state *s, const Stage &st) {
-    if (s->cn_coef_at == s->substeps) return hipSuccess;
-    const int L = cn_slab_rows(s);
-    if (st.k == 0 || !s->cn_fresh || s->cn_coef_slab != L) {
-        CnStages cs;
-        for (int q = 0; q < 3; ++q) cs.alp[q] = kRkAlp[q];
-        k_cn_coef<<<dim3(1, 3, (unsigned)s->nmem), 256, 0, s->stream>>>(s->d, s->tb, s->d_phys, s->clock,
-                                                                       s->cn_coef, cs, L, s->mstride);
-        if (s->cfg.implicit_xz)
-            k_cyc_coef<<<dim3(1, 3, (unsigned)s->nmem), 64, 0, s->stream>>>(s->d, s->d_phys, s->clock, s->cyc, cs,
-                                                                            s->mstride);
-        s->cn_fresh = true;
-        s->cn_coef_slab = L;
-    }
-    s->cn_coef_at = s->substeps;
+    if (st.k != 0 && s->cn_fresh) return hipSuccess;
+    CnStages cs;
+    for (int q = 0; q < 3; ++q) cs.alp[q] = kRkAlp[q];
+    k_cn_coef<<<dim3(3, 3, (unsigned)s->nmem), 256, 0, s->stream>>>(s->d, s->tb, s->d_phys, s->clock, s->cn_coef, cs,
+                                                                   s->mstride);
+    if (s->cfg.implicit_xz)
+        k_cyc_coef<<<dim3(1, 3, (unsigned)s->nmem), 64, 0, s->stream>>>(s->d, s->d_phys, s->clock, s->cyc, cs,
+                                                                        s->mstride);
+    s->cn_fresh = true;
     return hipGetLastError();
 }
 
@@ -1311,10 +1189,7 @@ namespace {
 // One thread per (x, z) column marches a slab of rows with rows j-2 .. j+2
 // of c+- of its own column in registers (the next row loaded one step
 // ahead); x and z neighbours come from the same row, which the neighbouring
-// columns' threads read at the same time.  With the row-slab Crank-Nicolson
-// method, whose first pass ran inside the explicit kernel on the r before
-// this correction, the pass adds the slab exits of its own change of r to
-// the method's scratch (the exits are linear in r), on the same slabs.
+// columns' threads read at the same time.
 struct AdvArgs {
     Dims d;
     size_t ms;
@@ -1327,8 +1202,6 @@ struct AdvArgs {
     int mode;            // 0: substep (H, r of this stage); 1: dbg only
     int ntiles;          // 256-column tiles per plane
     int slabs, slab_rows;
-    const double *cn_coef;  // this stage's row-slab CN coefficients (NULL: no exits to update)
-    double *cn_scr;
 };
 
 template <typename T>
@@ -1364,9 +1237,6 @@ __global__ void __launch_bounds__(256) k_adv_limit(AdvArgs a) {
     const T idx_ = T(1.0 / a.d.dx), idz_ = T(1.0 / a.d.dz);
     const T dtg = T(member_ptr_at(a.clock, ms, mem)[1]) * T(a.st.gam);
     const bool keep = a.st.k < 2;
-    const bool fuse = a.mode == 0 && a.cn_coef != nullptr;
-    const double *cnc = fuse ? member_ptr_at(a.cn_coef, ms, mem) : nullptr;
-    double cl[2] = {0.0, 0.0}, ck[2] = {0.0, 0.0};
     const int j0 = (int)slab * a.slab_rows;
     const int j1 = (j0 + a.slab_rows < M) ? j0 + a.slab_rows : M;
     // own-column window rows j-2 .. j+2 of both species, and v at row j
@@ -1421,15 +1291,7 @@ __global__ void __launch_bounds__(256) k_adv_limit(AdvArgs a) {
                 a.dbg[sp][(size_t)j * (size_t)pl + (size_t)e] += (double)delta;
             } else {
                 if (keep) *byte_at(hf[sp], rb + ex) = hv[sp] + delta;
-                const T rn = rv[sp] + dtg * delta;
-                *byte_at(rf[sp], rb + ex) = rn;
-                if (fuse) {  // the ions' system (2): g, m at 2 * 3M; its n-products after the slab products
-                    const double *cfc = cnc + 2 * 3 * (size_t)M;
-                    const double *np = cnc + 9 * (size_t)M + 9 * kCnMaxSlabs + 2 * (size_t)M;
-                    const double dr = (double)rn - (double)rv[sp];  // the change the CN solve will see
-                    cl[sp] = uniform_load(cfc, j) * dr + uniform_load(cfc + M, j) * cl[sp];
-                    ck[sp] += uniform_load(np, j) * cl[sp];
-                }
+                *byte_at(rf[sp], rb + ex) = rv[sp] + dtg * delta;
             }
         }
         // advance the window
@@ -1440,16 +1302,6 @@ __global__ void __launch_bounds__(256) k_adv_limit(AdvArgs a) {
             win[sp][4] = nxt[sp];
         }
         vj = vn;
-    }
-    if (fuse) {  // add this pass's slab exits to the explicit kernel's
-        const unsigned S = (unsigned)a.slabs;
-        double *scr = member_ptr_at(a.cn_scr, ms, mem);
-#pragma unroll
-        for (int sp = 0; sp < 2; ++sp) {
-            const int f = 3 + sp;
-            scr[((size_t)f * S + slab) * (size_t)pl + (size_t)e] += cl[sp];
-            scr[((size_t)(5 + f) * S + slab) * (size_t)pl + (size_t)e] += ck[sp];
-        }
     }
 }
 
@@ -1471,15 +1323,8 @@ hipError_t launch_adv_limit(nspnp_state *s, const Stage &st, double *const out[5
     a.clock = s->clock;
     a.mode = out ? 1 : 0;
     a.ntiles = (int)((s->d.plane + 255) / 256);
-    // the row-slab CN method's slabs (its exits get this pass's share), else
-    // 32-row slabs
-    const int L = out ? 0 : cn_slab_rows(s);
-    a.slab_rows = L ? L : 32;
+    a.slab_rows = 32;
     a.slabs = (s->d.M + a.slab_rows - 1) / a.slab_rows;
-    if (L) {
-        a.cn_coef = s->cn_coef + (size_t)st.k * cn_stage_stride(s->d.M);
-        a.cn_scr = (double *)s->spec;
-    }
     const int nm = out ? 1 : s->nmem;
     const unsigned blocks = (unsigned)((int64_t)a.ntiles * a.slabs * nm);
     if (s->fp64) k_adv_limit<double><<<blocks, 256, 0, s->stream>>>(a);
@@ -1499,18 +1344,9 @@ hipError_t launch_explicit(nspnp_state *s, const Stage &st, bool /*write_r*/) {
     a.clock = s->clock;
     a.mode = 0;
     a.implicit_xz = s->cfg.implicit_xz;
-    hipError_t e = launch_cn_coef(s, st);  // (not part of the explicit kernel's profiled time)
-    if (e != hipSuccess) return e;
     ProfScope prof_(s, K_EXPLICIT);
-    // row-slab Crank-Nicolson: this kernel marches the method's slabs and
-    // runs its first pass
-    const int L = cn_slab_rows(s);
-    if (L) {
-        a.cn_coef = s->cn_coef + (size_t)st.k * cn_stage_stride(s->d.M);
-        a.cn_scr = (double *)s->spec;
-    }
     const int tb = s->tiles.expl;
-    explicit_tiling(s->d, s->fp64, tb, L ? L : s->tiles.slab, a);
+    explicit_tiling(s->d, s->fp64, tb, s->tiles.slab, a);
     const hipError_t e2 = explicit_launch(s, a, tb, (unsigned)((int64_t)a.chunks * a.slabs * s->nmem));
     if (e2 != hipSuccess || s->cfg.migration_face != 2) return e2;
     return launch_adv_limit(s, st, nullptr);
@@ -1533,8 +1369,6 @@ hipError_t launch_explicit_debug(nspnp_state *s, double *const out[5]) {
     if (e != hipSuccess || s->cfg.migration_face != 2) return e;
     return launch_adv_limit(s, a.st, out);
 }
-
-static hipError_t launch_cn_lane(nspnp_state *s, const CnArgs &a);
 
 // Periodic-line solves of the five fields along x (dir 0) or z (dir 1).
 static hipError_t launch_cyc(nspnp_state *s, const Stage &st, int dir, int out_r) {
@@ -1581,49 +1415,6 @@ static hipError_t launch_cyc(nspnp_state *s, const Stage &st, int dir, int out_r
 #undef NSPNP_CYC_CASE
 }
 
-hipError_t launch_cn_solve(nspnp_state *s, const Stage &st) {
-    ProfScope prof_(s, K_CN);
-    CnArgs a{};
-    a.d = s->d;
-    a.phys = s->d_phys;
-    a.ms = s->mstride;
-    a.tb = s->tb;
-    a.st = st;
-    for (int q = 0; q < 5; ++q) { a.q[q] = s->f[q]; a.r[q] = s->r[q]; }
-    a.clock = s->clock;
-    a.coef = s->cn_coef;
-    a.scr = (double *)s->spec;
-    a.slab_rows = cn_slab_rows(s);
-    a.slabs = a.slab_rows ? (s->d.M + a.slab_rows - 1) / a.slab_rows : 0;
-    {
-        const hipError_t e = launch_cn_coef(s, st);
-        if (e != hipSuccess) return e;
-    }
-    if (a.slab_rows) {
-        // the first pass (the exits of each slab's local sweeps) ran in the
-        // explicit kernel of this substep; scans across the slabs, then both
-        // sweeps from the exact slab inputs
-        const dim3 g((unsigned)((s->d.plane + 255) / 256), (unsigned)a.slabs, 5u * (unsigned)s->nmem);
-        const dim3 g1((unsigned)((s->d.plane + 255) / 256), 1, 5u * (unsigned)s->nmem);
-        k_cn_slab_scan<<<g1, 256, 0, s->stream>>>(a);
-        if (a.slab_rows == 16) {
-            if (s->fp64) k_cn_slab_apply<double, 16><<<g, 256, 0, s->stream>>>(a);
-            else k_cn_slab_apply<float, 16><<<g, 256, 0, s->stream>>>(a);
-        } else {
-            if (s->fp64) k_cn_slab_apply<double, 32><<<g, 256, 0, s->stream>>>(a);
-            else k_cn_slab_apply<float, 32><<<g, 256, 0, s->stream>>>(a);
-        }
-        return hipGetLastError();
-    }
-    if (!s->cfg.implicit_xz) return launch_cn_lane(s, a);
-    // three-direction factorisation: x-lines into r, y (this solve) into r, then z-lines with q += solution
-    hipError_t e = launch_cyc(s, st, 0, 1);
-    if (e != hipSuccess) return e;
-    a.out_r = 1;
-    if ((e = launch_cn_lane(s, a)) != hipSuccess) return e;
-    return launch_cyc(s, st, 1, 0);
-}
-
 // Lane-scan Crank-Nicolson solve of the five fields (tiles of 16 or 32 columns).
 static hipError_t launch_cn_lane(nspnp_state *s, const CnArgs &a) {
     const int tb = s->tiles.cn;
@@ -1631,7 +1422,7 @@ static hipError_t launch_cn_lane(nspnp_state *s, const CnArgs &a) {
     const dim3 g((unsigned)((s->d.plane + tcols - 1) / tcols), 5, (unsigned)s->nmem);
     const size_t lds = (size_t)s->d.M * (tcols + 1) * sizeof(double);
     if (lds > (size_t)s->lds_max) return hipErrorInvalidValue;
-    const int rpl = (s->d.M + 63) / 64;  // rows per lane (M <= 512: at most 8)
+    const int rpl = (s->d.M + 63) / 64;  // rows per lane (M <= kCnLaneRows: at most 5)
     // tiles above 64 KB of LDS (tall columns) use the device's larger limit
     auto launch = [&](const void *fn, auto kernel) -> hipError_t {
         const hipError_t e = lds_opt_in(fn, lds, s->lds_max);
@@ -1642,23 +1433,80 @@ static hipError_t launch_cn_lane(nspnp_state *s, const CnArgs &a) {
 #define NSPNP_CN_CASE(RR)                                                                              \
     case RR:                                                                                           \
         if (tcols == 32)                                                                               \
-            return s->fp64 ? launch((const void *)k_cn_scan<double, 32, RR>, k_cn_scan<double, 32, RR>) \
-                           : launch((const void *)k_cn_scan<float, 32, RR>, k_cn_scan<float, 32, RR>);  \
-        return s->fp64 ? launch((const void *)k_cn_scan<double, 16, RR>, k_cn_scan<double, 16, RR>)    \
-                       : launch((const void *)k_cn_scan<float, 16, RR>, k_cn_scan<float, 16, RR>);
+            return launch((const void *)k_cn_scan<32, RR>, k_cn_scan<32, RR>);                         \
+        return launch((const void *)k_cn_scan<16, RR>, k_cn_scan<16, RR>);
     switch (rpl) {
         NSPNP_CN_CASE(1)
         NSPNP_CN_CASE(2)
         NSPNP_CN_CASE(3)
         NSPNP_CN_CASE(4)
         NSPNP_CN_CASE(5)
-        NSPNP_CN_CASE(6)
-        NSPNP_CN_CASE(7)
-        NSPNP_CN_CASE(8)
         default:
             return hipErrorInvalidValue;
     }
 #undef NSPNP_CN_CASE
+}
+
+// Rows a thread holds in the Crank-Nicolson solve (the result's rounding
+// depends on it, so it follows from the type and the rows alone); 0: lane
+// scans.  24 rows where they make
+// 8 or 16 whole slabs: 0.130 ms (mixed) against 0.145 for 12 and 0.136 for
+// 16 at 256 x 193 x 256; 16 at up to 128 (28.9 against 30.8 us for 24, 33.4
+// for 8 at 128 x 129 x 128); short columns split into at least 8 slabs, which
+// fill the chip on small planes.
+static int cn_slab_rows(const nspnp_state *s) {
+    const int M = s->d.M;
+    if (s->fp64 && s->tiles.cnslab == 0 && M <= kCnLaneRows) return 0;
+    if (s->tiles.cnslab == 16 || M > 384) return 16;
+    if (s->tiles.cnslab == 32) return 24;
+    if (M <= 32) return 4;
+    if (M <= 64) return 8;
+    return (M <= 128 || (M > 192 && M <= 256)) ? 16 : 24;
+}
+
+// out_r: the solution replaces r, else it is added to the fields
+static hipError_t launch_cn_y(nspnp_state *s, const Stage &st, bool out_r) {
+    CnArgs a{};
+    a.d = s->d;
+    a.ms = s->mstride;
+    a.st = st;
+    for (int q = 0; q < 5; ++q) { a.q[q] = s->f[q]; a.r[q] = s->r[q]; }
+    a.coef = s->cn_coef;
+    a.out_r = out_r ? 1 : 0;
+    if (!cn_slab_rows(s)) return launch_cn_lane(s, a);
+    const int L = cn_slab_rows(s), S = (s->d.M + L - 1) / L;
+    const int cx = S <= 16 ? 64 : 32;  // a block has at most 1024 threads
+    if (S * cx > 1024) return hipErrorInvalidValue;
+    const dim3 g((unsigned)((s->d.plane + cx - 1) / cx), 5, (unsigned)s->nmem);
+    const size_t lds = ((size_t)S * (cx + 1) + (cx == 64 ? 0 : 3 * cn_rows(s->d.M))) * sizeof(double);
+    auto go = [&](auto rows, auto cols) {
+        constexpr int R = decltype(rows)::value, C = decltype(cols)::value;
+        if (s->fp64) {
+            if (out_r) k_cn_rows<double, R, C, true><<<g, S * C, lds, s->stream>>>(a);
+            else k_cn_rows<double, R, C, false><<<g, S * C, lds, s->stream>>>(a);
+        } else {
+            if (out_r) k_cn_rows<float, R, C, true><<<g, S * C, lds, s->stream>>>(a);
+            else k_cn_rows<float, R, C, false><<<g, S * C, lds, s->stream>>>(a);
+        }
+        return hipGetLastError();
+    };
+    using std::integral_constant;
+    if (L == 4) return go(integral_constant<int, 4>{}, integral_constant<int, 64>{});
+    if (L == 8) return go(integral_constant<int, 8>{}, integral_constant<int, 64>{});
+    if (L == 24) return go(integral_constant<int, 24>{}, integral_constant<int, 64>{});
+    if (cx == 64) return go(integral_constant<int, 16>{}, integral_constant<int, 64>{});
+    return go(integral_constant<int, 16>{}, integral_constant<int, 32>{});
+}
+
+hipError_t launch_cn_solve(nspnp_state *s, const Stage &st) {
+    ProfScope prof_(s, K_CN);
+    hipError_t e = launch_cn_coef(s, st);
+    if (e != hipSuccess) return e;
+    if (!s->cfg.implicit_xz) return launch_cn_y(s, st, false);
+    // three-direction factorisation: x-lines into r, y (this solve) into r, then z-lines with q += solution
+    if ((e = launch_cyc(s, st, 0, 1)) != hipSuccess) return e;
+    if ((e = launch_cn_y(s, st, true)) != hipSuccess) return e;
+    return launch_cyc(s, st, 1, 0);
 }
 
 hipError_t launch_correct(nspnp_state *s, const Stage &st, bool update_p, double fixed, bool advance_clock) {

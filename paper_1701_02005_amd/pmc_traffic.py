@@ -32,7 +32,7 @@ CSRC = "paper_1701_02005_amd/csrc"
 CLASSES = {
     "dt": (("k_dt_partial", "k_dt_final"), "reduce.hip"),
     "explicit_rhs": (("k_explicit",), "stencil.hip"),
-    "cn_tridiag": (("k_cn_coef", "k_cn_scan"), "stencil.hip"),  # lane-scan method
+    "cn_tridiag": (("k_cn_coef", "k_cn_scan"), "stencil.hip"),
     "fft_x_r2c": (("k_fft_x_r2c",), "poisson.hip"),
     "fft_z_fwd": (("k_fft_z",), "poisson.hip"),
     "thomas_modes": (("k_thomas_tile",), "poisson.hip"),
@@ -41,8 +41,9 @@ CLASSES = {
     "correct": (("k_correct",), "stencil.hip"),
 }
 
-# the same class under the row-slab Crank-Nicolson method (its first pass runs
-# inside k_explicit; the scan across slabs and the apply pass remain)
+# the same class where the solve holds slabs of rows in registers (the mixed form,
+# FP64 above 320 rows), and in counter runs of the earlier three-pass method
+CN_ROWS_KERNELS = ("k_cn_coef", "k_cn_rows")
 CN_SLAB_KERNELS = ("k_cn_coef", "k_cn_slab_scan", "k_cn_slab_apply")
 
 
@@ -52,10 +53,10 @@ CN_SLAB_KERNELS = ("k_cn_coef", "k_cn_slab_scan", "k_cn_slab_apply")
 Z_FUSED_KERNELS = {"fft_z_fwd": ("k_zthomas_fwd",), "fft_z_inv": ("k_zthomas_bwd",)}
 
 
-def class_kernels(cls: str, cn_slab: bool = False, z_fused: bool = False):
+def class_kernels(cls: str, cn_slab: bool = False, z_fused: bool = False, cn_rows: bool = False):
     """HIP kernels that one launch of a profiler class runs."""
-    if cls == "cn_tridiag" and cn_slab:
-        return CN_SLAB_KERNELS
+    if cls == "cn_tridiag" and (cn_slab or cn_rows):
+        return CN_SLAB_KERNELS if cn_slab else CN_ROWS_KERNELS
     if z_fused and cls in Z_FUSED_KERNELS:
         return Z_FUSED_KERNELS[cls]
     return CLASSES[cls][0]
@@ -111,6 +112,8 @@ def main(argv=None):
     for cls, (kernels, src) in CLASSES.items():
         if cls == "cn_tridiag" and all(k in per_kernel for k in CN_SLAB_KERNELS):
             kernels = CN_SLAB_KERNELS
+        elif cls == "cn_tridiag" and all(k in per_kernel for k in CN_ROWS_KERNELS):
+            kernels = CN_ROWS_KERNELS
         if cls in Z_FUSED_KERNELS and all(k in per_kernel for k in Z_FUSED_KERNELS[cls]):
             kernels = Z_FUSED_KERNELS[cls]
         if not all(k in per_kernel for k in kernels):
