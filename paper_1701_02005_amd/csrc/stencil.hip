@@ -187,13 +187,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves
         hold_n[f] = zero;
     }
     {
-        HaloRegs<T, kHalo> r0;
+        HaloRegs<T, kHalo> r0, r1;  // both rows in flight together (above the last row: it again, not used)
         load_rows(j0, r0);
+        load_rows(j0 + 1 < M ? j0 + 1 : j0, r1);
         store_rows(j0 & 1, r0);
-        if (j0 + 1 < M) {
-            load_rows(j0 + 1, r0);
-            store_rows((j0 + 1) & 1, r0);
-        }
+        store_rows((j0 + 1) & 1, r1);
     }
     __syncthreads();
 
@@ -1109,20 +1107,31 @@ inline dim3 grid1(int64_t n, int b = 256) { return dim3((unsigned)((n + b - 1) /
 
 }  // namespace
 
+// Rows that one block of a row march takes: `rows`, halved (not below `least`)
+// while that leaves the chip with fewer than two blocks per CU.  A march is
+// serial in its rows, about 2.7 us a row in the explicit kernel: with 16 rows
+// a 32 x 33 x 32 grid has 8 blocks and takes 44 us, with 1 row 128 blocks.
+// The results do not depend on it.
+static int march_rows(int M, int rows, int64_t columns, int least) {
+    while (rows > least && columns * ((M + rows - 1) / rows) < 512) rows = (rows + 1) / 2;
+    return rows;
+}
+
 // Column tiles of the explicit kernel: up to 64 columns along x in the mixed
 // form, 32 in FP64 (whole x-lines when nx is smaller), times as many z-lines
 // as the block has room for.  The FP64 32 x 8 tile loads 1.33 halo values
 // per cell against 1.55 for 64 x 4 (256 bytes of a row per access run);
 // the FP32 form keeps 64 columns, a whole 256-byte run of a row.
-static void explicit_tiling(const Dims &d, bool fp64, int threads, int slab_rows, ExplicitArgs &a) {
+// slab_rows is what a block marches at most (march_rows).
+static void explicit_tiling(const Dims &d, bool fp64, int threads, int slab_rows, int nmem, ExplicitArgs &a) {
     const int wx = fp64 ? 32 : 64;
     a.tx = d.nx < wx ? d.nx : wx;
     if (a.tx > threads) a.tx = threads;
     a.tz = threads / a.tx;
     a.ntx = (d.nx + a.tx - 1) / a.tx;
     a.chunks = a.ntx * ((d.nz + a.tz - 1) / a.tz);
-    a.slab_rows = slab_rows;
-    a.slabs = (d.M + slab_rows - 1) / slab_rows;
+    a.slab_rows = march_rows(d.M, slab_rows, (int64_t)a.chunks * nmem, 1);
+    a.slabs = (d.M + a.slab_rows - 1) / a.slab_rows;
 }
 
 // Launch of the explicit kernel with its halo-tile LDS ring; kHalo halo
@@ -1323,7 +1332,7 @@ hipError_t launch_adv_limit(nspnp_state *s, const Stage &st, double *const out[5
     a.clock = s->clock;
     a.mode = out ? 1 : 0;
     a.ntiles = (int)((s->d.plane + 255) / 256);
-    a.slab_rows = 32;
+    a.slab_rows = march_rows(s->d.M, 32, (int64_t)a.ntiles * (out ? 1 : s->nmem), 1);
     a.slabs = (s->d.M + a.slab_rows - 1) / a.slab_rows;
     const int nm = out ? 1 : s->nmem;
     const unsigned blocks = (unsigned)((int64_t)a.ntiles * a.slabs * nm);
@@ -1346,7 +1355,7 @@ hipError_t launch_explicit(nspnp_state *s, const Stage &st, bool /*write_r*/) {
     a.implicit_xz = s->cfg.implicit_xz;
     ProfScope prof_(s, K_EXPLICIT);
     const int tb = s->tiles.expl;
-    explicit_tiling(s->d, s->fp64, tb, s->tiles.slab, a);
+    explicit_tiling(s->d, s->fp64, tb, s->tiles.slab, s->nmem, a);
     const hipError_t e2 = explicit_launch(s, a, tb, (unsigned)((int64_t)a.chunks * a.slabs * s->nmem));
     if (e2 != hipSuccess || s->cfg.migration_face != 2) return e2;
     return launch_adv_limit(s, st, nullptr);
@@ -1364,7 +1373,7 @@ hipError_t launch_explicit_debug(nspnp_state *s, double *const out[5]) {
     a.clock = s->clock;
     a.mode = 1;
     a.implicit_xz = s->cfg.implicit_xz;
-    explicit_tiling(s->d, s->fp64, 256, s->tiles.slab, a);
+    explicit_tiling(s->d, s->fp64, 256, s->tiles.slab, 1, a);
     const hipError_t e = explicit_launch(s, a, 256, (unsigned)((int64_t)a.chunks * a.slabs));
     if (e != hipSuccess || s->cfg.migration_face != 2) return e;
     return launch_adv_limit(s, a.st, out);
@@ -1529,7 +1538,7 @@ hipError_t launch_correct(nspnp_state *s, const Stage &st, bool update_p, double
     a.tz = tb / a.tx;
     a.ntx = (s->d.nx + a.tx - 1) / a.tx;
     a.chunks = a.ntx * ((s->d.nz + a.tz - 1) / a.tz);
-    a.slab_rows = s->tiles.slab;
+    a.slab_rows = march_rows(s->d.M, s->tiles.slab, (int64_t)a.chunks * s->nmem, kCorrRows);
     a.slabs = (s->d.M + a.slab_rows - 1) / a.slab_rows;
     const dim3 g((unsigned)((int64_t)a.chunks * a.slabs * s->nmem));
     if (s->cfg.implicit_xz) {
