@@ -12,6 +12,7 @@
 // so weights are kept as BF16 in both [in][out] and [out][in] order and
 // activations / gradients in both batch-major and feature-major order.  All
 // dimensions are padded to multiples of 32 with zeros that stay zero.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <string>
@@ -23,6 +24,7 @@ using namespace nspnp;
 
 typedef __bf16 bf16;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 namespace {
@@ -90,6 +92,258 @@ __global__ void __launch_bounds__(256) k_gemm_nt(GemmArgs g) {
     }
 }
 
+// ---- networks whose layers fit one block: two launches a training step ----
+// k_net runs the network for 16 rows per block, forward and, for training,
+// the loss gradient and the back-propagated dZ of every layer, all of them row-local:
+// activations stay in LDS (batch-major, the A operand), 16 waves take the
+// 16-column output tiles in turn, and each wave loads the weights of its next
+// tile ahead of the barrier between layers.  What the weight gradients need
+// (activations and dZ, feature-major) and Z (for GELU') go to memory.
+// k_update then forms every layer's weight and bias gradients and, for a
+// training step, applies Adam to them in place.  Every sum runs in the order
+// of the layer-by-layer kernels (k_gemm_nt, k_bias_grad), so the results are
+// the same bit for bit; the loss alone is summed by blocks.
+// Bound by latency (layer after layer) and by a block's reads of the weights
+// from the L2.
+constexpr int kNetThreads = 1024, kNetWaves = kNetThreads / 64;
+constexpr int kNetChunks = 8;  // K chunks of 32 loaded together
+
+struct NetArgs {
+    int nl, rows, cols, outs, Bp;  // Bp: row stride of the feature-major arrays
+    int ld;                        // row stride of the LDS buffers
+    int pd[kMaxLayers + 1];
+    const bf16 *wb[kMaxLayers], *wtb[kMaxLayers];
+    const float *bias[kMaxLayers];
+    float *z[kMaxLayers];                             // feature-major [N x Bp]
+    bf16 *actt[kMaxLayers + 1], *dzt[kMaxLayers];
+    const float *x, *y;
+    float *out;   // forward only: [rows x outs]
+    float *part;  // training: sum of squared errors per block
+    float scale;  // 2 / (rows outs)
+};
+
+template <bool kGrad>
+__global__ void __launch_bounds__(kNetThreads) k_net(NetArgs a) {
+    extern __shared__ bf16 s_net[];
+    __shared__ float s_sum[kNetWaves];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int r = lane & 15, kc = (lane >> 4) * 8, mb = (lane >> 4) * 4;
+    const int m0 = (int)blockIdx.x * 16, ld = a.ld;
+    bf16 *src = s_net, *dst = s_net + 16 * ld;
+    // B operand of a tile: rows n0 .. n0 + 15 of W [N x K], chunks k0 .. of 32
+    auto load_b = [&](const bf16 *W, int K, int n0, int k0, bf16x8 *b) {
+        const bf16 *p = W + (size_t)(n0 + r) * K + k0 + kc;
+#pragma unroll
+        for (int q = 0; q < kNetChunks; ++q)
+            if (k0 + 32 * q < K) b[q] = *(const bf16x8 *)(p + 32 * q);
+    };
+    // product of src and one tile, the first chunks of B already in b
+    auto tile = [&](const bf16 *W, int K, int n0, bf16x8 *b) -> f32x4 {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int k0 = 0; k0 < K; k0 += 32 * kNetChunks) {
+            if (k0) load_b(W, K, n0, k0, b);
+            const bf16 *pa = src + r * ld + k0 + kc;
+#pragma unroll
+            for (int q = 0; q < kNetChunks; ++q)
+                if (k0 + 32 * q < K)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const bf16x8 *)(pa + 32 * q), b[q], acc, 0, 0, 0);
+        }
+        return acc;
+    };
+    bf16x8 b[kNetChunks];
+    if (wave < a.pd[1] / 16) load_b(a.wtb[0], a.pd[0], wave * 16, 0, b);
+    for (int e = threadIdx.x; e < 16 * a.pd[0]; e += kNetThreads) {
+        const int k = e >> 4, m = e & 15;
+        const float v = (m0 + m < a.rows && k < a.cols) ? a.x[(size_t)(m0 + m) * a.cols + k] : 0.f;
+        const bf16 xb = (bf16)v;
+        src[m * ld + k] = xb;
+        if (kGrad) a.actt[0][(size_t)k * a.Bp + m0 + m] = xb;
+    }
+    __syncthreads();
+    float sq = 0.f;
+    for (int l = 0; l < a.nl; ++l) {
+        const int K = a.pd[l], N = a.pd[l + 1];
+        const bool last = l == a.nl - 1;
+        for (int t = wave; t < N / 16; t += kNetWaves) {
+            const int n = t * 16 + r;
+            if (t != wave) load_b(a.wtb[l], K, t * 16, 0, b);
+            const float bias = a.bias[l][n];
+            float yt[4];
+            if (kGrad && last) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const bool in = m0 + mb + q < a.rows && n < a.outs;
+                    yt[q] = in ? a.y[(size_t)(m0 + mb + q) * a.outs + n] : 0.f;
+                }
+            }
+            const f32x4 acc = tile(a.wtb[l], K, t * 16, b);
+            bf16x4 v;
+            f32x4 zv;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int m = mb + q;
+                const float z = acc[q] + bias;
+                zv[q] = z;
+                if (!last) {
+                    v[q] = (bf16)gelu_f(z);
+                } else if (kGrad) {
+                    float g = 0.f;
+                    if (m0 + m < a.rows && n < a.outs) {
+                        const float d = z - yt[q];
+                        sq += d * d;
+                        g = a.scale * d;
+                    }
+                    v[q] = (bf16)g;
+                } else if (m0 + m < a.rows && n < a.outs) {
+                    a.out[(size_t)(m0 + m) * a.outs + n] = z;
+                }
+                if (kGrad || !last) dst[m * ld + n] = v[q];
+            }
+            if (kGrad) {
+                const size_t o = (size_t)n * a.Bp + m0 + mb;
+                if (!last) *(f32x4 *)(a.z[l] + o) = zv;
+                *(bf16x4 *)((last ? a.dzt[l] : a.actt[l + 1]) + o) = v;
+            }
+        }
+        // the next layer's (or the backward pass's first) weights
+        if (!last) {
+            if (wave < a.pd[l + 2] / 16) load_b(a.wtb[l + 1], N, wave * 16, 0, b);
+        } else if (kGrad && l > 0) {
+            if (wave < K / 16) load_b(a.wb[l], N, wave * 16, 0, b);
+        }
+        __syncthreads();
+        bf16 *sw = src;
+        src = dst;
+        dst = sw;
+    }
+    if (!kGrad) return;
+    for (int l = a.nl - 1; l > 0; --l) {
+        const int K = a.pd[l + 1], N = a.pd[l];
+        for (int t = wave; t < N / 16; t += kNetWaves) {
+            const int n = t * 16 + r;
+            const size_t o = (size_t)n * a.Bp + m0 + mb;
+            const f32x4 zv = *(const f32x4 *)(a.z[l - 1] + o);  // (this thread's own stores)
+            if (t != wave) load_b(a.wb[l], K, t * 16, 0, b);
+            const f32x4 acc = tile(a.wb[l], K, t * 16, b);
+            bf16x4 v;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                v[q] = (bf16)(acc[q] * gelu_grad_f(zv[q]));
+                dst[(mb + q) * ld + n] = v[q];
+            }
+            *(bf16x4 *)(a.dzt[l - 1] + o) = v;
+        }
+        if (l > 1 && wave < a.pd[l - 1] / 16) load_b(a.wb[l - 1], N, wave * 16, 0, b);
+        __syncthreads();
+        bf16 *sw = src;
+        src = dst;
+        dst = sw;
+    }
+    for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
+    if (lane == 0) s_sum[wave] = sq;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float s = 0.f;
+        for (int w = 0; w < kNetWaves; ++w) s += s_sum[w];
+        a.part[blockIdx.x] = s;
+    }
+}
+
+// Adam on one FP32 master weight (the multiply-add order is written out, so
+// that every kernel using it rounds alike).
+struct AdamStep {
+    float lr, b1, b2, eps, c1, c2;
+};
+__device__ __forceinline__ float adam_element(const AdamStep &s, float w, float &m, float &v, float g) {
+    m = __builtin_fmaf(1.f - s.b1, g, s.b1 * m);
+    v = __builtin_fmaf(g, (1.f - s.b2) * g, s.b2 * v);
+    return w - s.lr * (m / s.c1) / (sqrtf(v / s.c2) + s.eps);
+}
+
+struct UpdateArgs {
+    int nl, Bp, K;  // K: batch rows summed (multiple of 32), Bp their stride
+    int pd[kMaxLayers + 1];
+    int first[kMaxLayers + 1];  // first wave of each layer: its weight tiles, then its bias columns by 64
+    const bf16 *actt[kMaxLayers], *dzt[kMaxLayers];
+    float *w[kMaxLayers], *m[kMaxLayers], *v[kMaxLayers], *g[kMaxLayers];
+    bf16 *wb[kMaxLayers], *wtb[kMaxLayers];
+    int apply;  // 0: gradients only
+    AdamStep s;
+    const float *part;
+    int nparts;
+    float count;  // rows * outs
+    float *loss, *loss2;  // loss2: the caller's (may be NULL)
+};
+
+__global__ void __launch_bounds__(256) k_update(UpdateArgs a) {
+    const int lane = threadIdx.x & 63;
+    const int job = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+    if (job > a.first[a.nl]) return;
+    if (job == a.first[a.nl]) {  // the loss, block sums in order
+        float s = 0.f;
+        for (int p = lane; p < a.nparts; p += 64) s += a.part[p];
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        if (lane == 0) {
+            s /= a.count;
+            *a.loss = s;
+            if (a.loss2) *a.loss2 = s;
+        }
+        return;
+    }
+    int l = 0;
+    while (job >= a.first[l + 1]) ++l;
+    const int M = a.pd[l], N = a.pd[l + 1], tn = N / 16, t = job - a.first[l];
+    float *w = a.w[l], *mo = a.m[l], *ve = a.v[l], *g = a.g[l];
+    if (t >= (M / 16) * tn) {  // bias columns
+        const int n = (t - (M / 16) * tn) * 64 + lane;
+        if (n >= N) return;
+        const bf16 *p = a.dzt[l] + (size_t)n * a.Bp;
+        float s = 0.f;
+        for (int k = 0; k < a.K; k += 32) {
+            bf16x8 v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = *(const bf16x8 *)(p + k + 8 * q);
+#pragma unroll
+            for (int q = 0; q < 32; ++q) s += (float)v[q >> 3][q & 7];
+        }
+        const size_t o = (size_t)M * N + n;
+        g[o] = s;
+        if (a.apply) w[o] = adam_element(a.s, w[o], mo[o], ve[o], s);
+        return;
+    }
+    const int m0 = (t / tn) * 16, n0 = (t % tn) * 16;
+    const int r = lane & 15, kc = (lane >> 4) * 8, m = m0 + (lane >> 4) * 4, n = n0 + r;
+    float ww[4], wm[4], wv[4];
+    if (a.apply) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const size_t o = (size_t)(m + q) * N + n;
+            ww[q] = w[o];
+            wm[q] = mo[o];
+            wv[q] = ve[o];
+        }
+    }
+    const bf16 *pa = a.actt[l] + (size_t)(m0 + r) * a.Bp + kc, *pb = a.dzt[l] + (size_t)(n0 + r) * a.Bp + kc;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int k0 = 0; k0 < a.K; k0 += 32)
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const bf16x8 *)(pa + k0), *(const bf16x8 *)(pb + k0), acc, 0, 0, 0);
+    bf16x4 wt;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const size_t o = (size_t)(m + q) * N + n;
+        g[o] = acc[q];
+        if (a.apply) {
+            const float wn = adam_element(a.s, ww[q], wm[q], wv[q], acc[q]);
+            w[o] = wn;
+            mo[o] = wm[q];
+            ve[o] = wv[q];
+            wt[q] = (bf16)wn;
+            a.wb[l][o] = wt[q];
+        }
+    }
+    if (a.apply) *(bf16x4 *)(a.wtb[l] + (size_t)n * M + m) = wt;
+}
+
 // Loss and output-layer gradient: mean over the valid rows and outputs of
 // (yhat - y)^2; dZ = 2 (yhat - y) / (rows * outs), zero in the padding.
 __global__ void __launch_bounds__(256) k_loss(const float *yhat, const float *y, int rows, int outs, int Bp, int Np,
@@ -133,19 +387,14 @@ struct AdamArgs {
     const float *g;     // gradients in the same layout
     bf16 *wb, *wtb;     // BF16 weights [in_p][out_p] and [out_p][in_p]
     int in_p, out_p;
-    float lr, b1, b2, eps, c1, c2;
+    AdamStep s;
 };
 
 __global__ void __launch_bounds__(256) k_adam(AdamArgs a) {
     const int nW = a.in_p * a.out_p;
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= nW + a.out_p) return;
-    const float g = a.g[e];
-    const float m = a.b1 * a.m[e] + (1.f - a.b1) * g;
-    const float v = a.b2 * a.v[e] + (1.f - a.b2) * g * g;
-    a.m[e] = m;
-    a.v[e] = v;
-    const float w = a.w[e] - a.lr * (m / a.c1) / (sqrtf(v / a.c2) + a.eps);
+    const float w = adam_element(a.s, a.w[e], a.m[e], a.v[e], a.g[e]);
     a.w[e] = w;
     if (e < nW) {
         const int i = e / a.out_p, o = e - i * a.out_p;
@@ -192,6 +441,8 @@ struct nspnp_mlp {
     int sizes[kMaxLayers + 1];   // unpadded widths
     int padded[kMaxLayers + 1];  // padded to 32
     int Bp, Bmax;                // padded batch rows
+    bool fused;                  // k_net / k_update (net_fits), else layer by layer
+    int ld;                      // row stride of k_net's LDS buffers
     hipStream_t stream;
     float *w[kMaxLayers], *m[kMaxLayers], *v[kMaxLayers], *g[kMaxLayers];  // each [in_p*out_p + out_p]
     bf16 *wb[kMaxLayers], *wtb[kMaxLayers];
@@ -204,6 +455,15 @@ struct nspnp_mlp {
 };
 
 namespace {
+
+// Two row-major LDS buffers of 16 rows (8 values of padding a row spread the
+// banks) within 64 KB.
+size_t net_lds(int widest) { return 2 * 16 * (size_t)(widest + 8) * sizeof(bf16); }
+bool net_fits(int nl, int widest, size_t weights) {
+    (void)nl;
+    (void)weights;
+    return net_lds(widest) <= 65536 - 256;
+}
 
 size_t mlp_layout(int nl, const int *sizes, int batch, nspnp_mlp *h, char *base) {
     size_t o = 0;
@@ -234,7 +494,7 @@ size_t mlp_layout(int nl, const int *sizes, int batch, nspnp_mlp *h, char *base)
         if (h) { h->z[l] = zz; h->dz[l] = d; h->dzt[l] = dt; }
     }
     float *yh = (float *)take((size_t)Bp * pd[nl] * 4);
-    float *ls = (float *)take(256);
+    float *ls = (float *)take(4 * (size_t)(64 + Bp / 16));  // the loss, then k_net's block sums
     if (h) {
         h->yhat = yh;
         h->loss = ls;
@@ -242,6 +502,12 @@ size_t mlp_layout(int nl, const int *sizes, int batch, nspnp_mlp *h, char *base)
         h->Bp = Bp;
         h->Bmax = batch;
         for (int l = 0; l <= nl; ++l) { h->sizes[l] = sizes[l]; h->padded[l] = pd[l]; }
+        int widest = 0;
+        size_t weights = 0;
+        for (int l = 0; l <= nl; ++l) widest = std::max(widest, pd[l]);
+        for (int l = 0; l < nl; ++l) weights += (size_t)pd[l] * pd[l + 1];
+        h->ld = widest + 8;
+        h->fused = net_fits(nl, widest, weights);
     }
     return o;
 }
@@ -334,6 +600,68 @@ int backward(nspnp_mlp *h, const float *y, int rows) {
     return NSPNP_OK;
 }
 
+// k_net on the handle's weights: forward into out, or (out NULL) forward and
+// backward towards y.
+int run_net(nspnp_mlp *h, const float *x, const float *y, int rows, float *out) {
+    NetArgs a{};
+    a.nl = h->nl;
+    a.rows = rows;
+    a.cols = h->sizes[0];
+    a.outs = h->sizes[h->nl];
+    a.Bp = h->Bp;
+    a.ld = h->ld;
+    for (int l = 0; l <= h->nl; ++l) {
+        a.pd[l] = h->padded[l];
+        a.actt[l] = h->actt[l];
+    }
+    for (int l = 0; l < h->nl; ++l) {
+        a.wb[l] = h->wb[l];
+        a.wtb[l] = h->wtb[l];
+        a.bias[l] = h->w[l] + (size_t)h->padded[l] * h->padded[l + 1];
+        a.z[l] = h->z[l];
+        a.dzt[l] = h->dzt[l];
+    }
+    a.x = x;
+    a.y = y;
+    a.out = out;
+    a.part = h->loss + 64;
+    a.scale = 2.0f / ((float)rows * (float)a.outs);
+    const size_t lds = net_lds(h->ld - 8);
+    if (out) k_net<false><<<(rows + 15) / 16, kNetThreads, lds, h->stream>>>(a);
+    else k_net<true><<<pad32(rows) / 16, kNetThreads, lds, h->stream>>>(a);
+    M_TRY(hipGetLastError());
+    return NSPNP_OK;
+}
+
+// Weight and bias gradients of the rows that k_net ran, and (apply) Adam.
+int run_update(nspnp_mlp *h, int rows, const AdamStep *s, float *dev_loss) {
+    UpdateArgs a{};
+    a.nl = h->nl;
+    a.Bp = h->Bp;
+    a.K = pad32(rows);
+    int jobs = 0;
+    for (int l = 0; l < h->nl; ++l) {
+        a.first[l] = jobs;
+        jobs += (h->padded[l] / 16) * (h->padded[l + 1] / 16) + (h->padded[l + 1] + 63) / 64;
+        a.actt[l] = h->actt[l];
+        a.dzt[l] = h->dzt[l];
+        a.w[l] = h->w[l]; a.m[l] = h->m[l]; a.v[l] = h->v[l]; a.g[l] = h->g[l];
+        a.wb[l] = h->wb[l]; a.wtb[l] = h->wtb[l];
+    }
+    a.first[h->nl] = jobs;  // one more wave: the loss
+    for (int l = 0; l <= h->nl; ++l) a.pd[l] = h->padded[l];
+    a.apply = s != nullptr;
+    if (s) a.s = *s;
+    a.part = h->loss + 64;
+    a.nparts = a.K / 16;
+    a.count = (float)rows * (float)h->sizes[h->nl];
+    a.loss = h->loss;
+    a.loss2 = dev_loss;
+    k_update<<<(jobs + 1 + 3) / 4, 256, 0, h->stream>>>(a);
+    M_TRY(hipGetLastError());
+    return NSPNP_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -412,6 +740,7 @@ int nspnp_mlp_get_params(nspnp_mlp *h, float *host_params, float *host_grads) {
 
 int nspnp_mlp_forward(nspnp_mlp *h, const float *dev_x, int32_t rows, float *dev_y) {
     if (!h || !dev_x || !dev_y || rows < 1 || rows > h->Bmax) return fail_code(NSPNP_ERR_INVALID, "mlp_forward: bad rows");
+    if (h->fused) return run_net(h, dev_x, nullptr, rows, dev_y);
     int rc = pack_input(h, dev_x, rows);
     if (rc || (rc = forward(h))) return rc;
     const int n = rows * h->sizes[h->nl];
@@ -422,8 +751,10 @@ int nspnp_mlp_forward(nspnp_mlp *h, const float *dev_x, int32_t rows, float *dev
 
 int nspnp_mlp_gradients(nspnp_mlp *h, const float *dev_x, const float *dev_y, int32_t rows, float *loss) {
     if (!h || !dev_x || !dev_y || rows < 1 || rows > h->Bmax) return fail_code(NSPNP_ERR_INVALID, "mlp_gradients: bad rows");
-    int rc = pack_input(h, dev_x, rows);
-    if (rc || (rc = forward(h)) || (rc = backward(h, dev_y, rows))) return rc;
+    int rc;
+    if (h->fused) rc = run_net(h, dev_x, dev_y, rows, nullptr), rc = rc ? rc : run_update(h, rows, nullptr, nullptr);
+    else rc = pack_input(h, dev_x, rows), rc = rc ? rc : forward(h), rc = rc ? rc : backward(h, dev_y, rows);
+    if (rc) return rc;
     if (loss) {
         M_TRY(hipMemcpyAsync(loss, h->loss, 4, hipMemcpyDeviceToHost, h->stream));
         M_TRY(hipStreamSynchronize(h->stream));
@@ -434,17 +765,18 @@ int nspnp_mlp_gradients(nspnp_mlp *h, const float *dev_x, const float *dev_y, in
 int nspnp_mlp_train_step(nspnp_mlp *h, const float *dev_x, const float *dev_y, int32_t rows, float lr,
                          float *dev_loss) {
     if (!h || !dev_x || !dev_y || rows < 1 || rows > h->Bmax) return fail_code(NSPNP_ERR_INVALID, "mlp_train_step: bad rows");
-    int rc = pack_input(h, dev_x, rows);
-    if (rc || (rc = forward(h)) || (rc = backward(h, dev_y, rows))) return rc;
+    const double t = (double)(h->t + 1);
+    const AdamStep step{lr, 0.9f, 0.999f, 1e-8f, (float)(1.0 - std::pow(0.9, t)), (float)(1.0 - std::pow(0.999, t))};
+    int rc;
+    if (h->fused) {
+        if ((rc = run_net(h, dev_x, dev_y, rows, nullptr))) return rc;
+        h->t += 1;
+        return run_update(h, rows, &step, dev_loss);
+    }
+    if ((rc = pack_input(h, dev_x, rows)) || (rc = forward(h)) || (rc = backward(h, dev_y, rows))) return rc;
     h->t += 1;
-    const float b1 = 0.9f, b2 = 0.999f;
     AdamArgs a{};
-    a.lr = lr;
-    a.b1 = b1;
-    a.b2 = b2;
-    a.eps = 1e-8f;
-    a.c1 = (float)(1.0 - std::pow(0.9, (double)h->t));
-    a.c2 = (float)(1.0 - std::pow(0.999, (double)h->t));
+    a.s = step;
     for (int l = 0; l < h->nl; ++l) {
         a.w = h->w[l]; a.m = h->m[l]; a.v = h->v[l]; a.g = h->g[l];
         a.wb = h->wb[l]; a.wtb = h->wtb[l];
