@@ -109,7 +109,8 @@ Layout make_layout(const nspnp_config *c) {
     L.off_phiw = o; o = align256(o + 2 * (int64_t)c->nx * c->nz * 8);
     L.off_cyc = o; o = align256(o + cyc_block_doubles(c->nx, c->nz) * kCycBlocks * 8);
     L.nred = std::max<int64_t>({(int64_t)kDtParts * dt_max_blocks((int64_t)c->nx * c->nz), M * kPlaneQ,
-                                 M * (int64_t)run_stats_chunks((int)M) * kRunStatsQ});
+                                 M * (int64_t)run_stats_chunks((int)M) * kRunStatsQ,
+                                 M * (int64_t)(run_stats_chunks((int)M) + 1) * kPlaneQ});
     L.off_red = o; o = align256(o + L.nred * 8);
     L.ntab = 11 * M + 2 + nxh + c->nz + 2 * c->nx + 2 * c->nz;
     L.off_tab = o; o = align256(o + L.ntab * 8);
@@ -200,8 +201,8 @@ void build_tables(nspnp_state *s, double *dev_tab) {
 const double *host_dn(const nspnp_state *s) { return s->host_tables.data() + s->d.M; }
 const double *host_dc(const nspnp_state *s) { return s->host_tables.data() + 2 * s->d.M; }
 
-int plane_reduce(nspnp_state *s, std::vector<double> &host) {
-    HIP_TRY(launch_plane_sums(s, 0, s->red));
+int plane_reduce(nspnp_state *s, int what, std::vector<double> &host) {
+    HIP_TRY(launch_plane_sums(s, what, s->red));
     host.resize((size_t)s->d.M * kPlaneQ);
     HIP_TRY(hipMemcpyAsync(host.data(), s->red, host.size() * sizeof(double), hipMemcpyDeviceToHost, s->stream));
     HIP_TRY(hipStreamSynchronize(s->stream));
@@ -381,7 +382,7 @@ int init_member(nspnp_state *s) {
     HIP_TRY(launch_init_fields(s));
     // remove the volume mean of the concentration noise
     std::vector<double> ps;
-    int rc = plane_reduce(s, ps);  // synchronises: the stack clock0 is consumed
+    int rc = plane_reduce(s, PLANE_IONS, ps);  // synchronises: the stack clock0 is consumed
     if (rc) return rc;
     double sp = 0.0, sm = 0.0, vol = 0.0;
     for (int j = 0; j < d.M; ++j) {
@@ -601,7 +602,7 @@ int nspnp_poisson_solve(nspnp_state *s, int32_t kind, const double *dev_rhs, dou
 int nspnp_wall_shear_stress(nspnp_state *s, double *tau_bottom, double *tau_top) {
     if (!s || !tau_bottom || !tau_top) return fail(NSPNP_ERR_INVALID, "bad wall_shear_stress arguments");
     std::vector<double> ps;
-    int rc = plane_reduce(s, ps);
+    int rc = plane_reduce(s, PLANE_WALL, ps);
     if (rc) return rc;
     const int M = s->d.M;
     const double pl = (double)s->d.plane;
@@ -615,7 +616,7 @@ int nspnp_wall_shear_stress(nspnp_state *s, double *tau_bottom, double *tau_top)
 int nspnp_ion_flux(nspnp_state *s, double *jp, double *jm, double *mass_p, double *mass_m) {
     if (!s || !jp || !jm || !mass_p || !mass_m) return fail(NSPNP_ERR_INVALID, "bad ion_flux arguments");
     std::vector<double> ps;
-    int rc = plane_reduce(s, ps);
+    int rc = plane_reduce(s, PLANE_IONS, ps);
     if (rc) return rc;
     const int M = s->d.M;
     const double pl = (double)s->d.plane;
@@ -664,7 +665,7 @@ int nspnp_explicit_terms(nspnp_state *s, double *const dev_out[5]) {
 int nspnp_diagnostics(nspnp_state *s, double out[6]) {
     if (!s || !out) return fail(NSPNP_ERR_INVALID, "bad diagnostics arguments");
     std::vector<double> ps;
-    int rc = plane_reduce(s, ps);
+    int rc = plane_reduce(s, PLANE_DIAG, ps);
     if (rc) return rc;
     double ke = 0.0, dv = 0.0, mp = 1e300, mm = 1e300, cs = 0.0, pe = 0.0;
     for (int j = 0; j < s->d.M; ++j) {

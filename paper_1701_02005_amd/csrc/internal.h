@@ -233,6 +233,9 @@ enum PlaneQ {
     PQ_MAX_DPHI,                         // max |Phi difference| across the row's faces
     kPlaneQ
 };
+// What a plane reduction forms: the wall rows' sums of u; sums and fluxes of
+// the ions; PQ_KE and what follows.
+enum PlaneWhat { PLANE_WALL = 0, PLANE_IONS, PLANE_DIAG };
 
 // Health word of a run (device clock slot 2), sticky until the clock is set:
 // bit 0 a non-finite field value or step, bit 1 a negative concentration.

@@ -212,85 +212,165 @@ __global__ void __launch_bounds__(kRedThreads) k_dt_final(int nparts, const doub
 // out[j * kPlaneQ + q], q as in PlaneQ: sums of u, c+, c-; total ion fluxes
 // at node j; kinetic energy of row j; max |div u|; min c+, min c-,
 // max (c+ + c-); max |dPhi| across the x, z and lower y faces of row j.
+// Only the quantities of `what` are formed (the others are 0), from the
+// fields that they need.
+//
+// Bound by memory: 2048 blocks or more over the grid (plane_chunks blocks per
+// row, each its part of the row), every load of an element issued before its
+// arithmetic; the block sums go to part[(j * chunks + chunk) * Q + q] and
+// k_plane_close combines a row's in order, so results repeat bit for bit.
+// 256 x 193 x 256 FP64: 454 us with one block a row and every quantity.
+constexpr int kEnergyQ = 3;
 
-template <typename T>
-__global__ void __launch_bounds__(kRedThreads) k_plane(Dims d, const Phys *phys, Tables tb, const T *u, const T *v,
-                                                       const T *w, const T *cp, const T *cm, const T *phi,
-                                                       double *out, size_t ms) {
-    __shared__ double s[kPlaneQ][kRedThreads];
-    u = member_ptr(u, ms); v = member_ptr(v, ms); w = member_ptr(w, ms);
-    cp = member_ptr(cp, ms); cm = member_ptr(cm, ms); phi = member_ptr(phi, ms); out = member_ptr(out, ms);
-    const Phys ph = *member_ptr(phys, ms);
-    const int j = blockIdx.x;
-    const int64_t pl = d.plane;
-    const int64_t base = (int64_t)j * pl;
-    double acc[kPlaneQ] = {0, 0, 0, 0, 0, 0, 0, 1e300, 1e300, 0, 0};
-    static_assert(kPlaneQ == 11, "plane quantities");
-    const double dn = tb.dn[j];
-    const double dcj = tb.dc[j];
-    for (int64_t e = threadIdx.x; e < pl; e += blockDim.x) {
-        const int64_t q = base + e;
-        const int i = (int)(e % d.nx), k = (int)(e / d.nx);
-        const int64_t xp = q - i + ((i + 1 == d.nx) ? 0 : i + 1);
-        const int64_t zp = q + (int64_t)(((k + 1 == d.nz) ? 0 : k + 1) - k) * d.nx;
-        const double uu = (double)u[q], ww = (double)w[q], vv = (double)v[q];
-        const double c1 = (double)cp[q], c2 = (double)cm[q];
-        acc[0] += uu;
-        acc[1] += c1;
-        acc[2] += c2;
-        if (j > 0) {
-            const int64_t qd = q - pl;
-            const double e_y = ph.e0 + ((double)phi[q] - (double)phi[qd]) / dcj;
-            const double m1 = 0.5 * (c1 + (double)cp[qd]);
-            const double m2 = 0.5 * (c2 + (double)cm[qd]);
-            // advective face values: the mean, or the limited upwind value
-            double f1 = m1, f2 = m2;
-            if (ph.limited != 0.0) {
-                const bool up = vv >= 0.0, have = up ? (j > 1) : (j + 1 < d.M);
-                const int64_t quu = up ? q - 2 * pl : q + pl;
-                f1 = adv_face((double)cp[qd], c1, have ? (double)cp[quu] : 0.0, up, have);
-                f2 = adv_face((double)cm[qd], c2, have ? (double)cm[quu] : 0.0, up, have);
-            }
-            // migration face values (hybrid rule: upwind where |dPhi| >= 2)
-            const bool hyb = ph.hybrid != 0.0;
-            const double dpy = hyb ? y_dphi(ph.e0, dcj, (double)phi[q] - (double)phi[qd]) : 0.0;
-            const double g1 = mig_face(hyb, m1, (double)cp[qd], c1, dpy, 1.0);
-            const double g2 = mig_face(hyb, m2, (double)cm[qd], c2, dpy, -1.0);
-            acc[3] += vv * f1 - ph.kd * ((c1 - (double)cp[qd]) / dcj + g1 * e_y);
-            acc[4] += vv * f2 - ph.kd * ((c2 - (double)cm[qd]) / dcj - g2 * e_y);
-            acc[5] += 0.5 * vv * vv * d.dx * dcj * d.dz;
-            acc[10] = fmax(acc[10], fabs((double)phi[q] - (double)phi[qd] + ph.e0 * dcj));
-        }
-        const double f0 = (double)phi[q];
-        acc[10] = fmax(acc[10], fmax(fabs((double)phi[xp] - f0), fabs((double)phi[zp] - f0)));
-        acc[5] += 0.5 * (uu * uu + ww * ww) * d.dx * dn * d.dz;
-        const double vt = (j + 1 < d.M) ? (double)v[q + pl] : 0.0;
-        const double vb = (j > 0) ? vv : 0.0;
-        const double div = ((double)u[xp] - uu) / d.dx + (vt - vb) / dn + ((double)w[zp] - ww) / d.dz;
-        acc[6] = fmax(acc[6], fabs(div));
-        acc[7] = fmin(acc[7], c1);
-        acc[8] = fmin(acc[8], c2);
-        acc[9] = fmax(acc[9], c1 + c2);
-    }
+// Combines a value over the block (fixed order: lanes, then waves); valid in thread 0.
+enum { OP_SUM = 0, OP_MAX, OP_MIN };
+template <int kOp>
+__device__ __forceinline__ double combine(double a, double b) {
+    return kOp == OP_SUM ? a + b : (kOp == OP_MAX ? fmax(a, b) : fmin(a, b));
+}
+template <int kOp>
+__device__ __forceinline__ double block_reduce(double v, double *s_wave) {
 #pragma unroll
-    for (int qq = 0; qq < kPlaneQ; ++qq) s[qq][threadIdx.x] = acc[qq];
+    for (int o = 32; o > 0; o >>= 1) v = combine<kOp>(v, __shfl_xor(v, o, 64));
+    const int wave = threadIdx.x >> 6;
+    __syncthreads();  // (the previous quantity's values have been read)
+    if ((threadIdx.x & 63) == 0) s_wave[wave] = v;
     __syncthreads();
-    for (int o = kRedThreads / 2; o > 0; o >>= 1) {
-        if (threadIdx.x < o) {
-            for (int qq = 0; qq < 6; ++qq) s[qq][threadIdx.x] += s[qq][threadIdx.x + o];
-            s[6][threadIdx.x] = fmax(s[6][threadIdx.x], s[6][threadIdx.x + o]);
-            s[7][threadIdx.x] = fmin(s[7][threadIdx.x], s[7][threadIdx.x + o]);
-            s[8][threadIdx.x] = fmin(s[8][threadIdx.x], s[8][threadIdx.x + o]);
-            s[9][threadIdx.x] = fmax(s[9][threadIdx.x], s[9][threadIdx.x + o]);
-            s[10][threadIdx.x] = fmax(s[10][threadIdx.x], s[10][threadIdx.x + o]);
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x < kPlaneQ) out[(int64_t)j * kPlaneQ + threadIdx.x] = s[threadIdx.x][0];
+    for (int w = 1; w < kRedThreads / 64; ++w) v = combine<kOp>(v, s_wave[w]);
+    return v;
+}
+// (max and min of PlaneQ, sums else)
+__device__ __forceinline__ int plane_op(int q) {
+    return (q == PQ_MAX_DIV || q == PQ_MAX_CSUM || q == PQ_MAX_DPHI) ? OP_MAX
+                                                                    : ((q == PQ_MIN_CP || q == PQ_MIN_CM) ? OP_MIN : OP_SUM);
 }
 
-// Kinetic-energy budget terms of one cell row (one block per row), in the
-// volume-weighted forms of the semi-discrete equations:
+template <typename T, int kWhat>
+__global__ void __launch_bounds__(kRedThreads) k_plane(Dims d, const Phys *phys, Tables tb, const T *u, const T *v,
+                                                       const T *w, const T *cp, const T *cm, const T *phi,
+                                                       double *part, int chunks, size_t ms) {
+    __shared__ double s_wave[kRedThreads / 64];
+    u = member_ptr(u, ms); v = member_ptr(v, ms); w = member_ptr(w, ms);
+    cp = member_ptr(cp, ms); cm = member_ptr(cm, ms); phi = member_ptr(phi, ms); part = member_ptr(part, ms);
+    const Phys ph = *member_ptr(phys, ms);
+    const int M = d.M, chunk = blockIdx.x;
+    const int j = (kWhat == PLANE_WALL && blockIdx.y) ? M - 1 : (int)blockIdx.y;
+    const unsigned pl = (unsigned)d.plane, nx = (unsigned)d.nx, nz = (unsigned)d.nz;
+    const unsigned per = (pl + chunks - 1) / chunks, lo = chunk * per, hi = lo + per < pl ? lo + per : pl;
+    const unsigned base = (unsigned)j * pl;
+    double *out = part + ((size_t)j * chunks + chunk) * kPlaneQ;
+    if constexpr (kWhat == PLANE_WALL) {
+        double a = 0.0;
+        for (unsigned e = lo + threadIdx.x; e < hi; e += kRedThreads) a += (double)u[base + e];
+        a = block_reduce<OP_SUM>(a, s_wave);
+        if (threadIdx.x == 0) out[PQ_SUM_U] = a;
+        return;
+    }
+    // rows below and above (the row itself at the walls: loaded, not used)
+    const bool has_dn = j > 0, has_up = j + 1 < M;
+    const unsigned dn_off = has_dn ? pl : 0u, up_off = has_up ? pl : 0u;
+    const double idc = 1.0 / tb.dc[j], dcj = tb.dc[j];
+    if constexpr (kWhat == PLANE_IONS) {
+        const bool lim = ph.limited != 0.0, hyb = ph.hybrid != 0.0;
+        double s1 = 0.0, s2 = 0.0, j1 = 0.0, j2 = 0.0;
+        for (unsigned e = lo + threadIdx.x; e < hi; e += kRedThreads) {
+            const unsigned q = base + e, qd = q - dn_off;
+            const double c1 = (double)cp[q], c2 = (double)cm[q], d1 = (double)cp[qd], d2 = (double)cm[qd];
+            const double vv = (double)v[q], dph = (double)phi[q] - (double)phi[qd];
+            s1 += c1;
+            s2 += c2;
+            if (has_dn) {
+                const double e_y = ph.e0 + dph * idc;
+                const double m1 = 0.5 * (c1 + d1), m2 = 0.5 * (c2 + d2);
+                // advective face values: the mean, or the limited upwind value
+                double f1 = m1, f2 = m2;
+                if (lim) {
+                    const bool up = vv >= 0.0, have = up ? (j > 1) : has_up;
+                    const unsigned quu = have ? (up ? q - 2 * pl : q + pl) : q;
+                    f1 = adv_face(d1, c1, (double)cp[quu], up, have);
+                    f2 = adv_face(d2, c2, (double)cm[quu], up, have);
+                }
+                // migration face values (hybrid rule: upwind where |dPhi| >= 2)
+                const double dpy = hyb ? y_dphi(ph.e0, dcj, dph) : 0.0;
+                const double g1 = mig_face(hyb, m1, d1, c1, dpy, 1.0);
+                const double g2 = mig_face(hyb, m2, d2, c2, dpy, -1.0);
+                j1 += vv * f1 - ph.kd * ((c1 - d1) * idc + g1 * e_y);
+                j2 += vv * f2 - ph.kd * ((c2 - d2) * idc - g2 * e_y);
+            }
+        }
+        const double r[4] = {block_reduce<OP_SUM>(s1, s_wave), block_reduce<OP_SUM>(s2, s_wave),
+                             block_reduce<OP_SUM>(j1, s_wave), block_reduce<OP_SUM>(j2, s_wave)};
+        if (threadIdx.x == 0) {
+            out[PQ_SUM_CP] = r[0];
+            out[PQ_SUM_CM] = r[1];
+            out[PQ_FLUX_P] = r[2];
+            out[PQ_FLUX_M] = r[3];
+        }
+        return;
+    }
+    const double idx = 1.0 / d.dx, idz = 1.0 / d.dz, idn = 1.0 / tb.dn[j];
+    const double wu = 0.5 * d.dx * tb.dn[j] * d.dz, wv = 0.5 * d.dx * dcj * d.dz;
+    const double ey0 = ph.e0 * dcj;
+    double ke = 0.0, dv = 0.0, m1 = 1e300, m2 = 1e300, cs = 0.0, pe = 0.0;
+    for (unsigned e = lo + threadIdx.x; e < hi; e += kRedThreads) {
+        const unsigned k = e / nx, i = e - k * nx, q = base + e;
+        const unsigned xp = (i + 1 == nx) ? q - i : q + 1, zp = (k + 1 == nz) ? q - k * nx : q + nx;
+        const double uu = (double)u[q], ww = (double)w[q], vv = (double)v[q], f0 = (double)phi[q];
+        const double ux = (double)u[xp], wz = (double)w[zp], va = (double)v[q + up_off];
+        const double fx = (double)phi[xp], fz = (double)phi[zp], fd = (double)phi[q - dn_off];
+        const double c1 = (double)cp[q], c2 = (double)cm[q];
+        ke += wu * (uu * uu + ww * ww);
+        if (has_dn) {
+            ke += wv * vv * vv;
+            pe = fmax(pe, fabs(f0 - fd + ey0));
+        }
+        pe = fmax(pe, fmax(fabs(fx - f0), fabs(fz - f0)));
+        const double vt = has_up ? va : 0.0, vb = has_dn ? vv : 0.0;
+        dv = fmax(dv, fabs((ux - uu) * idx + (vt - vb) * idn + (wz - ww) * idz));
+        m1 = fmin(m1, c1);
+        m2 = fmin(m2, c2);
+        cs = fmax(cs, c1 + c2);
+    }
+    const double r[6] = {block_reduce<OP_SUM>(ke, s_wave), block_reduce<OP_MAX>(dv, s_wave),
+                         block_reduce<OP_MIN>(m1, s_wave), block_reduce<OP_MIN>(m2, s_wave),
+                         block_reduce<OP_MAX>(cs, s_wave), block_reduce<OP_MAX>(pe, s_wave)};
+    if (threadIdx.x == 0) {
+        out[PQ_KE] = r[0];
+        out[PQ_MAX_DIV] = r[1];
+        out[PQ_MIN_CP] = r[2];
+        out[PQ_MIN_CM] = r[3];
+        out[PQ_MAX_CSUM] = r[4];
+        out[PQ_MAX_DPHI] = r[5];
+    }
+}
+
+// A row's block sums combined in order: one thread per (row, quantity).  The
+// rows and quantities that `what` does not form become 0.
+__global__ void __launch_bounds__(kRedThreads) k_plane_close(int M, int what, const double *part, double *out,
+                                                             int chunks, size_t ms) {
+    part = member_ptr(part, ms);
+    out = member_ptr(out, ms);
+    const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (t >= M * kPlaneQ) return;
+    const int j = t / kPlaneQ, q = t - j * kPlaneQ;
+    const bool have = what == PLANE_WALL   ? q == PQ_SUM_U && (j == 0 || j == M - 1)
+                      : what == PLANE_IONS ? q >= PQ_SUM_CP && q <= PQ_FLUX_M
+                                           : q >= PQ_KE;
+    double v = 0.0;
+    if (have) {
+        const double *p = part + (size_t)j * chunks * kPlaneQ + q;
+        const int op = plane_op(q);
+        v = p[0];
+        for (int c = 1; c < chunks; ++c) {
+            const double x = p[(size_t)c * kPlaneQ];
+            v = op == OP_SUM ? v + x : (op == OP_MAX ? fmax(v, x) : fmin(v, x));
+        }
+    }
+    out[t] = v;
+}
+
+// Kinetic-energy budget terms of one cell row, in the volume-weighted forms
+// of the semi-discrete equations:
 //   out[4 j + 0]  sum over the row's velocity unknowns of |grad u|^2 times the
 //                 control volume of each difference (x, z differences of u, w
 //                 and v; y differences of u, w across centre rows and of v
@@ -299,78 +379,78 @@ __global__ void __launch_bounds__(kRedThreads) k_plane(Dims d, const Phys *phys,
 //   out[4 j + 1]  sum of u . f Omega, f the Coulomb force at the u, v, w points
 //   out[4 j + 2]  row 0: sum of (u - u_bot); row M-1: sum of (u_top - u)
 //   out[4 j + 3]  0
-// The wall work follows on the host from out[2] of the two wall rows.
+// The wall work follows on the host from out[2] of the two wall rows.  Split
+// and combined as the plane sums (part: kEnergyQ per block; 256 x 193 x 256
+// FP64: 820 us with one block a row and divisions per element).
 template <typename T>
 __global__ void __launch_bounds__(kRedThreads) k_energy(Dims d, const Phys *phys, Tables tb, const T *u, const T *v,
                                                         const T *w, const T *cp, const T *cm, const T *phi,
-                                                        double *out, size_t ms) {
-    __shared__ double s[3][kRedThreads];
+                                                        double *part, int chunks, size_t ms) {
+    __shared__ double s_wave[kRedThreads / 64];
     u = member_ptr(u, ms); v = member_ptr(v, ms); w = member_ptr(w, ms);
-    cp = member_ptr(cp, ms); cm = member_ptr(cm, ms); phi = member_ptr(phi, ms); out = member_ptr(out, ms);
+    cp = member_ptr(cp, ms); cm = member_ptr(cm, ms); phi = member_ptr(phi, ms); part = member_ptr(part, ms);
     const Phys ph = *member_ptr(phys, ms);
-    const int j = blockIdx.x, M = d.M;
-    const int64_t pl = d.plane;
-    const int64_t base = (int64_t)j * pl;
+    const int j = blockIdx.y, chunk = blockIdx.x, M = d.M;
+    const unsigned pl = (unsigned)d.plane, nx = (unsigned)d.nx, nz = (unsigned)d.nz;
+    const unsigned per = (pl + chunks - 1) / chunks, lo = chunk * per, hi = lo + per < pl ? lo + per : pl;
+    const unsigned base = (unsigned)j * pl;
+    const bool has_dn = j > 0, has_up = j + 1 < M;
+    const unsigned dn_off = has_dn ? pl : 0u, up_off = has_up ? pl : 0u;
     const double dx = d.dx, dz = d.dz, dn = tb.dn[j];
-    const double dcj = tb.dc[j], dcu = tb.dc[j + 1], dc0 = tb.dc[0], dcM = tb.dc[M];
+    const double dcj = tb.dc[j], dcu = tb.dc[j + 1];
+    // weights of the squared differences and of the force work
+    const double area = dx * dz, wxn = dn * dz / dx, wzn = dn * dx / dz, wxc = dcj * dz / dx, wzc = dcj * dx / dz;
+    const double wyu = area / dcu, wyb = area / dcj, wyn = area / dn;
+    const double idc = 1.0 / dcj;
+    const double fxw = ph.kf * 0.5 * dn * dz, fzw = ph.kf * 0.5 * dn * dx, fyw = ph.kf * 0.5 * dcj * area;
     double dis = 0.0, fwk = 0.0, wall = 0.0;
-    for (int64_t e = threadIdx.x; e < pl; e += blockDim.x) {
-        const int64_t q = base + e;
-        const int i = (int)(e % d.nx), k = (int)(e / d.nx);
-        const int64_t xp = q - i + ((i + 1 == d.nx) ? 0 : i + 1);
-        const int64_t xm = q - i + ((i == 0) ? d.nx - 1 : i - 1);
-        const int64_t zp = q + (int64_t)(((k + 1 == d.nz) ? 0 : k + 1) - k) * d.nx;
-        const int64_t zm = q + (int64_t)(((k == 0) ? d.nz - 1 : k - 1) - k) * d.nx;
-        const double uu = (double)u[q], vv = (double)v[q], ww = (double)w[q];
-        const double gux = ((double)u[xp] - uu) / dx, guz = ((double)u[zp] - uu) / dz;
-        const double gwx = ((double)w[xp] - ww) / dx, gwz = ((double)w[zp] - ww) / dz;
-        dis += (gux * gux + guz * guz + gwx * gwx + gwz * gwz) * dx * dn * dz;
-        if (j + 1 < M) {
-            const double guy = ((double)u[q + pl] - uu) / dcu, gwy = ((double)w[q + pl] - ww) / dcu;
-            dis += (guy * guy + gwy * gwy) * dx * dcu * dz;
-        }
-        if (j > 0) {
-            const double gvx = ((double)v[xp] - vv) / dx, gvz = ((double)v[zp] - vv) / dz;
-            dis += (gvx * gvx + gvz * gvz) * dx * dcj * dz;
-        }
-        {
-            const double vb = (j > 0) ? vv : 0.0, vt = (j + 1 < M) ? (double)v[q + pl] : 0.0;
-            const double gvy = (vt - vb) / dn;
-            dis += gvy * gvy * dx * dn * dz;
-        }
-        if (j == 0) {
-            const double gub = (uu - ph.u_bot) / dc0, gwb = ww / dc0;
-            dis += (gub * gub + gwb * gwb) * dx * dc0 * dz;
+    for (unsigned e = lo + threadIdx.x; e < hi; e += kRedThreads) {
+        const unsigned k = e / nx, i = e - k * nx, q = base + e;
+        const unsigned xp = (i + 1 == nx) ? q - i : q + 1, xm = (i == 0) ? q + nx - 1 : q - 1;
+        const unsigned zp = (k + 1 == nz) ? q - k * nx : q + nx, zm = (k == 0) ? q + (nz - 1) * nx : q - nx;
+        const unsigned qu = q + up_off, qd = q - dn_off;
+        const double uu = (double)u[q], vv = (double)v[q], ww = (double)w[q], f0 = (double)phi[q];
+        const double ux = (double)u[xp], uz = (double)u[zp], ua = (double)u[qu];
+        const double wx = (double)w[xp], wz = (double)w[zp], wa = (double)w[qu];
+        const double vx = (double)v[xp], vz = (double)v[zp], va = (double)v[qu];
+        const double r0 = (double)cp[q] - (double)cm[q], rx = (double)cp[xm] - (double)cm[xm];
+        const double rz = (double)cp[zm] - (double)cm[zm], rd = (double)cp[qd] - (double)cm[qd];
+        const double fx = (double)phi[xm], fz = (double)phi[zm], fd = (double)phi[qd];
+        auto sq = [](double a) { return a * a; };
+        dis += (sq(ux - uu) + sq(wx - ww)) * wxn + (sq(uz - uu) + sq(wz - ww)) * wzn;
+        if (has_up) dis += (sq(ua - uu) + sq(wa - ww)) * wyu;
+        if (has_dn) dis += sq(vx - vv) * wxc + sq(vz - vv) * wzc;
+        const double vb = has_dn ? vv : 0.0, vt = has_up ? va : 0.0;
+        dis += sq(vt - vb) * wyn;
+        if (!has_dn) {
+            dis += (sq(uu - ph.u_bot) + sq(ww)) * wyb;
             wall += uu - ph.u_bot;
         }
-        if (j == M - 1) {
-            const double gut = (ph.u_top - uu) / dcM, gwt = -ww / dcM;
-            dis += (gut * gut + gwt * gwt) * dx * dcM * dz;
+        if (!has_up) {
+            dis += (sq(ph.u_top - uu) + sq(ww)) * wyu;
             wall += ph.u_top - uu;
         }
         // Coulomb force sF K rho_face grad Phi at the u, w and v points
-        const double f0 = (double)phi[q];
-        const double r0 = (double)cp[q] - (double)cm[q];
-        const double fu = ph.kf * 0.5 * (r0 + (double)cp[xm] - (double)cm[xm]) * (f0 - (double)phi[xm]) / dx;
-        const double fw = ph.kf * 0.5 * (r0 + (double)cp[zm] - (double)cm[zm]) * (f0 - (double)phi[zm]) / dz;
-        fwk += (uu * fu + ww * fw) * dx * dn * dz;
-        if (j > 0) {
-            const int64_t qd = q - pl;
-            const double ey = ph.e0 + (f0 - (double)phi[qd]) / dcj;
-            const double fv = ph.kf * 0.5 * (r0 + (double)cp[qd] - (double)cm[qd]) * ey;
-            fwk += vv * fv * dx * dcj * dz;
-        }
+        fwk += uu * (r0 + rx) * (f0 - fx) * fxw + ww * (r0 + rz) * (f0 - fz) * fzw;
+        if (has_dn) fwk += vv * (r0 + rd) * (ph.e0 + (f0 - fd) * idc) * fyw;
     }
-    s[0][threadIdx.x] = dis;
-    s[1][threadIdx.x] = fwk;
-    s[2][threadIdx.x] = wall;
-    __syncthreads();
-    for (int o = kRedThreads / 2; o > 0; o >>= 1) {
-        if (threadIdx.x < o)
-            for (int qq = 0; qq < 3; ++qq) s[qq][threadIdx.x] += s[qq][threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x < 4) out[(int64_t)j * 4 + threadIdx.x] = threadIdx.x < 3 ? s[threadIdx.x][0] : 0.0;
+    const double r[kEnergyQ] = {block_reduce<OP_SUM>(dis, s_wave), block_reduce<OP_SUM>(fwk, s_wave),
+                                block_reduce<OP_SUM>(wall, s_wave)};
+    if (threadIdx.x == 0)
+        for (int q = 0; q < kEnergyQ; ++q) part[((size_t)j * chunks + chunk) * kEnergyQ + q] = r[q];
+}
+
+__global__ void __launch_bounds__(kRedThreads) k_energy_close(int M, const double *part, double *out, int chunks,
+                                                              size_t ms) {
+    part = member_ptr(part, ms);
+    out = member_ptr(out, ms);
+    const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (t >= M * 4) return;
+    const int j = t >> 2, q = t & 3;
+    double v = 0.0;
+    if (q < kEnergyQ)
+        for (int c = 0; c < chunks; ++c) v += part[((size_t)j * chunks + c) * kEnergyQ + q];
+    out[t] = v;
 }
 
 // time sums (weight alp dt) of the plane means of u, c+ - c- and phi per row
@@ -468,31 +548,56 @@ hipError_t launch_dt(nspnp_state *s) {
     return hipGetLastError();
 }
 
-// per-plane sums of every member (results in each member's dev_out copy)
-hipError_t launch_plane_sums(nspnp_state *s, int /*what*/, double *dev_out) {
-    const dim3 g((unsigned)s->d.M, 1, (unsigned)s->nmem);
-    if (s->fp64)
-        k_plane<double><<<g, kRedThreads, 0, s->stream>>>(
-            s->d, s->d_phys, s->tb, (const double *)s->f[0], (const double *)s->f[1], (const double *)s->f[2],
-            (const double *)s->f[3], (const double *)s->f[4], (const double *)s->f[5], dev_out, s->mstride);
-    else
-        k_plane<float><<<g, kRedThreads, 0, s->stream>>>(
-            s->d, s->d_phys, s->tb, (const float *)s->f[0], (const float *)s->f[1], (const float *)s->f[2],
-            (const float *)s->f[3], (const float *)s->f[4], (const float *)s->f[5], dev_out, s->mstride);
+// Blocks per row of the plane reductions: about 2048 over the grid, at least
+// two rounds of elements per thread.
+static int plane_chunks(const nspnp_state *s) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>(run_stats_chunks(s->d.M), s->d.plane / (2 * kRedThreads)));
+}
+
+// per-plane sums of every member (results in each member's dev_out copy, the
+// block sums behind them in the reduction scratch)
+hipError_t launch_plane_sums(nspnp_state *s, int what, double *dev_out) {
+    const int chunks = plane_chunks(s);
+    const int M = s->d.M;
+    if (dev_out != s->red || (int64_t)M * kPlaneQ * (chunks + 1) > s->nred) return hipErrorInvalidValue;
+    double *part = dev_out + (size_t)M * kPlaneQ;
+    const dim3 g((unsigned)chunks, what == PLANE_WALL ? 2u : (unsigned)M, (unsigned)s->nmem);
+    auto go = [&](auto zero) {
+        using T = decltype(zero);
+        const T *f[6];
+        for (int q = 0; q < 6; ++q) f[q] = (const T *)s->f[q];
+#define NSPNP_PLANE(W)                                                                                            \
+    k_plane<T, W><<<g, kRedThreads, 0, s->stream>>>(s->d, s->d_phys, s->tb, f[0], f[1], f[2], f[3], f[4], f[5], part, \
+                                                    chunks, s->mstride)
+        if (what == PLANE_WALL) NSPNP_PLANE(PLANE_WALL);
+        else if (what == PLANE_IONS) NSPNP_PLANE(PLANE_IONS);
+        else NSPNP_PLANE(PLANE_DIAG);
+#undef NSPNP_PLANE
+    };
+    if (s->fp64) go(double{});
+    else go(float{});
+    k_plane_close<<<dim3((unsigned)((M * kPlaneQ + kRedThreads - 1) / kRedThreads), 1, (unsigned)s->nmem), kRedThreads,
+                    0, s->stream>>>(M, what, part, dev_out, chunks, s->mstride);
     return hipGetLastError();
 }
 
 // energy-budget partial sums, 4 per row (k_energy)
 hipError_t launch_energy_sums(nspnp_state *s, double *dev_out) {
-    const dim3 g((unsigned)s->d.M, 1, (unsigned)s->nmem);
-    if (s->fp64)
-        k_energy<double><<<g, kRedThreads, 0, s->stream>>>(
-            s->d, s->d_phys, s->tb, (const double *)s->f[0], (const double *)s->f[1], (const double *)s->f[2],
-            (const double *)s->f[3], (const double *)s->f[4], (const double *)s->f[5], dev_out, s->mstride);
-    else
-        k_energy<float><<<g, kRedThreads, 0, s->stream>>>(
-            s->d, s->d_phys, s->tb, (const float *)s->f[0], (const float *)s->f[1], (const float *)s->f[2],
-            (const float *)s->f[3], (const float *)s->f[4], (const float *)s->f[5], dev_out, s->mstride);
+    const int chunks = plane_chunks(s);
+    const int M = s->d.M;
+    if (dev_out != s->red || (int64_t)M * (4 + kEnergyQ * chunks) > s->nred) return hipErrorInvalidValue;
+    double *part = dev_out + 4 * (size_t)M;
+    const dim3 g((unsigned)chunks, (unsigned)M, (unsigned)s->nmem);
+    auto go = [&](auto zero) {
+        using T = decltype(zero);
+        k_energy<T><<<g, kRedThreads, 0, s->stream>>>(s->d, s->d_phys, s->tb, (const T *)s->f[0], (const T *)s->f[1],
+                                                      (const T *)s->f[2], (const T *)s->f[3], (const T *)s->f[4],
+                                                      (const T *)s->f[5], part, chunks, s->mstride);
+    };
+    if (s->fp64) go(double{});
+    else go(float{});
+    k_energy_close<<<dim3((unsigned)((4 * M + kRedThreads - 1) / kRedThreads), 1, (unsigned)s->nmem), kRedThreads, 0,
+                     s->stream>>>(M, part, dev_out, chunks, s->mstride);
     return hipGetLastError();
 }
 
