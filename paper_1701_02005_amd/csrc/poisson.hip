@@ -73,17 +73,29 @@ __device__ __forceinline__ void dft_small<8>(double2 *v, bool inv) {
     v[7] = csub(e[3], t3);
 }
 
-template <>
-__device__ __forceinline__ void dft_small<3>(double2 *v, bool inv) {
+// kOwn: the products with sin(2 pi / 3) are rounded on their own (where the
+// direction is a run-time value the compiler cannot fuse them into the sums;
+// a kernel with a fixed direction that has to agree with that asks for it).
+__device__ __forceinline__ double2 scale_own(double s, double2 a) {
+#pragma clang fp contract(off)
+    return make_double2(s * a.x, s * a.y);
+}
+template <bool kOwn>
+__device__ __forceinline__ void dft3(double2 *v, bool inv) {
     const double s3 = 0.86602540378443864676;  // sin(2 pi / 3)
     const double2 t1 = cadd(v[1], v[2]);
     const double2 t2 = csub(v[1], v[2]);
     const double2 m = make_double2(v[0].x - 0.5 * t1.x, v[0].y - 0.5 * t1.y);
+    const double2 p = kOwn ? scale_own(s3, t2) : make_double2(s3 * t2.x, s3 * t2.y);
     // -i s3 t2 (forward) / +i s3 t2 (inverse)
-    const double2 r = rot(make_double2(s3 * t2.x, s3 * t2.y), inv);
+    const double2 r = rot(p, inv);
     v[0] = cadd(v[0], t1);
     v[1] = cadd(m, r);
     v[2] = csub(m, r);
+}
+template <>
+__device__ __forceinline__ void dft_small<3>(double2 *v, bool inv) {
+    dft3<false>(v, inv);
 }
 
 // q = e / d and r = e % d for 0 <= e, d < 2^22 from a float reciprocal
@@ -198,8 +210,8 @@ __device__ __forceinline__ void stage_twiddles(double2 *s_tw, const double2 *tw,
 // The right-hand side of each line is produced while it is loaded: a plain
 // FP64 array, the divergence of the staggered velocity (pressure), or the
 // charge -(c+ - c-)/(2 lam^2) (potential).
-// The line pairs of an x-transform block into LDS, as (line 2p, line 2p+1)
-// complex values, for one source type S (block-uniform).  Each batch of kXB
+// The line pairs of an x-transform block into LDS (pair p from buf + p ld), as
+// (line 2p, line 2p+1) complex values, for one source type S (block-uniform).  Each batch of kXB
 // elements per thread issues all of its loads before any value is formed
 // (elements past the block or lines past the grid read element 0 of line 0
 // and are dropped), so a thread waits for memory once per batch.  Offsets
@@ -208,7 +220,8 @@ constexpr int kXB = 2;
 
 template <typename T, int S>
 __device__ __forceinline__ void r2c_stage(const PoissonSrc &src, const Dims &d, const Tables &tb, double ch,
-                                          double sc, double idx, double idz, int64_t pair0, int ppb, double2 *buf) {
+                                          double sc, double idx, double idz, int64_t pair0, int ppb, double2 *buf,
+                                          int ld) {
     const int nx = d.nx, nz = d.nz, M = d.M, n = ppb * nx, bd = (int)blockDim.x;
     const int64_t nlines = (int64_t)M * nz;
     const unsigned upl = (unsigned)d.plane;
@@ -315,7 +328,11 @@ __device__ __forceinline__ void r2c_stage(const PoissonSrc &src, const Dims &d, 
 #pragma unroll
         for (int u = 0; u < kXB; ++u) {
             const int e = e0 + u * bd;
-            if (e < n) buf[e] = make_double2(ok[u][0] ? val[u][0] : 0.0, ok[u][1] ? val[u][1] : 0.0);
+            if (e < n) {
+                int p, i;
+                dnx.split(e, p, i);
+                buf[p * ld + i] = make_double2(ok[u][0] ? val[u][0] : 0.0, ok[u][1] ? val[u][1] : 0.0);
+            }
         }
     }
 }
@@ -349,9 +366,9 @@ __global__ void __launch_bounds__(256) k_fft_x_r2c(Dims d, Tables tb, FftPlan pl
     // [j][kx][kz] row run on one XCD, so their partial-line stores merge in
     // that XCD's L2 before they reach memory
     const int64_t pair0 = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * ppb;
-    if (src.type == SRC_DIV) r2c_stage<T, SRC_DIV>(src, d, tb, ch, sc, idx, idz, pair0, ppb, bf[0]);
-    else if (src.type == SRC_CHARGE) r2c_stage<T, SRC_CHARGE>(src, d, tb, ch, sc, idx, idz, pair0, ppb, bf[0]);
-    else r2c_stage<T, SRC_REAL>(src, d, tb, ch, sc, idx, idz, pair0, ppb, bf[0]);
+    if (src.type == SRC_DIV) r2c_stage<T, SRC_DIV>(src, d, tb, ch, sc, idx, idz, pair0, ppb, bf[0], nx);
+    else if (src.type == SRC_CHARGE) r2c_stage<T, SRC_CHARGE>(src, d, tb, ch, sc, idx, idz, pair0, ppb, bf[0], nx);
+    else r2c_stage<T, SRC_REAL>(src, d, tb, ch, sc, idx, idz, pair0, ppb, bf[0], nx);
     __syncthreads();
     const int w = lds_fft<kR8>(bf[0], bf[1], nx, ppb, pl, s_tw, false);
     // (offsets from the LDS base rather than bf[w]: a pointer picked from an
@@ -522,6 +539,200 @@ __global__ void __launch_bounds__(256) k_fft_z(Dims d, FftPlan pl, const double2
         for (int e = threadIdx.x; e < nt * nz; e += blockDim.x) base[e] = z[e];
         __syncthreads();  // bf[0] and the result buffer are reused by the next tile
     }
+}
+
+// ---- whole planes: x and z transforms of one row in one kernel ----
+// A block owns one row j of one problem and member, all of its nx x nz plane:
+// forward, the right-hand side of every line, the x transforms of the line
+// pairs, the half spectrum and its z transforms, one contiguous store;
+// inverse, the same backwards.  Each saves a pass over the spectrum (read and
+// write) and a launch.  Lanes run over the lines, whose LDS stride is odd in
+// 16-byte units: every access of a pass is free of bank conflicts, and a
+// wave's twiddles are one or two entries.  The butterflies and their order
+// are those of the separate kernels, so the results are the same bit for bit.
+// 32 members of 64 x 65 x 64 and 48 x 49 x 48 (mean of both): forward 75 us
+// (4.4 TB/s at the larger), inverse 55, against 85 and 94 for two kernels;
+// a 32 x 33 x 32 grid 10 and 7 us against 12 and 11 (latency and launches).
+// (kOwn: as k_fft_z, whose direction is a run-time value, see dft3)
+template <int R, bool kOwn>
+__device__ __forceinline__ void plane_pass(const double2 *__restrict__ src, double2 *__restrict__ dst, int N, int nl,
+                                           const Div &dnl, int ld, int Ns, const double2 *__restrict__ tw, bool inv) {
+    const int NR = N / R;
+    const Div dNs(Ns);
+    for (int e = threadIdx.x; e < nl * NR; e += blockDim.x) {
+        int jb, line, blk, k;
+        dnl.split(e, jb, line);
+        dNs.split(jb, blk, k);
+        const double2 *in = src + line * ld + jb;
+        double2 v[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] = in[r * NR];
+#pragma unroll
+        for (int r = 1; r < R; ++r) {
+            double2 w = tw[(r - 1) * Ns + k];
+            if (inv) w.y = -w.y;
+            v[r] = cmul(v[r], w);
+        }
+        if constexpr (R == 3) dft3<kOwn>(v, inv);
+        else dft_small<R>(v, inv);
+        double2 *out = dst + line * ld + blk * Ns * R + k;
+#pragma unroll
+        for (int r = 0; r < R; ++r) out[r * Ns] = v[r];
+    }
+}
+
+// nl lines of length N (stride ld) in b0; returns the buffer (0 or 1) holding
+// the result.
+template <bool kOwn>
+__device__ __forceinline__ int plane_fft(double2 *b0, double2 *b1, int N, int nl, int ld, const FftPlan &pl,
+                                         const double2 *tw, bool inv) {
+    double2 *src = b0, *dst = b1;
+    const Div dnl(nl);
+    int which = 0, Ns = 1, off = 0;
+    for (int s = 0; s < pl.nstages; ++s) {
+        const int R = pl.radix[s];
+        if (R == 4) plane_pass<4, kOwn>(src, dst, N, nl, dnl, ld, Ns, tw + off, inv);
+        else if (R == 2) plane_pass<2, kOwn>(src, dst, N, nl, dnl, ld, Ns, tw + off, inv);
+        else plane_pass<3, kOwn>(src, dst, N, nl, dnl, ld, Ns, tw + off, inv);
+        off += Ns * (R - 1);
+        __syncthreads();
+        double2 *t = src;
+        src = dst;
+        dst = t;
+        which ^= 1;
+        Ns *= R;
+    }
+    return which;
+}
+
+// LDS slots of one of the two buffers: the line pairs or the half spectrum.
+__host__ __device__ inline int plane_slots(int nx, int nz) {
+    const int a = nz / 2 * (nx + 1), b = (nx / 2 + 1) * (nz + 1);
+    return a > b ? a : b;
+}
+inline size_t plane_lds(int nx, int nz) { return (2 * (size_t)plane_slots(nx, nz) + nx + nz) * sizeof(double2); }
+
+template <typename T>
+__global__ void __launch_bounds__(1024) k_plane_fwd(Dims d, Tables tb, FftPlan plx, FftPlan plz, PoissonBatch b,
+                                                    const double *clock, double2 *spec, int64_t nspec) {
+    extern __shared__ double2 sm[];
+    const int prob = blockIdx.y;
+    PoissonSrc src = b.src[prob];
+    src.a = member_ptr(src.a, b.ms);
+    src.b = member_ptr(src.b, b.ms);
+    src.c = member_ptr(src.c, b.ms);
+    if (src.wall) src.wall = member_ptr(src.wall, b.ms);
+    clock = member_ptr(clock, b.ms);
+    const double ch = member_ptr(b.phys, b.ms)->ch;
+    const int nx = d.nx, nz = d.nz, nxh = d.nxh, np = nz / 2, ldx = nx + 1, ldz = nz + 1;
+    const int j = (int)xcd_tile(blockIdx.x, gridDim.x);  // neighbouring rows share an L2
+    double2 *out = member_ptr(spec, b.ms) + prob * nspec + (int64_t)j * nxh * nz;
+    const int bs = plane_slots(nx, nz);
+    double2 *s_twx = sm + 2 * bs, *s_twz = s_twx + nx;
+    stage_twiddles(s_twx, tb.twx, nx);
+    stage_twiddles(s_twz, tb.twz, nz);
+    const double sc = (src.type == SRC_DIV) ? ((src.alp > 0.0) ? 1.0 / (src.alp * clock[1]) : src.fixed) : 0.0;
+    const double idx = 1.0 / d.dx, idz = 1.0 / d.dz;
+    const int64_t pair0 = (int64_t)j * np;
+    if (src.type == SRC_DIV) r2c_stage<T, SRC_DIV>(src, d, tb, ch, sc, idx, idz, pair0, np, sm, ldx);
+    else if (src.type == SRC_CHARGE) r2c_stage<T, SRC_CHARGE>(src, d, tb, ch, sc, idx, idz, pair0, np, sm, ldx);
+    else r2c_stage<T, SRC_REAL>(src, d, tb, ch, sc, idx, idz, pair0, np, sm, ldx);
+    __syncthreads();
+    int w = plane_fft<false>(sm, sm + bs, nx, np, ldx, plx, s_twx, false);
+    const double2 *z = sm + w * bs;
+    double2 *o = sm + (1 - w) * bs;  // [kx][kz]
+    const Div dnp(np), dnz(nz);
+    for (int e = threadIdx.x; e < np * nxh; e += blockDim.x) {
+        int kk, p;
+        dnp.split(e, kk, p);
+        const double2 zk = z[p * ldx + kk];
+        const double2 zc = z[p * ldx + (kk == 0 ? 0 : nx - kk)];
+        // A = (Z_k + conj(Z_{N-k}))/2, B = (Z_k - conj(Z_{N-k}))/(2i)
+        o[kk * ldz + 2 * p] = make_double2(0.5 * (zk.x + zc.x), 0.5 * (zk.y - zc.y));
+        o[kk * ldz + 2 * p + 1] = make_double2(0.5 * (zk.y + zc.y), -0.5 * (zk.x - zc.x));
+    }
+    __syncthreads();
+    const int wz = plane_fft<true>(o, sm + w * bs, nz, nxh, ldz, plz, s_twz, false);
+    z = sm + ((1 - w) ^ wz) * bs;
+    for (int e = threadIdx.x; e < nxh * nz; e += blockDim.x) {
+        int kk, k;
+        dnz.split(e, kk, k);
+        out[e] = z[kk * ldz + k];
+    }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(1024) k_plane_inv(Dims d, Tables tb, FftPlan plx, FftPlan plz, PoissonBatch b,
+                                                    const double2 *spec, int64_t nspec) {
+    extern __shared__ double2 sm[];
+    const int prob = blockIdx.y;
+    const int nx = d.nx, nz = d.nz, nxh = d.nxh, np = nz / 2, ldx = nx + 1, ldz = nz + 1;
+    const int j = (int)xcd_tile(blockIdx.x, gridDim.x);
+    const double2 *in = member_ptr(spec, b.ms) + prob * nspec + (int64_t)j * nxh * nz;
+    const int bs = plane_slots(nx, nz);
+    double2 *s_twx = sm + 2 * bs, *s_twz = s_twx + nx;
+    stage_twiddles(s_twx, tb.twx, nx);
+    stage_twiddles(s_twz, tb.twz, nz);
+    const Div dnp(np), dnz(nz), dnx(nx);
+    const int ns = nxh * nz, bd = (int)blockDim.x;
+    for (int e0 = threadIdx.x; e0 < ns; e0 += 4 * bd) {  // (past the end: the first value, dropped)
+        double2 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = ld_once(in + (e0 + u * bd < ns ? e0 + u * bd : 0));
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            int kk, k;
+            dnz.split(e0 + u * bd, kk, k);
+            if (e0 + u * bd < ns) sm[kk * ldz + k] = v[u];
+        }
+    }
+    __syncthreads();
+    const int w = plane_fft<true>(sm, sm + bs, nz, nxh, ldz, plz, s_twz, true);
+    const double2 *o = sm + w * bs;
+    double2 *f = sm + (1 - w) * bs;  // [pair][x]
+    for (int e = threadIdx.x; e < np * nx; e += bd) {
+        int kk, p;
+        dnp.split(e, kk, p);
+        const bool lower = kk < nxh;
+        const int src = lower ? kk : nx - kk;
+        double2 A = o[src * ldz + 2 * p];
+        double2 B = o[src * ldz + 2 * p + 1];
+        if (!lower) {  // Hermitian continuation of a real line's spectrum
+            A.y = -A.y;
+            B.y = -B.y;
+        }
+        f[p * ldx + kk] = make_double2(A.x - B.y, A.y + B.x);  // Z = A + i B
+    }
+    __syncthreads();
+    const int wx = plane_fft<false>(f, sm + w * bs, nx, np, ldx, plx, s_twx, true);
+    const double2 *z = sm + ((1 - w) ^ wx) * bs;
+    const bool as_state = b.out_state[prob] != 0;
+    double *o64 = (double *)member_ptr(b.out[prob], b.ms);
+    T *ot = (T *)member_ptr(b.out[prob], b.ms);
+    const int64_t l0 = (int64_t)j * nz;
+    for (int e = threadIdx.x; e < np * nx; e += bd) {
+        int p, i;
+        dnx.split(e, p, i);
+        const int64_t qa = (l0 + 2 * p) * nx + i, qb = qa + nx;
+        const double2 v = z[p * ldx + i];
+        if (as_state) {
+            st_once(ot + qa, (T)v.x);
+            st_once(ot + qb, (T)v.y);
+        } else {
+            st_once(o64 + qa, v.x);
+            st_once(o64 + qb, v.y);
+        }
+    }
+}
+
+// Whole planes where two blocks fit a CU's LDS (64 x 64: 70 KB a block).
+inline bool plane_fits(const nspnp_state *s) {
+    return plane_lds(s->d.nx, s->d.nz) <= std::min((size_t)80 << 10, (size_t)s->lds_max);
+}
+// One butterfly of the wider direction's radix-4 passes per thread.
+inline unsigned plane_threads(int nx, int nz) {
+    const int work = std::max(nz / 2 * nx, (nx / 2 + 1) * nz) / 4;
+    return (unsigned)std::min(1024, std::max(64, (work + 63) / 64 * 64));
 }
 
 // ---- y direction: one tridiagonal solve per (kx, kz) mode ----
@@ -1010,7 +1221,19 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
         return false;
     };
     const bool r8x = has_r8(s->planx), r8z = has_r8(s->planz);
-    {
+    const bool march = s->tiles.thomas == 0 && s->cpv && s->mu;  // z transforms fused with the y solve
+    const bool planes = !march && plane_fits(s);
+    const dim3 gp((unsigned)d.M, (unsigned)b.nprob, (unsigned)nmem);
+    const size_t ldsp = plane_lds(d.nx, d.nz);
+    const unsigned tp = plane_threads(d.nx, d.nz);
+    if (planes) {
+        ProfScope prof_(s, K_FFTX_FWD);
+        const hipError_t e = lds_opt_in(s->fp64 ? (const void *)k_plane_fwd<double> : (const void *)k_plane_fwd<float>,
+                                        ldsp, s->lds_max);
+        if (e != hipSuccess) return e;
+        if (s->fp64) k_plane_fwd<double><<<gp, tp, ldsp, s->stream>>>(d, s->tb, s->planx, s->planz, b, s->clock, s->spec, nspec);
+        else k_plane_fwd<float><<<gp, tp, ldsp, s->stream>>>(d, s->tb, s->planx, s->planz, b, s->clock, s->spec, nspec);
+    } else {
         ProfScope prof_(s, K_FFTX_FWD);
         const dim3 gx((unsigned)((npairs + ppb - 1) / ppb), (unsigned)b.nprob, (unsigned)nmem);
         const size_t ldsx = (2 * (size_t)x_buffer_slots(d.nx, ppb) + d.nx) * sizeof(double2);
@@ -1028,7 +1251,7 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
         }
 #undef NSPNP_R2C
     }
-    if (s->tiles.thomas == 0 && s->cpv && s->mu) {
+    if (march) {
         // z transforms and mode solves fused into two row marches: tiles of
         // tk x-modes, about one mode of a row per thread (the marches are
         // serial in y, so the most tiles give the most parallelism)
@@ -1057,7 +1280,7 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
         const int zblocks = std::max(1, std::min(ztiles, 2048 / std::max(1, b.nprob * nmem)));
         const dim3 gz((unsigned)zblocks, (unsigned)b.nprob, (unsigned)nmem);
         const size_t ldsz = (2 * (size_t)tk * d.nz + d.nz) * sizeof(double2);
-        {
+        if (!planes) {
             ProfScope prof_(s, K_FFTZ_FWD);
             if (r8z) k_fft_z<true><<<gz, 256, ldsz, s->stream>>>(d, s->planz, s->tb.twz, s->spec, nspec, tk, 0, b.ms);
             else k_fft_z<false><<<gz, 256, ldsz, s->stream>>>(d, s->planz, s->tb.twz, s->spec, nspec, tk, 0, b.ms);
@@ -1087,13 +1310,20 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
             }
 #undef NSPNP_TH_CASE
         }
-        {
+        if (!planes) {
             ProfScope prof_(s, K_FFTZ_INV);
             if (r8z) k_fft_z<true><<<gz, 256, ldsz, s->stream>>>(d, s->planz, s->tb.twz, s->spec, nspec, tk, 1, b.ms);
             else k_fft_z<false><<<gz, 256, ldsz, s->stream>>>(d, s->planz, s->tb.twz, s->spec, nspec, tk, 1, b.ms);
         }
     }
-    {
+    if (planes) {
+        ProfScope prof_(s, K_FFTX_INV);
+        const hipError_t e = lds_opt_in(s->fp64 ? (const void *)k_plane_inv<double> : (const void *)k_plane_inv<float>,
+                                        ldsp, s->lds_max);
+        if (e != hipSuccess) return e;
+        if (s->fp64) k_plane_inv<double><<<gp, tp, ldsp, s->stream>>>(d, s->tb, s->planx, s->planz, b, s->spec, nspec);
+        else k_plane_inv<float><<<gp, tp, ldsp, s->stream>>>(d, s->tb, s->planx, s->planz, b, s->spec, nspec);
+    } else {
         ProfScope prof_(s, K_FFTX_INV);
         // at least 8 lines per block, so that every kx of the transposed load
         // reads whole 128-byte lines of the [j][kx][kz] spectrum
@@ -1124,8 +1354,9 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
 // Raise the dynamic-LDS limit of the FP64 x transforms ahead of use (their
 // blocks may take more than 64 KB), so that later launches find the record.
 hipError_t prime_x_transform_lds(int lds_max) {
-    const void *fns[4] = {(const void *)k_fft_x_r2c<double, false>, (const void *)k_fft_x_r2c<double, true>,
-                          (const void *)k_fft_x_c2r<double, false>, (const void *)k_fft_x_c2r<double, true>};
+    const void *fns[6] = {(const void *)k_fft_x_r2c<double, false>, (const void *)k_fft_x_r2c<double, true>,
+                          (const void *)k_fft_x_c2r<double, false>, (const void *)k_fft_x_c2r<double, true>,
+                          (const void *)k_plane_fwd<double>, (const void *)k_plane_inv<double>};
     for (const void *fn : fns) {
         const hipError_t e = lds_opt_in(fn, (size_t)lds_max, lds_max);
         if (e != hipSuccess) return e;
