@@ -785,15 +785,19 @@ __global__ void __launch_bounds__(256) k_thomas_factors(Dims d, Tables tb, doubl
 }
 
 // Solve of one tile of tm consecutive modes of one problem: the tile's rows
-// are staged in LDS with coalesced loads; each wave then solves one mode at
-// a time with its rows split into 64 contiguous lane segments of R rows (the
-// mode's pivots are one contiguous read per wave).  Each recurrence is a
-// local sweep per lane, a 6-step scan of affine maps across the wave and a
-// second sweep from the correct incoming value.  The tile is written back
-// with coalesced stores.
+// are staged in LDS with coalesced loads; each group of W lanes then solves
+// one mode at a time with its rows split into W contiguous lane segments of R
+// rows (the mode's pivots are one contiguous read per group; 16 or 32 lanes
+// where they hold all rows, with R 1: the idle lanes of a whole wave would
+// only pass values through, so the result is the same).  Each recurrence is
+// a local sweep per lane, a scan of affine maps across the group and a second
+// sweep from the correct incoming value.  The tile is written back with
+// coalesced stores.  The members of a batch share one grid, so all of them
+// read member 0's pivots, which then stay in the caches: 32 instead of 48
+// bytes of memory traffic per mode and row.
 constexpr int kThBatch = 12;  // a whole 16-mode tile of 192 rows in one batch
 
-template <int R>
+template <int R, int W>
 __global__ void __launch_bounds__(256) k_thomas_tile(Dims d, Tables tb, PoissonBatch b, double2 *spec_all,
                                                      const double2 *fac_all, int64_t nspec, int tm) {
     extern __shared__ double2 s_x[];
@@ -803,7 +807,7 @@ __global__ void __launch_bounds__(256) k_thomas_tile(Dims d, Tables tb, PoissonB
     const int64_t nmodes = (int64_t)d.nxh * d.nz;
     const int M = d.M;
     double2 *spec = member_ptr_at(spec_all, b.ms, blk.z) + prob * nspec;
-    const double2 *fac = member_ptr_at(fac_all, b.ms, blk.z) + (int64_t)kind * nmodes * M;
+    const double2 *fac = fac_all + (int64_t)kind * nmodes * M;
     const int64_t m0 = (int64_t)blk.x * tm;
     const int ncol = (int)((nmodes - m0) < tm ? (nmodes - m0) : tm);
     const int LD = tm + 1;
@@ -831,7 +835,8 @@ __global__ void __launch_bounds__(256) k_thomas_tile(Dims d, Tables tb, PoissonB
         }
     }
     __syncthreads();
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = blockDim.x >> 6;
+    const int lane = (int)threadIdx.x % W, wave = (int)threadIdx.x / W, nwave = (int)blockDim.x / W;  // (groups)
+    constexpr int kSteps = W == 64 ? 6 : (W == 32 ? 5 : 4);
     const int js = lane * R;
     const double scale = 1.0 / ((double)d.nx * (double)d.nz);
     double lo[R];
@@ -881,16 +886,16 @@ __global__ void __launch_bounds__(256) k_thomas_tile(Dims d, Tables tb, PoissonB
             Ss *= nn[t];
         }
         // multipliers of the scans of x -> T + Q x (forward, from lane 0 up)
-        // and x -> U + S x (backward, from lane 63 down)
-        double qm[6], sm[6];
+        // and x -> U + S x (backward, from the last lane down)
+        double qm[kSteps], sm[kSteps];
 #pragma unroll
-        for (int st = 0; st < 6; ++st) {
+        for (int st = 0; st < kSteps; ++st) {
             const int sft = 1 << st;
             qm[st] = Qs;
             sm[st] = Ss;
-            const double Qp = __shfl_up(Qs, sft, 64), Sp = __shfl_down(Ss, sft, 64);
+            const double Qp = __shfl_up(Qs, sft, W), Sp = __shfl_down(Ss, sft, W);
             if (lane >= sft) Qs *= Qp;
-            if (lane + sft < 64) Ss *= Sp;
+            if (lane + sft < W) Ss *= Sp;
         }
         // forward sweep
         double tx = 0.0, ty = 0.0;
@@ -900,14 +905,14 @@ __global__ void __launch_bounds__(256) k_thomas_tile(Dims d, Tables tb, PoissonB
             ty = g[t] * x[t].y + mm[t] * ty;
         }
 #pragma unroll
-        for (int st = 0; st < 6; ++st) {
-            const double px = __shfl_up(tx, 1 << st, 64), py = __shfl_up(ty, 1 << st, 64);
+        for (int st = 0; st < kSteps; ++st) {
+            const double px = __shfl_up(tx, 1 << st, W), py = __shfl_up(ty, 1 << st, W);
             if (lane >= (1 << st)) {
                 tx += qm[st] * px;
                 ty += qm[st] * py;
             }
         }
-        double dx_ = __shfl_up(tx, 1, 64), dy_ = __shfl_up(ty, 1, 64);
+        double dx_ = __shfl_up(tx, 1, W), dy_ = __shfl_up(ty, 1, W);
         if (lane == 0) dx_ = dy_ = 0.0;
 #pragma unroll
         for (int t = 0; t < R; ++t) {
@@ -924,15 +929,15 @@ __global__ void __launch_bounds__(256) k_thomas_tile(Dims d, Tables tb, PoissonB
             uy = (in ? x[t].y : 0.0) + nn[t] * uy;
         }
 #pragma unroll
-        for (int st = 0; st < 6; ++st) {
-            const double px = __shfl_down(ux, 1 << st, 64), py = __shfl_down(uy, 1 << st, 64);
-            if (lane + (1 << st) < 64) {
+        for (int st = 0; st < kSteps; ++st) {
+            const double px = __shfl_down(ux, 1 << st, W), py = __shfl_down(uy, 1 << st, W);
+            if (lane + (1 << st) < W) {
                 ux += sm[st] * px;
                 uy += sm[st] * py;
             }
         }
-        double xx = __shfl_down(ux, 1, 64), xy = __shfl_down(uy, 1, 64);
-        if (lane == 63) xx = xy = 0.0;
+        double xx = __shfl_down(ux, 1, W), xy = __shfl_down(uy, 1, W);
+        if (lane == W - 1) xx = xy = 0.0;
 #pragma unroll
         for (int t = R - 1; t >= 0; --t) {
             const bool in = g[t] != 0.0;
@@ -953,10 +958,10 @@ __global__ void __launch_bounds__(256) k_thomas_tile(Dims d, Tables tb, PoissonB
                 }
             }
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                sx += __shfl_xor(sx, o, 64);
-                sy += __shfl_xor(sy, o, 64);
-                vol += __shfl_xor(vol, o, 64);
+            for (int o = W / 2; o > 0; o >>= 1) {
+                sx += __shfl_xor(sx, o, W);
+                sy += __shfl_xor(sy, o, W);
+                vol += __shfl_xor(vol, o, W);
             }
             const double mx = sx / vol, my = sy / vol;
 #pragma unroll
@@ -1288,16 +1293,26 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
         const int64_t nmodes = (int64_t)d.nxh * d.nz;
         {
             ProfScope prof_(s, K_THOMAS);
-            const int tm = thomas_tile_modes(d.M, s->tiles.thomas);
+            const int lanes = d.M <= 16 ? 16 : (d.M <= 32 ? 32 : 64);
+            int tm = thomas_tile_modes(d.M, s->tiles.thomas);
+            // small problems: fewer modes per tile, down to one per group of
+            // lanes, until every CU has two blocks (a group solves its modes
+            // one after the other, about 1 us each)
+            while (tm > 256 / lanes && (nmodes + tm - 1) / tm * b.nprob * nmem < 512) tm = std::max(tm / 2, 256 / lanes);
             const dim3 gt((unsigned)((nmodes + tm - 1) / tm), (unsigned)b.nprob, (unsigned)nmem);
             const size_t ldst = (size_t)d.M * (tm + 1) * sizeof(double2);
             const int rpl = (d.M + 63) / 64;  // rows per lane (M <= 512: at most 8)
+#define NSPNP_TH(RR, WW) k_thomas_tile<RR, WW><<<gt, 256, ldst, s->stream>>>(d, s->tb, b, s->spec, s->fac, nspec, tm)
 #define NSPNP_TH_CASE(RR)                                                                                \
         case RR:                                                                                             \
-            k_thomas_tile<RR><<<gt, 256, ldst, s->stream>>>(d, s->tb, b, s->spec, s->fac, nspec, tm);        \
+            NSPNP_TH(RR, 64);                                                                                \
             break;
             switch (rpl) {
-                NSPNP_TH_CASE(1)
+                case 1:
+                    if (lanes == 16) NSPNP_TH(1, 16);
+                    else if (lanes == 32) NSPNP_TH(1, 32);
+                    else NSPNP_TH(1, 64);
+                    break;
                 NSPNP_TH_CASE(2)
                 NSPNP_TH_CASE(3)
                 NSPNP_TH_CASE(4)
@@ -1309,6 +1324,7 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
                     return hipErrorInvalidValue;
             }
 #undef NSPNP_TH_CASE
+#undef NSPNP_TH
         }
         if (!planes) {
             ProfScope prof_(s, K_FFTZ_INV);
