@@ -784,13 +784,18 @@ struct CycArgs {
     int out_r;  // 1: the solution replaces r; 0: q += solution
 };
 
+// One block per stage, diffusivity and direction; one thread runs the serial
+// recurrences in LDS, elimination and forward sweep of z together (the
+// division of a row is what the chain waits for), and the block stores them.
+constexpr int kMaxLine = 1024;
+
 __global__ void __launch_bounds__(64) k_cyc_coef(Dims d, const Phys *phys, const double *clock, double *cyc,
                                                  CnStages stages, size_t ms) {
+    __shared__ double s_t[4][kMaxLine];  // g, m, n, z
     phys = member_ptr(phys, ms);
     clock = member_ptr(clock, ms);
     cyc = member_ptr(cyc, ms);
-    const int stage = blockIdx.y, sys = threadIdx.x;
-    if (sys >= 4) return;
+    const int stage = blockIdx.y, sys = blockIdx.x;
     const int ty = sys >> 1, dir = sys & 1;  // diffusivity (velocity, ions), direction
     const int N = dir == 0 ? d.nx : d.nz;
     const double h = dir == 0 ? d.dx : d.dz;
@@ -799,29 +804,36 @@ __global__ void __launch_bounds__(64) k_cyc_coef(Dims d, const Phys *phys, const
     const double dg = 1.0 + 2.0 * b / (h * h), e = -b / (h * h), gam = -dg;
     const int64_t nb = cyc_block_doubles(d.nx, d.nz), Nmax = (nb - 4) / 4;
     double *blk = cyc + ((int64_t)(stage * 2 + ty) * 2 + dir) * nb;
-    double *g = blk, *m = blk + Nmax, *n = blk + 2 * Nmax, *z = blk + 3 * Nmax;
-    double cprev = 0.0;
-    for (int i = 0; i < N; ++i) {
-        const double bi = (i == 0) ? dg - gam : (i == N - 1 ? dg - e * e / gam : dg);
-        const double ai = (i == 0) ? 0.0 : e;
-        const double rden = 1.0 / (bi - ai * cprev);
-        const double ci = (i == N - 1) ? 0.0 : e * rden;
-        g[i] = rden;
-        m[i] = -ai * rden;
-        n[i] = -ci;
-        cprev = ci;
+    double *g = s_t[0], *m = s_t[1], *n = s_t[2], *z = s_t[3];
+    if (threadIdx.x == 0) {
+        double cprev = 0.0, dp = 0.0;
+        for (int i = 0; i < N; ++i) {
+            const double bi = (i == 0) ? dg - gam : (i == N - 1 ? dg - e * e / gam : dg);
+            const double ai = (i == 0) ? 0.0 : e;
+            const double rden = 1.0 / (bi - ai * cprev);
+            const double ci = (i == N - 1) ? 0.0 : e * rden;
+            const double mi = -ai * rden;
+            g[i] = rden;
+            m[i] = mi;
+            n[i] = -ci;
+            cprev = ci;
+            // z = B^-1 u, u = (gamma, 0, ..., 0, e)
+            const double ui = (i == 0) ? gam : (i == N - 1 ? e : 0.0);
+            dp = rden * ui + mi * dp;
+            z[i] = dp;
+        }
+        for (int i = N - 2; i >= 0; --i) {
+            dp = z[i] + n[i] * dp;
+            z[i] = dp;
+        }
+        const double vf = e / gam;
+        blk[4 * Nmax] = vf;
+        blk[4 * Nmax + 1] = 1.0 / (1.0 + z[0] + vf * z[N - 1]);
     }
-    // z = B^-1 u, u = (gamma, 0, ..., 0, e)
-    double dp = 0.0;
-    for (int i = 0; i < N; ++i) {
-        const double ui = (i == 0) ? gam : (i == N - 1 ? e : 0.0);
-        dp = g[i] * ui + m[i] * dp;
-        z[i] = dp;
-    }
-    for (int i = N - 2; i >= 0; --i) z[i] = z[i] + n[i] * z[i + 1];
-    const double vf = e / gam;
-    blk[4 * Nmax] = vf;
-    blk[4 * Nmax + 1] = 1.0 / (1.0 + z[0] + vf * z[N - 1]);
+    __syncthreads();
+    for (int i = threadIdx.x; i < N; i += 64)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) blk[q * Nmax + i] = s_t[q][i];
 }
 
 // One tile of kCycTx periodic lines of one field per block, staged in LDS
@@ -1179,7 +1191,7 @@ static hipError_t launch_cn_coef(nspnp_state *s, const Stage &st) {
     k_cn_coef<<<dim3(3, 3, (unsigned)s->nmem), 256, 0, s->stream>>>(s->d, s->tb, s->d_phys, s->clock, s->cn_coef, cs,
                                                                    s->mstride);
     if (s->cfg.implicit_xz)
-        k_cyc_coef<<<dim3(1, 3, (unsigned)s->nmem), 64, 0, s->stream>>>(s->d, s->d_phys, s->clock, s->cyc, cs,
+        k_cyc_coef<<<dim3(4, 3, (unsigned)s->nmem), 64, 0, s->stream>>>(s->d, s->d_phys, s->clock, s->cyc, cs,
                                                                         s->mstride);
     s->cn_fresh = true;
     return hipGetLastError();
