@@ -374,8 +374,9 @@ struct nspnp_state {
     void *r[5];          // Crank-Nicolson right-hand sides, state type
     double *psi;         // pressure increment (n, FP64)
     double2 *spec;       // two half spectra, 2 * nxh * nz * M
-    double2 *fac;        // Thomas pivots (1/den, c') of both elliptic operators, [kind][mode][row]
-    double *cpv;         // c' alone, [kind][row][mode], for the fused y-march (NULL: not kept)
+    double2 *fac;        // Thomas pivots (1/den, c') of both elliptic operators, [kind][mode][row] (NULL: not
+                         // kept; FP64 handles, for the lane-split solve)
+    double *gv;          // 1/den alone, [kind][row][mode]
     double2 *mu;         // volume mean of the pinned pressure mode, per problem (fused y-march)
     double *cn_coef;     // Crank-Nicolson recurrence coefficients, cn_stage_stride(M) per stage
     bool cn_fresh = false;  // cn_coef matches the device dt of the current step

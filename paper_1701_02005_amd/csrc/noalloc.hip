@@ -54,7 +54,7 @@ ScratchLayout scratch_layout(const nspnp_config *c) {
     o = align256(o + tables_len((int)M, c->nx, c->nz) * sizeof(double));
     L.phys = o;
     o = align256(o + sizeof(Phys));
-    L.fac = o;  // [kind][mode][row], both operators
+    L.fac = o;  // pivots of both operators (1/den takes half of the room)
     o = align256(o + 2 * (size_t)nspec * sizeof(double2));
     L.spec = o;  // one half spectrum
     o = align256(o + (size_t)nspec * sizeof(double2));
@@ -111,11 +111,11 @@ extern "C" int nspnp_poisson_solve_noalloc(const nspnp_config *cfg, int32_t kind
     s.fp64 = true;  // caller arrays are FP64 (the state type is not involved)
     s.wsize = 8;
     s.d_phys = (Phys *)(D.ptr + L.phys);
-    s.fac = (double2 *)(D.ptr + L.fac);
+    s.fac = nullptr;  // (the row-slab solve needs 1/den alone)
+    s.gv = (double *)(D.ptr + L.fac);
     s.spec = (double2 *)(D.ptr + L.spec);
     s.clock = nullptr;  // read only by divergence sources
-    s.cpv = nullptr;    // (the default mode-solve method keeps no row-order c' table)
-    s.mu = nullptr;
+    s.mu = nullptr;  // (no fused march)
     s.host_tables.swap(D.host_tab);
     fill_tables(&s, (double *)(D.ptr + L.tab));  // also sets the device table pointers
     if (!D.have_grid || !same_grid(D.grid, *cfg)) {

@@ -747,17 +747,17 @@ inline unsigned plane_threads(int nx, int nz) {
 
 // One thread per (kind, mode): the forward pass of Thomas' algorithm on the
 // matrix only.
-// Also c' alone in row order, cpv[kind][row][mode], for the fused y-march
-// (cpv_all may be NULL).
-__global__ void __launch_bounds__(256) k_thomas_factors(Dims d, Tables tb, double2 *fac_all, double *cpv_all,
+// Also g alone in row order, gv[kind][row][mode], for the row-slab solve and
+// the fused y-march.  (fac_all may be NULL: not kept.)
+__global__ void __launch_bounds__(256) k_thomas_factors(Dims d, Tables tb, double2 *fac_all, double *gv_all,
                                                         size_t ms) {
     const int kind = blockIdx.y;
     const int64_t nmodes = (int64_t)d.nxh * d.nz;
     const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (m >= nmodes) return;
     const int M = d.M;
-    double2 *fac = member_ptr(fac_all, ms) + ((int64_t)kind * nmodes + m) * M;
-    double *cpv = cpv_all ? member_ptr(cpv_all, ms) + (int64_t)kind * M * nmodes + m : nullptr;
+    double2 *fac = fac_all ? member_ptr(fac_all, ms) + ((int64_t)kind * nmodes + m) * M : nullptr;
+    double *gv = member_ptr(gv_all, ms) + (int64_t)kind * M * nmodes + m;
     const int kx = (int)(m / d.nz), kz = (int)(m % d.nz);  // spectrum layout [j][kx][kz]
     const double k2 = tb.kx2[kx] + tb.kz2[kz];
     const bool pin = (kind == 0 && m == 0);
@@ -777,11 +777,153 @@ __global__ void __launch_bounds__(256) k_thomas_factors(Dims d, Tables tb, doubl
             up = 0.0;
         }
         const double den = B - lo * cprev;
-        const double cj = up / den;
-        fac[j] = make_double2(1.0 / den, cj);
-        if (cpv) cpv[(int64_t)j * nmodes] = cj;
+        const double cj = up / den, g = 1.0 / den;
+        if (fac) fac[j] = make_double2(g, cj);
+        gv[(int64_t)j * nmodes] = g;
         cprev = cj;
     }
+}
+
+// ---- y solve over slabs of rows in registers ----
+// A block owns kModes neighbouring modes of one problem over all rows; its
+// threads split the rows into slabs of L, as the Crank-Nicolson solve does
+// (k_cn_rows), with the recurrence coefficients of each mode from its g,
+//   m_j = -lo_j g_j,   c'_j = up_j g_j:
+// the forward sweep with a zero input, the slabs' inputs from their exits and
+// the products of m through LDS, the input times the running product; then
+// the backward sweep the same way.  Every access is a run of 512 bytes.
+// Reads the spectrum and g once and writes the spectrum once, 40 bytes per
+// mode and row against 48 and two dozen shuffles per mode for the lane-split
+// solve below: bound by memory, 0.86 ms at 512 x 385 x 512 (4.7 TB/s; 1.13 ms
+// lane-split, 0.94 with tiles of 8 modes), one problem of 256 x 193 x 256 in
+// 45 us (63).  A run's own solves on up to kLaneRows rows stay lane-split
+// (0.111 against 0.087 ms at 256 x 193 x 256): it keeps their results, down
+// to plane means that are zero but for rounding, bit for bit what they were.
+constexpr int kModes = 32;
+constexpr int kLaneRows = 320;
+
+template <int L>
+__global__ void __launch_bounds__(1024) k_mode_rows(Dims d, Tables tb, PoissonBatch b, double2 *spec_all,
+                                                    const double *gv_all, int64_t nspec) {
+    extern __shared__ double2 s_m[];  // exits up, exits down [slab][kModes], products up, down, then lo, up
+    const uint3 blk = xcd_block3();
+    const int prob = (int)blk.y, kind = b.kind[prob];
+    const int M = d.M, S = (int)blockDim.x / kModes;
+    const int c = (int)threadIdx.x % kModes, slab = (int)threadIdx.x / kModes, j0 = slab * L;
+    const unsigned nm = (unsigned)d.nxh * (unsigned)d.nz;
+    const unsigned m = blk.x * (unsigned)kModes + (unsigned)c;
+    const bool in = m < nm;
+    const unsigned um = in ? m : nm - 1;  // (past the last mode: it again, not stored)
+    double2 *spec = member_ptr_at(spec_all, b.ms, blk.z) + prob * nspec;
+    const double *gv = gv_all + (int64_t)kind * M * nm;
+    // offsets within one spectrum: rows * modes < 2^32 for every supported
+    // grid; rows past the last repeat it (their g is taken as zero)
+    auto off = [&](int t) { return (unsigned)(j0 + t < M ? j0 + t : M - 1) * nm + um; };
+    double2 x[L];
+    double g[L];
+#pragma unroll
+    for (int t = 0; t < L; ++t) x[t] = spec[off(t)];
+#pragma unroll
+    for (int t = 0; t < L; ++t) g[t] = gv[off(t)];
+    double2 *s_f = s_m, *s_b = s_f + S * kModes;
+    double *s_pf = (double *)(s_b + S * kModes), *s_pb = s_pf + S * kModes;
+    double *s_lo = s_pb + S * kModes, *s_up = s_lo + S * L;
+    for (int j = threadIdx.x; j < S * L; j += blockDim.x) {
+        s_lo[j] = (j > 0 && j < M) ? tb.lyc_lo[j] : 0.0;
+        s_up[j] = (j < M - 1) ? tb.lyc_up[j] : 0.0;
+    }
+    __syncthreads();
+    const bool pin = kind == 0 && um == 0;  // the pressure's (0, 0) mode: row 0 holds 0
+    const double scale = 1.0 / ((double)d.nx * (double)d.nz);
+    double P = 1.0, dx_ = 0.0, dy_ = 0.0;
+#pragma unroll
+    for (int t = 0; t < L; ++t) {
+        if (j0 + t >= M) g[t] = 0.0;
+        const double mm = -s_lo[j0 + t] * g[t];
+        const double gs = (pin && j0 + t == 0) ? 0.0 : g[t] * scale;
+        dx_ = gs * x[t].x + mm * dx_;
+        dy_ = gs * x[t].y + mm * dy_;
+        x[t] = make_double2(dx_, dy_);
+        P *= mm;
+    }
+    const int at = slab * kModes + c;
+    s_f[at] = make_double2(dx_, dy_);
+    s_pf[at] = P;
+    __syncthreads();
+    double vx = 0.0, vy = 0.0;
+    for (int t = 0; t < slab; ++t) {
+        const double2 e = s_f[t * kModes + c];
+        const double p = s_pf[t * kModes + c];
+        vx = e.x + p * vx;
+        vy = e.y + p * vy;
+    }
+#pragma unroll
+    for (int t = 0; t < L; ++t) {
+        const double mm = -s_lo[j0 + t] * g[t];
+        vx *= mm;
+        vy *= mm;
+        x[t].x += vx;
+        x[t].y += vy;
+    }
+    if (pin && j0 == 0) g[0] = 0.0;  // (its row does not couple upwards)
+    P = 1.0;
+    dx_ = dy_ = 0.0;
+#pragma unroll
+    for (int t = L - 1; t >= 0; --t) {
+        const double nn = -s_up[j0 + t] * g[t];
+        dx_ = x[t].x + nn * dx_;
+        dy_ = x[t].y + nn * dy_;
+        x[t] = make_double2(dx_, dy_);
+        P *= nn;
+    }
+    s_b[at] = make_double2(dx_, dy_);
+    s_pb[at] = P;
+    __syncthreads();
+    vx = vy = 0.0;
+    for (int t = S - 1; t > slab; --t) {
+        const double2 e = s_b[t * kModes + c];
+        const double p = s_pb[t * kModes + c];
+        vx = e.x + p * vx;
+        vy = e.y + p * vy;
+    }
+#pragma unroll
+    for (int t = L - 1; t >= 0; --t) {
+        const double nn = -s_up[j0 + t] * g[t];
+        vx *= nn;
+        vy *= nn;
+        x[t].x += vx;
+        x[t].y += vy;
+    }
+    if (kind == 0 && blk.x == 0) {  // zero volume mean of the pressure-type solution
+        double sx = 0.0, sy = 0.0, vol = 0.0;
+#pragma unroll
+        for (int t = 0; t < L; ++t) {
+            const double h = (j0 + t < M) ? tb.dn[j0 + t] : 0.0;
+            sx += x[t].x * h;
+            sy += x[t].y * h;
+            vol += h;
+        }
+        if (c == 0) {
+            s_f[slab] = make_double2(sx, sy);
+            s_pf[slab] = vol;
+        }
+        __syncthreads();
+        if (pin) {
+            sx = sy = vol = 0.0;
+            for (int t = 0; t < S; ++t) {
+                sx += s_f[t].x;
+                sy += s_f[t].y;
+                vol += s_pf[t];
+            }
+            const double mx = sx / vol, my = sy / vol;
+#pragma unroll
+            for (int t = 0; t < L; ++t) x[t] = make_double2(x[t].x - mx, x[t].y - my);
+        }
+    }
+    if (!in) return;
+#pragma unroll
+    for (int t = 0; t < L; ++t)
+        if (j0 + t < M) spec[off(t)] = x[t];
 }
 
 // Solve of one tile of tm consecutive modes of one problem: the tile's rows
@@ -988,7 +1130,7 @@ __global__ void __launch_bounds__(256) k_thomas_tile(Dims d, Tables tb, PoissonB
 // the pivot formed on the way, den_j = B_j - lo_j c'_{j-1}, c'_j = up_j / den_j
 // (the arithmetic of k_thomas_factors), and d'_j = (r_j - lo_j d'_{j-1}) /
 // den_j stored in place.  The backward kernel marches down: x_j = d'_j -
-// c'_j x_{j+1} with c' from the precomputed row-order table, then the row's
+// c'_j x_{j+1} with c' = up g from the precomputed row-order table, then the row's
 // inverse z transform.  Each solve thus reads and writes the spectrum twice
 // (plus c'), against three times for separate z transforms and mode solves.
 // The pressure problem's (0, 0) mode is pinned at row 0; its volume mean
@@ -1105,14 +1247,14 @@ __global__ void __launch_bounds__(256) k_zthomas_fwd(Dims d, Tables tb, FftPlan 
 
 template <bool kR8>
 __global__ void __launch_bounds__(256) k_zthomas_bwd(Dims d, Tables tb, FftPlan pl, PoissonBatch b,
-                                                     double2 *spec_all, const double *cpv_all, const double2 *mu_all,
+                                                     double2 *spec_all, const double *gv_all, const double2 *mu_all,
                                                      int64_t nspec, int tk) {
     extern __shared__ double2 sm[];
     const int prob = blockIdx.y, kind = b.kind[prob];
     const int nz = d.nz, nxh = d.nxh, M = d.M;
     const int64_t nmodes = (int64_t)nxh * nz;
     double2 *spec = member_ptr(spec_all, b.ms) + prob * nspec;
-    const double *cpv = member_ptr(cpv_all, b.ms) + (int64_t)kind * M * nmodes;
+    const double *gv = gv_all + (int64_t)kind * M * nmodes;  // (one grid: member 0's)
     const int kx0 = (int)blockIdx.x * tk;
     const int nt = (nxh - kx0 < tk) ? nxh - kx0 : tk;
     const int pts = nt * nz;
@@ -1124,7 +1266,7 @@ __global__ void __launch_bounds__(256) k_zthomas_bwd(Dims d, Tables tb, FftPlan 
     double2 xprev[kZtQ], nd[kZtQ];
     double nc[kZtQ];
     auto row_ptr = [&](int j) { return spec + ((int64_t)j * nxh + kx0) * nz; };
-    auto cp_ptr = [&](int j) { return cpv + (int64_t)j * nmodes + (int64_t)kx0 * nz; };
+    auto cp_ptr = [&](int j) { return gv + (int64_t)j * nmodes + (int64_t)kx0 * nz; };
     {
         const double2 *r0 = row_ptr(M - 1);
         const double *c0 = cp_ptr(M - 1);
@@ -1137,17 +1279,19 @@ __global__ void __launch_bounds__(256) k_zthomas_bwd(Dims d, Tables tb, FftPlan 
         }
     }
     for (int j = M - 1; j >= 0; --j) {
+        const double up = (j < M - 1) ? uniform_load(tb.lyc_up, j) : 0.0;
 #pragma unroll
         for (int q = 0; q < kZtQ; ++q) {
             const int e = (int)threadIdx.x + q * (int)blockDim.x;
             if (e < pts) {
-                const double2 x = make_double2(nd[q].x - nc[q] * xprev[q].x, nd[q].y - nc[q] * xprev[q].y);
+                const double cj = (pin && q == 0 && j == 0) ? 0.0 : up * nc[q];
+                const double2 x = make_double2(nd[q].x - cj * xprev[q].x, nd[q].y - cj * xprev[q].y);
                 xprev[q] = x;
                 sm[e] = (pin && q == 0) ? make_double2(x.x - mu.x, x.y - mu.y) : x;
             }
         }
         __syncthreads();
-        if (j > 0) {  // the next row's d' and c' land during this row's passes
+        if (j > 0) {  // the next row's d' and g land during this row's passes
             const double2 *rn = row_ptr(j - 1);
             const double *cn = cp_ptr(j - 1);
 #pragma unroll
@@ -1226,7 +1370,7 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
         return false;
     };
     const bool r8x = has_r8(s->planx), r8z = has_r8(s->planz);
-    const bool march = s->tiles.thomas == 0 && s->cpv && s->mu;  // z transforms fused with the y solve
+    const bool march = s->tiles.thomas == 0 && s->mu;  // z transforms fused with the y solve
     const bool planes = !march && plane_fits(s);
     const dim3 gp((unsigned)d.M, (unsigned)b.nprob, (unsigned)nmem);
     const size_t ldsp = plane_lds(d.nx, d.nz);
@@ -1272,9 +1416,9 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
         {
             ProfScope prof_(s, K_FFTZ_INV);
             if (r8z)
-                k_zthomas_bwd<true><<<gy, 256, lds, s->stream>>>(d, s->tb, s->planz, b, s->spec, s->cpv, s->mu, nspec, tk);
+                k_zthomas_bwd<true><<<gy, 256, lds, s->stream>>>(d, s->tb, s->planz, b, s->spec, s->gv, s->mu, nspec, tk);
             else
-                k_zthomas_bwd<false><<<gy, 256, lds, s->stream>>>(d, s->tb, s->planz, b, s->spec, s->cpv, s->mu, nspec,
+                k_zthomas_bwd<false><<<gy, 256, lds, s->stream>>>(d, s->tb, s->planz, b, s->spec, s->gv, s->mu, nspec,
                                                                  tk);
         }
     } else {
@@ -1291,7 +1435,21 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
             else k_fft_z<false><<<gz, 256, ldsz, s->stream>>>(d, s->planz, s->tb.twz, s->spec, nspec, tk, 0, b.ms);
         }
         const int64_t nmodes = (int64_t)d.nxh * d.nz;
-        {
+        // (caller-owned right-hand sides take the row-slab solve in FP64 too)
+        if (d.M > kLaneRows || !s->fac || b.src[0].type == SRC_REAL) {
+            ProfScope prof_(s, K_THOMAS);
+            // 8 to 32 slabs (256 to 1024 threads a block)
+            const int L = d.M <= 32 ? 4 : (d.M <= 128 ? 8 : ((d.M <= 192 || (d.M > 256 && d.M <= 384)) ? 12 : 16));
+            const int S = (d.M + L - 1) / L;
+            const dim3 gm((unsigned)((nmodes + kModes - 1) / kModes), (unsigned)b.nprob, (unsigned)nmem);
+            const size_t ldsm = (size_t)S * kModes * 48 + 2 * (size_t)S * L * sizeof(double);
+#define NSPNP_MR(LL) k_mode_rows<LL><<<gm, S * kModes, ldsm, s->stream>>>(d, s->tb, b, s->spec, s->gv, nspec)
+            if (L == 4) NSPNP_MR(4);
+            else if (L == 8) NSPNP_MR(8);
+            else if (L == 12) NSPNP_MR(12);
+            else NSPNP_MR(16);
+#undef NSPNP_MR
+        } else {
             ProfScope prof_(s, K_THOMAS);
             const int lanes = d.M <= 16 ? 16 : (d.M <= 32 ? 32 : 64);
             int tm = thomas_tile_modes(d.M, s->tiles.thomas);
@@ -1385,7 +1543,7 @@ hipError_t prime_x_transform_lds(int lds_max) {
 hipError_t launch_thomas_factors(nspnp_state *s) {
     const int64_t nmodes = (int64_t)s->d.nxh * s->d.nz;
     const dim3 g((unsigned)((nmodes + 255) / 256), 2, (unsigned)s->nmem);
-    k_thomas_factors<<<g, 256, 0, s->stream>>>(s->d, s->tb, s->fac, s->cpv, s->mstride);
+    k_thomas_factors<<<g, 256, 0, s->stream>>>(s->d, s->tb, s->fac, s->gv, s->mstride);
     return hipGetLastError();
 }
 
