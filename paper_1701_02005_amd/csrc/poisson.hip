@@ -1371,7 +1371,7 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
     };
     const bool r8x = has_r8(s->planx), r8z = has_r8(s->planz);
     const bool march = s->tiles.thomas == 0 && s->mu;  // z transforms fused with the y solve
-    const bool planes = !march && plane_fits(s);
+    const bool planes = !march && !r8x && !r8z && plane_fits(s);  // (its passes: radix 4, 2 and 3)
     const dim3 gp((unsigned)d.M, (unsigned)b.nprob, (unsigned)nmem);
     const size_t ldsp = plane_lds(d.nx, d.nz);
     const unsigned tp = plane_threads(d.nx, d.nz);
