@@ -487,6 +487,287 @@ __global__ void __launch_bounds__(256) k_fft_x_c2r(Dims d, Tables tb, FftPlan pl
     }
 }
 
+// ---- x lines of 256 and 512 points: one wave per line pair, in registers ----
+// A block of 4 waves owns 8 consecutive lines; a wave transforms one pair with
+// N / 64 values per lane, all passes in registers (radix 4 for 256 points,
+// radix 8 for 512, as make_plan has them) and exchanges within the wave
+// through its own piece of LDS, without block barriers.  Each exchange has an
+// index map that keeps its writes and reads free of bank conflicts.  The 8
+// lines make whole 128-byte lines of the [j][kx][kz] spectrum.  Butterflies
+// and their order are those of the general kernels: the same bit for bit.
+// Bound by memory; many independent waves with every load of a line in flight
+// beat tiles behind block barriers: 512 x 385 x 512 FP64 forward 1.49 -> 1.03
+// ms (5.4 TB/s), inverse 0.95 -> 0.56 ms (5.7 TB/s), mixed 1.14 -> 0.66 and
+// 0.93 -> 0.50 ms; 256 x 193 x 256 FP64 165 -> 130 and 106 -> 62 us.
+// Which product of a complex multiplication is rounded before the fused
+// multiply-add is written out, as the general kernels' compilation has it.
+__device__ __forceinline__ double2 twiddle(double2 a, double2 w, bool inv) {
+    if (inv) return make_double2(__builtin_fma(a.x, w.x, a.y * w.y), __builtin_fma(a.y, w.x, -(a.x * w.y)));
+    return make_double2(__builtin_fma(a.x, w.x, -(a.y * w.y)), __builtin_fma(a.y, w.x, a.x * w.y));
+}
+template <int R>
+__device__ __forceinline__ void wave_dft(double2 *v, bool inv) {
+    if constexpr (R == 4) {
+        dft_small<4>(v, inv);
+    } else {  // as dft_small<8>
+        double2 e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
+        dft_small<4>(e, inv);
+        dft_small<4>(o, inv);
+        const double c = 0.70710678118654752440;  // cos(pi / 4)
+        double2 t1, t3;
+        if (inv) {
+            const double m1 = o[1].y * c, m3 = o[3].y * -c;
+            t1 = make_double2(__builtin_fma(o[1].x, c, -m1), __builtin_fma(c, o[1].x, m1));
+            t3 = make_double2(__builtin_fma(-c, o[3].x, m3), __builtin_fma(c, o[3].x, m3));
+        } else {
+            const double m1 = o[1].x * c, m3 = o[3].y * c;
+            t1 = make_double2(__builtin_fma(c, o[1].y, m1), __builtin_fma(o[1].y, c, -m1));
+            t3 = make_double2(__builtin_fma(-c, o[3].x, m3), __builtin_fma(o[3].x, -c, -m3));
+        }
+        const double2 t2 = rot(o[2], inv);
+        v[0] = cadd(e[0], o[0]);
+        v[4] = csub(e[0], o[0]);
+        v[1] = cadd(e[1], t1);
+        v[5] = csub(e[1], t1);
+        v[2] = cadd(e[2], t2);
+        v[6] = csub(e[2], t2);
+        v[3] = cadd(e[3], t3);
+        v[7] = csub(e[3], t3);
+    }
+}
+
+template <int N>
+struct WaveFft {
+    static constexpr int R = N / 64;                 // values per lane and radix
+    static constexpr int kSlots = N == 256 ? 328 : 568;  // LDS slots of one pair (8 mod 16)
+    // slot of element i on the way from the pass with input stride Ns
+    static __device__ __forceinline__ int slot(int i, int Ns) {
+        if (Ns == 1) return i + (i >> 4);
+        if (N == 256) return Ns == 4 ? i + 4 * (i >> 4) : i;
+        return i + 8 * (i >> 6);
+    }
+    // v[r] holds element lane + 64 r before and after; z: the pair's slots
+    static __device__ __forceinline__ void run(double2 *v, double2 *z, const double2 *__restrict__ tw, int lane,
+                                               bool inv) {
+        wave_dft<R>(v, inv);  // (the first pass's twiddles are 1)
+        int off = R - 1;
+#pragma unroll
+        for (int Ns = R; Ns < N; Ns *= R) {
+            const int pNs = Ns / R, blk = lane / pNs, pk = lane % pNs, k = lane % Ns;
+            double2 w[R];
+#pragma unroll
+            for (int r = 1; r < R; ++r) w[r] = tw[off + (r - 1) * Ns + k];
+            off += Ns * (R - 1);
+#pragma unroll
+            for (int r = 0; r < R; ++r) z[slot(blk * Ns + pk + r * pNs, pNs)] = v[r];
+            wave_sync();
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[r] = z[slot(lane + 64 * r, pNs)];
+            wave_sync();
+#pragma unroll
+            for (int r = 1; r < R; ++r) v[r] = twiddle(v[r], w[r], inv);
+            wave_dft<R>(v, inv);
+        }
+    }
+    // orders the wave's LDS accesses (they execute in order; this keeps the
+    // compiler from moving them)
+    static __device__ __forceinline__ void wave_sync() {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+};
+
+// The right-hand side of lines (j, k) and (j, k + 1) at x = lane + 64 r, r in
+// [r0, r0 + B), all loads ahead of the arithmetic (that of r2c_stage).  j and
+// k are wave-uniform.
+template <typename T, int S, int N, int B>
+__device__ __forceinline__ void line_rhs(const PoissonSrc &src, const Dims &d, const Tables &tb, double ch, double sc,
+                                         double idx, double idz, int j, int k, int lane, int r0, double2 *v) {
+    const int M = d.M, nz = d.nz;
+    const size_t upl = (size_t)d.plane, q0 = (size_t)j * upl + (size_t)k * N;
+    unsigned i[B];
+#pragma unroll
+    for (int t = 0; t < B; ++t) i[t] = (unsigned)(lane + 64 * (r0 + t));
+    double val[B][2];
+    if constexpr (S == SRC_REAL) {
+        const double *a = (const double *)src.a + q0;
+#pragma unroll
+        for (int t = 0; t < B; ++t) {
+            val[t][0] = a[i[t]];
+            val[t][1] = (a + N)[i[t]];
+        }
+    } else if constexpr (S == SRC_CHARGE) {
+        const T *cp = (const T *)src.a + q0, *cm = (const T *)src.b + q0;
+        T xp[B][2], xm[B][2];
+#pragma unroll
+        for (int t = 0; t < B; ++t)
+#pragma unroll
+            for (int l = 0; l < 2; ++l) {
+                xp[t][l] = ld_once(cp + l * N + i[t]);
+                xm[t][l] = ld_once(cm + l * N + i[t]);
+            }
+#pragma unroll
+        for (int t = 0; t < B; ++t)
+#pragma unroll
+            for (int l = 0; l < 2; ++l) val[t][l] = ch * ((double)xp[t][l] - (double)xm[t][l]);
+        // wall values g of phi, as in r2c_stage
+        if (src.wall && (j == 0 || j == M - 1)) {
+            const double *gw = src.wall + (j == 0 ? 0 : upl) + (size_t)k * N;
+#pragma unroll
+            for (int t = 0; t < B; ++t)
+#pragma unroll
+                for (int l = 0; l < 2; ++l) {
+                    const double g = (gw + l * N)[i[t]];
+                    val[t][l] -= (j == 0 ? tb.lyc_lo[0] : tb.lyc_up[M - 1]) * g;
+                }
+        }
+    } else {
+        const T *u0 = (const T *)src.a + q0, *v0 = (const T *)src.b + q0, *w0 = (const T *)src.c + q0;
+        const T *w2 = (k + 2 == nz) ? (const T *)src.c + (size_t)j * upl : w0 + 2 * N;  // line k + 2
+        const bool has_up = j + 1 < M, has_dn = j > 0;
+        const T *v1 = has_up ? v0 + upl : v0;
+        T ux[B][2], uc[B][2], vt[B][2], vb[B][2], wc[B][3];
+#pragma unroll
+        for (int t = 0; t < B; ++t) {
+            const unsigned ip = (i[t] + 1 == (unsigned)N) ? 0u : i[t] + 1;
+#pragma unroll
+            for (int l = 0; l < 2; ++l) {
+                ux[t][l] = (u0 + l * N)[ip];
+                uc[t][l] = (u0 + l * N)[i[t]];
+                vt[t][l] = (v1 + l * N)[i[t]];
+                vb[t][l] = (v0 + l * N)[i[t]];
+                wc[t][l] = (w0 + l * N)[i[t]];
+            }
+            wc[t][2] = w2[i[t]];
+        }
+        const double idn = uniform_load(tb.idn, j);
+#pragma unroll
+        for (int t = 0; t < B; ++t)
+#pragma unroll
+            for (int l = 0; l < 2; ++l) {
+                const double tt = has_up ? (double)vt[t][l] : 0.0;
+                const double bb = has_dn ? (double)vb[t][l] : 0.0;
+                const double div = ((double)ux[t][l] - (double)uc[t][l]) * idx + (tt - bb) * idn +
+                                   ((double)wc[t][l + 1] - (double)wc[t][l]) * idz;
+                val[t][l] = div * sc;
+            }
+    }
+#pragma unroll
+    for (int t = 0; t < B; ++t) v[r0 + t] = make_double2(val[t][0], val[t][1]);
+}
+
+template <typename T, int N>
+__global__ void __launch_bounds__(256) k_lines_r2c(Dims d, Tables tb, PoissonBatch b, const double *clock,
+                                                   double2 *spec, int64_t nspec) {
+    using F = WaveFft<N>;
+    constexpr int nxh = N / 2 + 1;
+    __shared__ double2 s_z[4 * F::kSlots];
+    const int prob = blockIdx.y;
+    PoissonSrc src = b.src[prob];
+    src.a = member_ptr(src.a, b.ms);
+    src.b = member_ptr(src.b, b.ms);
+    src.c = member_ptr(src.c, b.ms);
+    if (src.wall) src.wall = member_ptr(src.wall, b.ms);
+    clock = member_ptr(clock, b.ms);
+    const double ch = member_ptr(b.phys, b.ms)->ch;
+    double2 *out = member_ptr(spec, b.ms) + prob * nspec;
+    const int nz = d.nz, nlines = d.M * nz;
+    const int line0 = (int)xcd_tile(blockIdx.x, gridDim.x) * 8;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const double sc = (src.type == SRC_DIV) ? ((src.alp > 0.0) ? 1.0 / (src.alp * clock[1]) : src.fixed) : 0.0;
+    const double idx = 1.0 / d.dx, idz = 1.0 / d.dz;
+    {
+        // (a pair past the last line repeats the last one and is not stored)
+        const int line = line0 + 2 * wave < nlines ? line0 + 2 * wave : nlines - 2;
+        const int j = line / nz, k = line - j * nz;
+        double2 v[F::R];
+        double2 *z = s_z + wave * F::kSlots;
+        constexpr int B = 4;
+#pragma unroll
+        for (int r0 = 0; r0 < F::R; r0 += B) {
+            if (src.type == SRC_DIV) line_rhs<T, SRC_DIV, N, B>(src, d, tb, ch, sc, idx, idz, j, k, lane, r0, v);
+            else if (src.type == SRC_CHARGE) line_rhs<T, SRC_CHARGE, N, B>(src, d, tb, ch, sc, idx, idz, j, k, lane, r0, v);
+            else line_rhs<T, SRC_REAL, N, B>(src, d, tb, ch, sc, idx, idz, j, k, lane, r0, v);
+        }
+        F::run(v, z, tb.twx, lane, false);
+#pragma unroll
+        for (int r = 0; r < F::R; ++r) z[lane + 64 * r] = v[r];
+    }
+    __syncthreads();
+    // A = (Z_k + conj(Z_{N-k}))/2 for the even lines, B = (Z_k - conj(Z_{N-k}))/(2i)
+    // for the odd ones; a thread keeps its line
+    const int l = threadIdx.x & 7, line = line0 + l;
+    if (line >= nlines) return;
+    const int j = line / nz, k = line - j * nz;
+    const double2 *z = s_z + (l >> 1) * F::kSlots;
+    double2 *o = out + (int64_t)j * nxh * nz + k;
+#pragma unroll 4
+    for (int kk = threadIdx.x >> 3; kk < nxh; kk += 32) {
+        const double2 zk = z[kk], zc = z[kk == 0 ? 0 : N - kk];
+        o[(int64_t)kk * nz] = (l & 1) ? make_double2(0.5 * (zk.y + zc.y), -0.5 * (zk.x - zc.x))
+                                      : make_double2(0.5 * (zk.x + zc.x), 0.5 * (zk.y - zc.y));
+    }
+}
+
+template <typename T, int N>
+__global__ void __launch_bounds__(256) k_lines_c2r(Dims d, Tables tb, PoissonBatch b, const double2 *spec,
+                                                   int64_t nspec) {
+    using F = WaveFft<N>;
+    constexpr int nxh = N / 2 + 1, kIt = (nxh + 31) / 32, kLine = N / 2 + 2;  // (2 mod 16)
+    __shared__ double2 s_z[4 * F::kSlots];
+    const int prob = blockIdx.y;
+    const double2 *in = member_ptr(spec, b.ms) + prob * nspec;
+    const int nz = d.nz, nlines = d.M * nz;
+    const int line0 = (int)xcd_tile(blockIdx.x, gridDim.x) * 8;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    {
+        const int l = threadIdx.x & 7, line = line0 + l < nlines ? line0 + l : nlines - 1;
+        const int j = line / nz, k = line - j * nz, k0 = threadIdx.x >> 3;
+        const double2 *p = in + (int64_t)j * nxh * nz + k;
+        double2 v[kIt];
+#pragma unroll
+        for (int t = 0; t < kIt; ++t) v[t] = ld_once(p + (int64_t)(k0 + 32 * t < nxh ? k0 + 32 * t : nxh - 1) * nz);
+        double2 *o = s_z + (l >> 1) * F::kSlots + (l & 1) * kLine;
+#pragma unroll
+        for (int t = 0; t < kIt; ++t)
+            if (k0 + 32 * t < nxh) o[k0 + 32 * t] = v[t];
+    }
+    __syncthreads();
+    if (line0 + 2 * wave >= nlines) return;
+    double2 *z = s_z + wave * F::kSlots;
+    double2 v[F::R];
+#pragma unroll
+    for (int r = 0; r < F::R; ++r) {
+        const int kk = lane + 64 * r;
+        const bool lower = kk < nxh;
+        const int src = lower ? kk : N - kk;
+        double2 A = z[src], B = z[kLine + src];
+        if (!lower) {  // Hermitian continuation of a real line's spectrum
+            A.y = -A.y;
+            B.y = -B.y;
+        }
+        v[r] = make_double2(A.x - B.y, A.y + B.x);  // Z = A + i B
+    }
+    F::wave_sync();
+    F::run(v, z, tb.twx, lane, true);
+    const int64_t la = (int64_t)(line0 + 2 * wave) * N;
+    const bool as_state = b.out_state[prob] != 0;
+    double *o64 = (double *)member_ptr(b.out[prob], b.ms) + la;
+    T *ot = (T *)member_ptr(b.out[prob], b.ms) + la;
+#pragma unroll
+    for (int r = 0; r < F::R; ++r) {
+        const int i = lane + 64 * r;
+        if (as_state) {
+            st_once(ot + i, (T)v[r].x);
+            st_once(ot + N + i, (T)v[r].y);
+        } else {
+            st_once(o64 + i, v[r].x);
+            st_once(o64 + N + i, v[r].y);
+        }
+    }
+}
+
 // ---- z direction: contiguous complex lines, tiles of tk lines ----
 // Persistent blocks: each block loops over tiles (j, kx0..kx0+tk-1) of its
 // problem and member; the next tile's values are loaded into registers while
@@ -1375,7 +1656,21 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
     const dim3 gp((unsigned)d.M, (unsigned)b.nprob, (unsigned)nmem);
     const size_t ldsp = plane_lds(d.nx, d.nz);
     const unsigned tp = plane_threads(d.nx, d.nz);
-    if (planes) {
+    // 256 and 512 points: a wave per line pair
+    const bool lines = !planes && (d.nx == 256 || d.nx == 512);
+    const dim3 gl((unsigned)((nlines + 7) / 8), (unsigned)b.nprob, (unsigned)nmem);
+    if (lines) {
+        ProfScope prof_(s, K_FFTX_FWD);
+#define NSPNP_LR(TT, NN) k_lines_r2c<TT, NN><<<gl, 256, 0, s->stream>>>(d, s->tb, b, s->clock, s->spec, nspec)
+        if (s->fp64) {
+            if (d.nx == 256) NSPNP_LR(double, 256);
+            else NSPNP_LR(double, 512);
+        } else {
+            if (d.nx == 256) NSPNP_LR(float, 256);
+            else NSPNP_LR(float, 512);
+        }
+#undef NSPNP_LR
+    } else if (planes) {
         ProfScope prof_(s, K_FFTX_FWD);
         const hipError_t e = lds_opt_in(s->fp64 ? (const void *)k_plane_fwd<double> : (const void *)k_plane_fwd<float>,
                                         ldsp, s->lds_max);
@@ -1490,7 +1785,18 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
             else k_fft_z<false><<<gz, 256, ldsz, s->stream>>>(d, s->planz, s->tb.twz, s->spec, nspec, tk, 1, b.ms);
         }
     }
-    if (planes) {
+    if (lines) {
+        ProfScope prof_(s, K_FFTX_INV);
+#define NSPNP_LC(TT, NN) k_lines_c2r<TT, NN><<<gl, 256, 0, s->stream>>>(d, s->tb, b, s->spec, nspec)
+        if (s->fp64) {
+            if (d.nx == 256) NSPNP_LC(double, 256);
+            else NSPNP_LC(double, 512);
+        } else {
+            if (d.nx == 256) NSPNP_LC(float, 256);
+            else NSPNP_LC(float, 512);
+        }
+#undef NSPNP_LC
+    } else if (planes) {
         ProfScope prof_(s, K_FFTX_INV);
         const hipError_t e = lds_opt_in(s->fp64 ? (const void *)k_plane_inv<double> : (const void *)k_plane_inv<float>,
                                         ldsp, s->lds_max);
