@@ -219,8 +219,17 @@ __global__ void __launch_bounds__(kRedThreads) k_dt_final(int nparts, const doub
 // row, each its part of the row), every load of an element issued before its
 // arithmetic; the block sums go to part[(j * chunks + chunk) * Q + q] and
 // k_plane_close combines a row's in order, so results repeat bit for bit.
-// 256 x 193 x 256 FP64: 454 us with one block a row and every quantity.
+// Blocks run through the rows of one part before the next (row_chunk), on one
+// XCD: the row above or below comes from its L2 (256 x 193 x 256 FP64: ion
+// sums 107 -> 99 us, energies 273 -> 235 us against rows dealt out to all
+// XCDs).  With one block a row and every quantity they took 454 and 820 us.
 constexpr int kEnergyQ = 3;
+
+__device__ __forceinline__ void row_chunk(int M, int &j, int &chunk) {
+    const int t = (int)xcd_tile(blockIdx.x, gridDim.x);
+    chunk = t / M;
+    j = t - chunk * M;
+}
 
 // Combines a value over the block (fixed order: lanes, then waves); valid in thread 0.
 enum { OP_SUM = 0, OP_MAX, OP_MIN };
@@ -253,8 +262,14 @@ __global__ void __launch_bounds__(kRedThreads) k_plane(Dims d, const Phys *phys,
     u = member_ptr(u, ms); v = member_ptr(v, ms); w = member_ptr(w, ms);
     cp = member_ptr(cp, ms); cm = member_ptr(cm, ms); phi = member_ptr(phi, ms); part = member_ptr(part, ms);
     const Phys ph = *member_ptr(phys, ms);
-    const int M = d.M, chunk = blockIdx.x;
-    const int j = (kWhat == PLANE_WALL && blockIdx.y) ? M - 1 : (int)blockIdx.y;
+    const int M = d.M;
+    int j, chunk;
+    if (kWhat == PLANE_WALL) {  // the first and the last row
+        chunk = (int)blockIdx.x >> 1;
+        j = (blockIdx.x & 1) ? M - 1 : 0;
+    } else {
+        row_chunk(M, j, chunk);
+    }
     const unsigned pl = (unsigned)d.plane, nx = (unsigned)d.nx, nz = (unsigned)d.nz;
     const unsigned per = (pl + chunks - 1) / chunks, lo = chunk * per, hi = lo + per < pl ? lo + per : pl;
     const unsigned base = (unsigned)j * pl;
@@ -390,7 +405,9 @@ __global__ void __launch_bounds__(kRedThreads) k_energy(Dims d, const Phys *phys
     u = member_ptr(u, ms); v = member_ptr(v, ms); w = member_ptr(w, ms);
     cp = member_ptr(cp, ms); cm = member_ptr(cm, ms); phi = member_ptr(phi, ms); part = member_ptr(part, ms);
     const Phys ph = *member_ptr(phys, ms);
-    const int j = blockIdx.y, chunk = blockIdx.x, M = d.M;
+    const int M = d.M;
+    int j, chunk;
+    row_chunk(M, j, chunk);
     const unsigned pl = (unsigned)d.plane, nx = (unsigned)d.nx, nz = (unsigned)d.nz;
     const unsigned per = (pl + chunks - 1) / chunks, lo = chunk * per, hi = lo + per < pl ? lo + per : pl;
     const unsigned base = (unsigned)j * pl;
@@ -561,7 +578,7 @@ hipError_t launch_plane_sums(nspnp_state *s, int what, double *dev_out) {
     const int M = s->d.M;
     if (dev_out != s->red || (int64_t)M * kPlaneQ * (chunks + 1) > s->nred) return hipErrorInvalidValue;
     double *part = dev_out + (size_t)M * kPlaneQ;
-    const dim3 g((unsigned)chunks, what == PLANE_WALL ? 2u : (unsigned)M, (unsigned)s->nmem);
+    const dim3 g((unsigned)chunks * (what == PLANE_WALL ? 2u : (unsigned)M), 1, (unsigned)s->nmem);
     auto go = [&](auto zero) {
         using T = decltype(zero);
         const T *f[6];
@@ -587,7 +604,7 @@ hipError_t launch_energy_sums(nspnp_state *s, double *dev_out) {
     const int M = s->d.M;
     if (dev_out != s->red || (int64_t)M * (4 + kEnergyQ * chunks) > s->nred) return hipErrorInvalidValue;
     double *part = dev_out + 4 * (size_t)M;
-    const dim3 g((unsigned)chunks, (unsigned)M, (unsigned)s->nmem);
+    const dim3 g((unsigned)(chunks * M), 1, (unsigned)s->nmem);
     auto go = [&](auto zero) {
         using T = decltype(zero);
         k_energy<T><<<g, kRedThreads, 0, s->stream>>>(s->d, s->d_phys, s->tb, (const T *)s->f[0], (const T *)s->f[1],

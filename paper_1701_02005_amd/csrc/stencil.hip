@@ -493,15 +493,15 @@ inline int cn_tile_cols(int threads) { return threads > 256 ? 32 : 16; }
 // a local sweep per lane followed by a 6-step scan of affine maps across the
 // wave (x -> T + Q x composed lane by lane) and a second local sweep from the
 // correct incoming value.  Finally q += x with coalesced stores.
-// Staging in batches of kCnBatch loads per thread in flight per wait, measured
-// best (more registers cost occupancy).
+// Staging in batches of kCnBatch loads per thread in flight per wait: 6,
+// measured best (more registers cost occupancy), or all of up to 64 rows.
 // Bound by memory: 0.273 ms at 256 x 193 x 256 (5.5 TB/s).
-constexpr int kCnBatch = 6;
 constexpr int kCnLaneRows = 320;
 
 template <int kCnTx, int kCnMaxR>
 __global__ void __launch_bounds__(512) k_cn_scan(CnArgs a) {
     using T = double;
+    constexpr int kCnBatch = kCnMaxR == 1 ? 4 : 6;
     extern __shared__ double s_r[];
     const uint3 blk = xcd_block3();  // adjacent column tiles share an L2
     const int f = (int)blk.y;
@@ -1438,8 +1438,12 @@ static hipError_t launch_cyc(nspnp_state *s, const Stage &st, int dir, int out_r
 
 // Lane-scan Crank-Nicolson solve of the five fields (tiles of 16 or 32 columns).
 static hipError_t launch_cn_lane(nspnp_state *s, const CnArgs &a) {
-    const int tb = s->tiles.cn;
-    const int tcols = cn_tile_cols(tb);
+    // up to two blocks per CU: 8 waves on 16 columns, so that a wave solves two
+    // columns one after the other instead of four (the result is the same;
+    // 16 x 17 x 16 7.1 -> 5.8 us, latency)
+    const bool small = (s->d.plane + 15) / 16 * 5 * s->nmem <= 512;
+    const int tb = small ? 512 : s->tiles.cn;
+    const int tcols = small ? 16 : cn_tile_cols(tb);
     const dim3 g((unsigned)((s->d.plane + tcols - 1) / tcols), 5, (unsigned)s->nmem);
     const size_t lds = (size_t)s->d.M * (tcols + 1) * sizeof(double);
     if (lds > (size_t)s->lds_max) return hipErrorInvalidValue;
