@@ -100,8 +100,8 @@ __device__ __forceinline__ void dft_small<3>(double2 *v, bool inv) {
 }
 
 // q = e / d and r = e % d for 0 <= e, d < 2^22 from a float reciprocal
-// rd = 1/d: the product is within half a unit of the true quotient, so one
-// correction step makes the result exact (integer division has no hardware
+// rd = 1/d (to one unit in the last place): the product is within a unit of
+// the true quotient, so one correction step makes the result exact (integer division has no hardware
 // instruction on the GPU).
 __device__ __forceinline__ void divmod(int e, int d, float rd, int &q, int &r) {
     q = (int)((float)e * rd);
@@ -121,7 +121,7 @@ struct Div {
     int d, sh;
     float rd;
     __device__ explicit Div(int dd) : d(dd), sh(((dd & (dd - 1)) == 0) ? __builtin_ctz((unsigned)dd) : -1),
-                                      rd(1.0f / (float)dd) {}
+                                      rd(__builtin_amdgcn_rcpf((float)dd)) {}
     __device__ __forceinline__ void split(int e, int &q, int &r) const {
         if (sh >= 0) {
             q = e >> sh;
@@ -848,66 +848,196 @@ __global__ void __launch_bounds__(256) k_fft_z(Dims d, FftPlan pl, const double2
 
 // ---- whole planes: x and z transforms of one row in one kernel ----
 // A block owns one row j of one problem and member, all of its nx x nz plane:
-// forward, the right-hand side of every line, the x transforms of the line
-// pairs, the half spectrum and its z transforms, one contiguous store;
-// inverse, the same backwards.  Each saves a pass over the spectrum (read and
-// write) and a launch.  Lanes run over the lines, whose LDS stride is odd in
-// 16-byte units: every access of a pass is free of bank conflicts, and a
-// wave's twiddles are one or two entries.  The butterflies and their order
-// are those of the separate kernels, so the results are the same bit for bit.
-// 32 members of 64 x 65 x 64 and 48 x 49 x 48 (mean of both): forward 75 us
-// (4.4 TB/s at the larger), inverse 55, against 85 and 94 for two kernels;
-// a 32 x 33 x 32 grid 10 and 7 us against 12 and 11 (latency and launches).
-// (kOwn: as k_fft_z, whose direction is a run-time value, see dft3)
-template <int R, bool kOwn>
-__device__ __forceinline__ void plane_pass(const double2 *__restrict__ src, double2 *__restrict__ dst, int N, int nl,
-                                           const Div &dnl, int ld, int Ns, const double2 *__restrict__ tw, bool inv) {
-    const int NR = N / R;
-    const Div dNs(Ns);
-    for (int e = threadIdx.x; e < nl * NR; e += blockDim.x) {
-        int jb, line, blk, k;
-        dnl.split(e, jb, line);
+// forward, the x transforms of the line pairs, the half spectrum and its z
+// transforms; inverse, the same backwards.  Each saves a pass over the
+// spectrum (read and write) and a launch.  The first and the last pass of the
+// spectrum's or the solution's own direction run along the lines and take
+// their values from memory or store them there; the half spectrum is split,
+// or joined, as the first pass of the second direction reads it: 5 or 6 trips
+// through LDS for 64 x 64.  The passes between run across the lines, whose LDS
+// stride is odd in 16-byte units: free of bank conflicts, and a wave's
+// twiddles are one or two entries.  The butterflies and their order are those of the separate
+// kernels, so the results are the same bit for bit.
+// 32 members of 64 x 65 x 64 and of 48 x 49 x 48, mixed form: forward 102 and
+// 48 us (3.0 TB/s: LDS passes and their latency), inverse 79 and 37; 119 and
+// 60, 87 and 43 with every pass through LDS and the right-hand side formed
+// element by element; a 32 x 33 x 32 grid in FP64 7.1 and 6.3 us (10.8 and
+// 7.3; two kernels each way 12 and 11: latency and launches).
+struct PlanePass {
+    int N, nl, Ns;     // points per line, lines, product of the radices before
+    bool first, last;
+};
+
+// ld(line, jb, NR, v) and st(line, base, Ns, v) move elements jb + r NR and
+// base + r Ns of a line.  kOwn: as k_fft_z, whose direction is a run-time
+// value, see dft3.
+template <int R, bool kOwn, class Ld, class St>
+__device__ __forceinline__ void plane_pass(const PlanePass &p, bool along, const double2 *__restrict__ tw, bool inv,
+                                           const Ld &ld, const St &st) {
+    const int NR = p.N / R;
+    const Div by(along ? NR : p.nl), dNs(p.Ns);
+    for (int e = threadIdx.x; e < p.nl * NR; e += blockDim.x) {
+        int hi, lo, blk, k;
+        by.split(e, hi, lo);
+        const int line = along ? hi : lo, jb = along ? lo : hi;
         dNs.split(jb, blk, k);
-        const double2 *in = src + line * ld + jb;
         double2 v[R];
+        ld(line, jb, NR, v);
+        if (!p.first) {  // (the first pass's twiddles are 1)
 #pragma unroll
-        for (int r = 0; r < R; ++r) v[r] = in[r * NR];
-#pragma unroll
-        for (int r = 1; r < R; ++r) {
-            double2 w = tw[(r - 1) * Ns + k];
-            if (inv) w.y = -w.y;
-            v[r] = cmul(v[r], w);
+            for (int r = 1; r < R; ++r) v[r] = twiddle(v[r], tw[(r - 1) * p.Ns + k], inv);
         }
         if constexpr (R == 3) dft3<kOwn>(v, inv);
         else dft_small<R>(v, inv);
-        double2 *out = dst + line * ld + blk * Ns * R + k;
-#pragma unroll
-        for (int r = 0; r < R; ++r) out[r * Ns] = v[r];
+        st(line, __mul24(blk, p.Ns * R) + k, p.Ns, v);
     }
 }
 
-// nl lines of length N (stride ld) in b0; returns the buffer (0 or 1) holding
-// the result.
-template <bool kOwn>
+// Position of element i of a line between the first pass and the second: the
+// first pass of radix 4, along the line, writes every fourth element.
+__device__ __forceinline__ int plane_slot(int i, int sw) { return i ^ ((i >> 4) & sw); }
+
+// nl lines of length N (LDS stride ld), buffers b0 and b1 in turn, the first
+// pass writes b0; returns the buffer (0 or 1) of the last pass.
+// kIn: the first pass runs along the lines, kOut: the last, and stores through
+// fst instead of LDS (no barrier after it).
+template <bool kOwn, bool kIn, bool kOut, class Ld, class St>
 __device__ __forceinline__ int plane_fft(double2 *b0, double2 *b1, int N, int nl, int ld, const FftPlan &pl,
-                                         const double2 *tw, bool inv) {
-    double2 *src = b0, *dst = b1;
-    const Div dnl(nl);
-    int which = 0, Ns = 1, off = 0;
+                                         const double2 *tw, bool inv, const Ld &fld, const St &fst) {
+    double2 *dst = b0, *src = b1;
+    int which = 0, off = 0;
+    const int sw = (kIn && pl.nstages > 1 && pl.radix[0] == 4) ? 3 : 0;
+    PlanePass p{N, nl, 1, true, false};
     for (int s = 0; s < pl.nstages; ++s) {
         const int R = pl.radix[s];
-        if (R == 4) plane_pass<4, kOwn>(src, dst, N, nl, dnl, ld, Ns, tw + off, inv);
-        else if (R == 2) plane_pass<2, kOwn>(src, dst, N, nl, dnl, ld, Ns, tw + off, inv);
-        else plane_pass<3, kOwn>(src, dst, N, nl, dnl, ld, Ns, tw + off, inv);
-        off += Ns * (R - 1);
+        p.first = s == 0;
+        p.last = s + 1 == pl.nstages;
+        const int swl = s == 1 ? sw : 0, sws = s == 0 ? sw : 0;
+        auto go = [&](auto rr) {
+            constexpr int RR = decltype(rr)::value;
+            plane_pass<RR, kOwn>(
+                p, (kIn && p.first) || (kOut && p.last), tw + off, inv,
+                [&](int line, int jb, int NR, double2(&v)[RR]) {
+                    if (p.first) {
+                        fld(line, jb, NR, v);
+                    } else {
+                        const double2 *in = src + __mul24(line, ld);
+#pragma unroll
+                        for (int r = 0; r < RR; ++r) v[r] = in[plane_slot(jb + r * NR, swl)];
+                    }
+                },
+                [&](int line, int base, int Ns, const double2(&v)[RR]) {
+                    if (kOut && p.last) {
+                        fst(line, base, Ns, v);
+                    } else {
+                        double2 *out = dst + __mul24(line, ld);
+#pragma unroll
+                        for (int r = 0; r < RR; ++r) out[plane_slot(base + r * Ns, sws)] = v[r];
+                    }
+                });
+        };
+        if (R == 4) go(std::integral_constant<int, 4>{});
+        else if (R == 2) go(std::integral_constant<int, 2>{});
+        else go(std::integral_constant<int, 3>{});
+        off += p.Ns * (R - 1);
+        p.Ns *= R;
+        if (kOut && p.last) break;
         __syncthreads();
         double2 *t = src;
         src = dst;
         dst = t;
         which ^= 1;
-        Ns *= R;
     }
-    return which;
+    return which ^ 1;
+}
+
+// An element of a plane: a block-uniform base and an offset of 32 bits in
+// bytes, which the loads and stores take as they are.
+template <typename P>
+__device__ __forceinline__ P *in_plane(P *base, unsigned i) {
+    using C = std::conditional_t<std::is_const_v<P>, const char, char>;
+    return (P *)((C *)base + (size_t)(i * (unsigned)sizeof(P)));
+}
+
+// The right-hand side of row j (that of r2c_stage) into LDS as line pairs, V
+// neighbouring elements of both lines of a pair per thread and load (the
+// state's fields and, nx being even, their lines are aligned to 2 elements,
+// and to 4 where nx is a multiple of 4).
+template <typename T, int S, int V>
+__device__ __forceinline__ void plane_rhs(const PoissonSrc &src, const Dims &d, const Tables &tb, double ch, double sc,
+                                          double idx, double idz, int j, double2 *buf, int ld) {
+    using TV = T __attribute__((ext_vector_type(V)));
+    const int M = d.M, nz = d.nz;
+    const unsigned un = (unsigned)d.nx;
+    const size_t upl = (size_t)d.plane, row = (size_t)j * upl;
+    const Div dv(d.nx / V);
+    for (int e = threadIdx.x; e < nz / 2 * (d.nx / V); e += blockDim.x) {
+        int p, i;
+        dv.split(e, p, i);
+        i *= V;
+        const unsigned o0 = 2u * (unsigned)__mul24(p, d.nx) + (unsigned)i, o[2] = {o0, o0 + un};
+        double val[V][2];
+        if constexpr (S == SRC_REAL) {
+            const double *a = (const double *)src.a + row;
+#pragma unroll
+            for (int l = 0; l < 2; ++l)
+#pragma unroll
+                for (int t = 0; t < V; ++t) val[t][l] = *in_plane(a, o[l] + t);
+        } else if constexpr (S == SRC_CHARGE) {
+            const T *cp = (const T *)src.a + row, *cm = (const T *)src.b + row;
+            TV xp[2], xm[2];
+#pragma unroll
+            for (int l = 0; l < 2; ++l) {
+                xp[l] = ld_once((const TV *)in_plane(cp, o[l]));
+                xm[l] = ld_once((const TV *)in_plane(cm, o[l]));
+            }
+#pragma unroll
+            for (int l = 0; l < 2; ++l)
+#pragma unroll
+                for (int t = 0; t < V; ++t) val[t][l] = ch * ((double)xp[l][t] - (double)xm[l][t]);
+            if (src.wall && (j == 0 || j == M - 1)) {  // wall values g of phi
+                const double *gw = src.wall + (j == 0 ? 0 : upl);
+#pragma unroll
+                for (int l = 0; l < 2; ++l)
+#pragma unroll
+                    for (int t = 0; t < V; ++t) {
+                        const double g = *in_plane(gw, o[l] + t);
+                        val[t][l] -= (j == 0 ? tb.lyc_lo[0] : tb.lyc_up[M - 1]) * g;
+                    }
+            }
+        } else {
+            const T *u0 = (const T *)src.a + row, *v0 = (const T *)src.b + row, *w0 = (const T *)src.c + row;
+            const bool has_up = j + 1 < M, has_dn = j > 0;
+            const T *v1 = has_up ? v0 + upl : v0;
+            const unsigned ip = (unsigned)i + V == un ? 0u : (unsigned)i + V;  // the element after the last
+            const unsigned o2 = (2 * p + 2 == nz) ? (unsigned)i : o[1] + un;   // line 2p + 2
+            TV uc[2], vt[2], vb[2], wc[3];
+            T un1[2];
+#pragma unroll
+            for (int l = 0; l < 2; ++l) {
+                uc[l] = *(const TV *)in_plane(u0, o[l]);
+                un1[l] = *in_plane(u0, o[l] - (unsigned)i + ip);
+                vt[l] = *(const TV *)in_plane(v1, o[l]);
+                vb[l] = *(const TV *)in_plane(v0, o[l]);
+                wc[l] = *(const TV *)in_plane(w0, o[l]);
+            }
+            wc[2] = *(const TV *)in_plane(w0, o2);
+            const double idn = uniform_load(tb.idn, j);
+#pragma unroll
+            for (int l = 0; l < 2; ++l)
+#pragma unroll
+                for (int t = 0; t < V; ++t) {
+                    const T ux = t + 1 < V ? uc[l][t + 1 < V ? t + 1 : 0] : un1[l];
+                    const double tt = has_up ? (double)vt[l][t] : 0.0;
+                    const double bb = has_dn ? (double)vb[l][t] : 0.0;
+                    const double div = ((double)ux - (double)uc[l][t]) * idx + (tt - bb) * idn +
+                                       ((double)wc[l + 1][t] - (double)wc[l][t]) * idz;
+                    val[t][l] = div * sc;
+                }
+        }
+#pragma unroll
+        for (int t = 0; t < V; ++t) buf[__mul24(p, ld) + i + t] = make_double2(val[t][0], val[t][1]);
+    }
 }
 
 // LDS slots of one of the two buffers: the line pairs or the half spectrum.
@@ -938,32 +1068,45 @@ __global__ void __launch_bounds__(1024) k_plane_fwd(Dims d, Tables tb, FftPlan p
     stage_twiddles(s_twz, tb.twz, nz);
     const double sc = (src.type == SRC_DIV) ? ((src.alp > 0.0) ? 1.0 / (src.alp * clock[1]) : src.fixed) : 0.0;
     const double idx = 1.0 / d.dx, idz = 1.0 / d.dz;
-    const int64_t pair0 = (int64_t)j * np;
-    if (src.type == SRC_DIV) r2c_stage<T, SRC_DIV>(src, d, tb, ch, sc, idx, idz, pair0, np, sm, ldx);
-    else if (src.type == SRC_CHARGE) r2c_stage<T, SRC_CHARGE>(src, d, tb, ch, sc, idx, idz, pair0, np, sm, ldx);
-    else r2c_stage<T, SRC_REAL>(src, d, tb, ch, sc, idx, idz, pair0, np, sm, ldx);
+    if (src.type == SRC_REAL) plane_rhs<T, SRC_REAL, 1>(src, d, tb, ch, sc, idx, idz, j, sm + bs, ldx);
+    else if (sizeof(T) == 4 && (nx & 3) == 0) {
+        if (src.type == SRC_DIV) plane_rhs<T, SRC_DIV, 4>(src, d, tb, ch, sc, idx, idz, j, sm + bs, ldx);
+        else plane_rhs<T, SRC_CHARGE, 4>(src, d, tb, ch, sc, idx, idz, j, sm + bs, ldx);
+    } else {
+        if (src.type == SRC_DIV) plane_rhs<T, SRC_DIV, 2>(src, d, tb, ch, sc, idx, idz, j, sm + bs, ldx);
+        else plane_rhs<T, SRC_CHARGE, 2>(src, d, tb, ch, sc, idx, idz, j, sm + bs, ldx);
+    }
     __syncthreads();
-    int w = plane_fft<false>(sm, sm + bs, nx, np, ldx, plx, s_twx, false);
+    const double2 *f = sm + bs;
+    const int w = plane_fft<false, false, false>(
+        sm, sm + bs, nx, np, ldx, plx, s_twx, false,
+        [&](int p, int jb, int NR, auto &v) {
+            constexpr int R = (int)(sizeof(v) / sizeof(v[0]));
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[r] = f[__mul24(p, ldx) + jb + r * NR];
+        },
+        [](int, int, int, auto &) {});
     const double2 *z = sm + w * bs;
-    double2 *o = sm + (1 - w) * bs;  // [kx][kz]
-    const Div dnp(np), dnz(nz);
-    for (int e = threadIdx.x; e < np * nxh; e += blockDim.x) {
-        int kk, p;
-        dnp.split(e, kk, p);
-        const double2 zk = z[p * ldx + kk];
-        const double2 zc = z[p * ldx + (kk == 0 ? 0 : nx - kk)];
-        // A = (Z_k + conj(Z_{N-k}))/2, B = (Z_k - conj(Z_{N-k}))/(2i)
-        o[kk * ldz + 2 * p] = make_double2(0.5 * (zk.x + zc.x), 0.5 * (zk.y - zc.y));
-        o[kk * ldz + 2 * p + 1] = make_double2(0.5 * (zk.y + zc.y), -0.5 * (zk.x - zc.x));
-    }
-    __syncthreads();
-    const int wz = plane_fft<true>(o, sm + w * bs, nz, nxh, ldz, plz, s_twz, false);
-    z = sm + ((1 - w) ^ wz) * bs;
-    for (int e = threadIdx.x; e < nxh * nz; e += blockDim.x) {
-        int kk, k;
-        dnz.split(e, kk, k);
-        out[e] = z[kk * ldz + k];
-    }
+    plane_fft<true, false, true>(
+        sm + (1 - w) * bs, sm + w * bs, nz, nxh, ldz, plz, s_twz, false,
+        [&](int kk, int jb, int NR, auto &v) {
+            constexpr int R = (int)(sizeof(v) / sizeof(v[0]));
+            const int kc = kk == 0 ? 0 : nx - kk;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                // A = (Z_k + conj(Z_{N-k}))/2 for the even lines, B = (Z_k - conj(Z_{N-k}))/(2i)
+                // for the odd ones
+                const int k = jb + r * NR;
+                const double2 zk = z[__mul24(k >> 1, ldx) + kk], zc = z[__mul24(k >> 1, ldx) + kc];
+                v[r] = (k & 1) ? make_double2(0.5 * (zk.y + zc.y), -0.5 * (zk.x - zc.x))
+                               : make_double2(0.5 * (zk.x + zc.x), 0.5 * (zk.y - zc.y));
+            }
+        },
+        [&](int kk, int base, int Ns, auto &v) {
+            constexpr int R = (int)(sizeof(v) / sizeof(v[0]));
+#pragma unroll
+            for (int r = 0; r < R; ++r) *in_plane(out, (unsigned)(__mul24(kk, nz) + base + r * Ns)) = v[r];
+        });
 }
 
 template <typename T>
@@ -978,66 +1121,62 @@ __global__ void __launch_bounds__(1024) k_plane_inv(Dims d, Tables tb, FftPlan p
     double2 *s_twx = sm + 2 * bs, *s_twz = s_twx + nx;
     stage_twiddles(s_twx, tb.twx, nx);
     stage_twiddles(s_twz, tb.twz, nz);
-    const Div dnp(np), dnz(nz), dnx(nx);
-    const int ns = nxh * nz, bd = (int)blockDim.x;
-    for (int e0 = threadIdx.x; e0 < ns; e0 += 4 * bd) {  // (past the end: the first value, dropped)
-        double2 v[4];
+    const int w = plane_fft<true, true, false>(
+        sm, sm + bs, nz, nxh, ldz, plz, s_twz, true,
+        [&](int kk, int jb, int NR, auto &v) {
+            constexpr int R = (int)(sizeof(v) / sizeof(v[0]));
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = ld_once(in + (e0 + u * bd < ns ? e0 + u * bd : 0));
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            int kk, k;
-            dnz.split(e0 + u * bd, kk, k);
-            if (e0 + u * bd < ns) sm[kk * ldz + k] = v[u];
-        }
-    }
-    __syncthreads();
-    const int w = plane_fft<true>(sm, sm + bs, nz, nxh, ldz, plz, s_twz, true);
+            for (int r = 0; r < R; ++r) v[r] = ld_once(in_plane(in, (unsigned)(__mul24(kk, nz) + jb + r * NR)));
+        },
+        [](int, int, int, auto &) {});
     const double2 *o = sm + w * bs;
-    double2 *f = sm + (1 - w) * bs;  // [pair][x]
-    for (int e = threadIdx.x; e < np * nx; e += bd) {
-        int kk, p;
-        dnp.split(e, kk, p);
-        const bool lower = kk < nxh;
-        const int src = lower ? kk : nx - kk;
-        double2 A = o[src * ldz + 2 * p];
-        double2 B = o[src * ldz + 2 * p + 1];
-        if (!lower) {  // Hermitian continuation of a real line's spectrum
-            A.y = -A.y;
-            B.y = -B.y;
-        }
-        f[p * ldx + kk] = make_double2(A.x - B.y, A.y + B.x);  // Z = A + i B
-    }
-    __syncthreads();
-    const int wx = plane_fft<false>(f, sm + w * bs, nx, np, ldx, plx, s_twx, true);
-    const double2 *z = sm + ((1 - w) ^ wx) * bs;
     const bool as_state = b.out_state[prob] != 0;
-    double *o64 = (double *)member_ptr(b.out[prob], b.ms);
-    T *ot = (T *)member_ptr(b.out[prob], b.ms);
-    const int64_t l0 = (int64_t)j * nz;
-    for (int e = threadIdx.x; e < np * nx; e += bd) {
-        int p, i;
-        dnx.split(e, p, i);
-        const int64_t qa = (l0 + 2 * p) * nx + i, qb = qa + nx;
-        const double2 v = z[p * ldx + i];
-        if (as_state) {
-            st_once(ot + qa, (T)v.x);
-            st_once(ot + qb, (T)v.y);
-        } else {
-            st_once(o64 + qa, v.x);
-            st_once(o64 + qb, v.y);
-        }
-    }
+    double *o64 = (double *)member_ptr(b.out[prob], b.ms) + (int64_t)j * d.plane;
+    T *ot = (T *)member_ptr(b.out[prob], b.ms) + (int64_t)j * d.plane;
+    plane_fft<false, false, true>(
+        sm + (1 - w) * bs, sm + w * bs, nx, np, ldx, plx, s_twx, true,
+        [&](int p, int jb, int NR, auto &v) {
+            constexpr int R = (int)(sizeof(v) / sizeof(v[0]));
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int kk = jb + r * NR;
+                const bool lower = kk < nxh;
+                const double2 *q = o + __mul24(lower ? kk : nx - kk, ldz) + 2 * p;
+                double2 A = q[0], B = q[1];
+                if (!lower) {  // Hermitian continuation of a real line's spectrum
+                    A.y = -A.y;
+                    B.y = -B.y;
+                }
+                v[r] = make_double2(A.x - B.y, A.y + B.x);  // Z = A + i B
+            }
+        },
+        [&](int p, int base, int Ns, auto &v) {
+            constexpr int R = (int)(sizeof(v) / sizeof(v[0]));
+            const unsigned q = 2u * (unsigned)__mul24(p, nx) + (unsigned)base;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const unsigned qa = q + (unsigned)(r * Ns), qb = qa + (unsigned)nx;
+                if (as_state) {
+                    st_once(in_plane(ot, qa), (T)v[r].x);
+                    st_once(in_plane(ot, qb), (T)v[r].y);
+                } else {
+                    st_once(in_plane(o64, qa), v[r].x);
+                    st_once(in_plane(o64, qb), v[r].y);
+                }
+            }
+        });
 }
 
 // Whole planes where two blocks fit a CU's LDS (64 x 64: 70 KB a block).
 inline bool plane_fits(const nspnp_state *s) {
     return plane_lds(s->d.nx, s->d.nz) <= std::min((size_t)80 << 10, (size_t)s->lds_max);
 }
-// One butterfly of the wider direction's radix-4 passes per thread.
-inline unsigned plane_threads(int nx, int nz) {
-    const int work = std::max(nz / 2 * nx, (nx / 2 + 1) * nz) / 4;
-    return (unsigned)std::min(1024, std::max(64, (work + 63) / 64 * 64));
+// One butterfly per thread of the pass that has the most of them.
+inline unsigned plane_threads(const nspnp_state *s) {
+    int work = 64;
+    for (int q = 0; q < s->planx.nstages; ++q) work = std::max(work, s->d.nz / 2 * (s->d.nx / s->planx.radix[q]));
+    for (int q = 0; q < s->planz.nstages; ++q) work = std::max(work, s->d.nxh * (s->d.nz / s->planz.radix[q]));
+    return (unsigned)std::min(1024, (work + 63) / 64 * 64);
 }
 
 // ---- y direction: one tridiagonal solve per (kx, kz) mode ----
@@ -1679,7 +1818,7 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
     const bool planes = !march && !r8x && !r8z && plane_fits(s);  // (its passes: radix 4, 2 and 3)
     const dim3 gp((unsigned)d.M, (unsigned)b.nprob, (unsigned)nmem);
     const size_t ldsp = plane_lds(d.nx, d.nz);
-    const unsigned tp = plane_threads(d.nx, d.nz);
+    const unsigned tp = plane_threads(s);
     // 256 and 512 points: a wave per line pair
     const bool lines = !planes && (d.nx == 256 || d.nx == 512);
     const dim3 gl((unsigned)((nlines + 7) / 8), (unsigned)b.nprob, (unsigned)nmem);

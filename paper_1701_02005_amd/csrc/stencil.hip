@@ -1440,7 +1440,7 @@ static hipError_t launch_cyc(nspnp_state *s, const Stage &st, int dir, int out_r
 static hipError_t launch_cn_lane(nspnp_state *s, const CnArgs &a) {
     // up to two blocks per CU: 8 waves on 16 columns, so that a wave solves two
     // columns one after the other instead of four (the result is the same;
-    // 16 x 17 x 16 7.1 -> 5.8 us, latency)
+    // 16 x 17 x 12 7 to 8 -> 5.8 us, latency)
     const bool small = (s->d.plane + 15) / 16 * 5 * s->nmem <= 512;
     const int tb = small ? 512 : s->tiles.cn;
     const int tcols = small ? 16 : cn_tile_cols(tb);

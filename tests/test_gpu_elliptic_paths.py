@@ -1,6 +1,7 @@
 """The elliptic solve on the paths that its sizes choose: whole-plane
 transforms (planes of up to two blocks per CU's LDS) and their limit, radices
-2, 3, 4 and 8 in either direction, lines of 256 and 512 points (a wave each), groups of 16, 32 and 64 lanes per mode, and,
+2, 3, 4 and 8 in either direction, lines of 256 and 512 points (a wave each),
+groups of 16, 32 and 64 lanes per mode, and,
 for caller-owned right-hand sides and above 320 rows, slabs of rows in
 registers at the edges of every slab height.  Against the oracle.  Bar: the
 wall-normal operator's condition number, about 1e6 on 512 stretched rows,
