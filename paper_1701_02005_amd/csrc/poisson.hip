@@ -1370,6 +1370,204 @@ __global__ void __launch_bounds__(1024) k_mode_rows(Dims d, Tables tb, PoissonBa
         if (j0 + t < M) spec[off(t)] = x[t];
 }
 
+// ---- y solve of ensembles: a mode's column in the registers of two lanes ----
+// A wave owns kColModes neighbouring modes of one problem and member, all
+// rows; a lane holds the real or the imaginary parts of the lower or the upper
+// L rows of one mode, every load of them in flight at once (runs of 256
+// bytes).  The scans of the lane-split solve below become loops over the rows
+// in place, the same operations in the same order on up to 64 rows, so the
+// results are its bit for bit, without its 80 moves through LDS per mode.  The
+// four waves of a block solve four members, which share the modes' pivots
+// (staged in LDS).
+// 32 members of 64 x 65 x 64 and of 48 x 49 x 48: 72 and 36 us (3.8 TB/s)
+// against 137 and 58 lane-split, which is bound by those moves.
+constexpr int kColModes = 16;
+constexpr int kColRows = 64;
+
+// The other half's value, lane for lane: the lower half's in the upper one
+// (kDown: the upper half's in the lower one), and `own` in the half itself.
+template <bool kDown>
+__device__ __forceinline__ double other_half(double v, double own) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v), w = __builtin_bit_cast(uint64_t, own);
+    // the upper half of the first and the lower half of the second change places
+    unsigned r[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const unsigned x = (unsigned)(u >> (32 * i)), o = (unsigned)(w >> (32 * i));
+        r[i] = kDown ? __builtin_amdgcn_permlane32_swap(x, o, false, false)[1]
+                     : __builtin_amdgcn_permlane32_swap(o, x, false, false)[0];
+    }
+    return __builtin_bit_cast(double, (uint64_t)r[1] << 32 | (uint64_t)r[0]);
+}
+
+template <int L>
+__global__ void __launch_bounds__(256, 2) k_mode_columns(Dims d, Tables tb, PoissonBatch b, double2 *spec_all,
+                                                         const double2 *fac_all, int64_t nspec, int nmem) {
+    constexpr int NR = 2 * L, LD = NR + 1;
+    __shared__ double s_g[kColModes * LD], s_c[kColModes * LD];  // pivots [mode][row]
+    __shared__ double s_lo[NR], s_v[4][2][64];
+    const int prob = (int)blockIdx.y, kind = b.kind[prob];
+    const int M = d.M;
+    const unsigned nm = (unsigned)d.nxh * (unsigned)d.nz, m0 = blockIdx.x * (unsigned)kColModes;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int mem = (int)blockIdx.z * 4 + wave;
+    const double2 *fac = fac_all + ((int64_t)kind * nm + m0) * M;
+    const int nc = (int)(nm - m0 < (unsigned)kColModes ? nm - m0 : (unsigned)kColModes);
+    constexpr int kF = kColModes * NR / 256;  // pivots per thread
+    double2 f[kF];
+#pragma unroll
+    for (int u = 0; u < kF; ++u) {
+        const int e = (int)threadIdx.x + 256 * u, c = e / NR, j = e % NR;
+        f[u] = fac[(c < nc && j < M) ? c * M + j : 0];
+    }
+    const int half = lane >> 5, r0 = half * L, cm = (lane & 31) >> 1;
+    // lanes past the last mode work on it again and do not store
+    const unsigned um = m0 + (unsigned)(cm < nc ? cm : nc - 1);
+    // row t of the lower half is wave-uniform (the spectrum of up to 64 rows has
+    // less than 2^32 bytes); rows past the last read the lower half's
+    char *base = (char *)(member_ptr_at(spec_all, b.ms, mem < nmem ? mem : 0) + prob * nspec);
+    const size_t row = (size_t)nm * sizeof(double2);
+    const unsigned at_lo = um * 16u + (lane & 1) * 8u, at = at_lo + (unsigned)r0 * (unsigned)row;
+    double x[L];
+#pragma unroll
+    for (int t = 0; t < L; ++t)
+        x[t] = *(const double *)(base + (size_t)(t < M ? t : M - 1) * row + (r0 + t < M ? at : at_lo));
+#pragma unroll
+    for (int u = 0; u < kF; ++u) {  // (rows past the last: zero)
+        const int e = (int)threadIdx.x + 256 * u, c = e / NR, j = e % NR;
+        s_g[c * LD + j] = j < M ? f[u].x : 0.0;
+        s_c[c * LD + j] = j < M ? f[u].y : 0.0;
+    }
+    if (threadIdx.x < NR) s_lo[threadIdx.x] = (threadIdx.x > 0 && (int)threadIdx.x < M) ? tb.lyc_lo[threadIdx.x] : 0.0;
+    __syncthreads();
+    if (mem >= nmem) return;
+    const double *pg = s_g + (int)(um - m0) * LD + r0, *pc = s_c + (int)(um - m0) * LD + r0, *lo = s_lo + r0;
+    const bool pin = kind == 0 && um == 0;
+    const double scale = 1.0 / ((double)d.nx * (double)d.nz);
+    // keeps the scheduler from running steps into each other (registers)
+    auto hold = [] { __builtin_amdgcn_sched_barrier(0); };
+    // d'_j = g_j r_j + m_j d'_{j-1}
+    double q[L], y[L];
+#pragma unroll
+    for (int t = 0; t < L; ++t) {
+        if (t % 8 == 0) hold();
+        const double g = pg[t], r = x[t] * scale;
+        q[t] = -lo[t] * g;
+        x[t] = y[t] = g * ((t == 0 && pin && half == 0) ? 0.0 : r);
+    }
+#pragma unroll
+    for (int s = 1; s < NR; s *= 2) {
+        if (s >= L) {  // (the last one: the lower half's rows do not change)
+#pragma unroll
+            for (int t0 = s - L; t0 < L; t0 += 8) {
+                double c[8];
+                hold();
+#pragma unroll
+                for (int t = 0; t < 8; ++t) c[t] = other_half<false>(y[t0 + t + L - s], 0.0);
+#pragma unroll
+                for (int t = 0; t < 8; ++t) y[t0 + t] = __builtin_fma(q[t0 + t], c[t], y[t0 + t]);
+            }
+            break;
+        }
+        double c[L];
+        hold();
+#pragma unroll
+        for (int t = 0; t < s; ++t) c[t] = other_half<false>(y[L + t - s], 0.0);
+#pragma unroll
+        for (int t = L - 1; t >= s; --t) y[t] = __builtin_fma(q[t], y[t - s], y[t]);
+#pragma unroll
+        for (int t = 0; t < s; ++t) y[t] = __builtin_fma(q[t], c[t], y[t]);
+        hold();
+#pragma unroll
+        for (int t = 0; t < L; ++t)
+            if (t < s) c[t] = other_half<false>(q[L + t - s], 1.0);
+#pragma unroll
+        for (int t = L - 1; t >= s; --t) q[t] *= q[t - s];
+#pragma unroll
+        for (int t = 0; t < L; ++t)
+            if (t < s) q[t] *= c[t];
+    }
+    WaveFft<256>::wave_sync();  // (the pivots are read again, not kept)
+    {
+        const double in = other_half<false>(y[L - 1], 0.0);
+#pragma unroll
+        for (int t = 0; t < L; ++t) {
+            const double mm = -lo[t] * pg[t];
+            x[t] = __builtin_fma(mm, t ? y[t ? t - 1 : 0] : in, x[t]);
+        }
+    }
+    // x_j = d'_j - c'_j x_{j+1}
+#pragma unroll
+    for (int t = 0; t < L; ++t) {
+        y[t] = x[t];
+        q[t] = -pc[t];
+    }
+#pragma unroll
+    for (int s = 1; s < NR; s *= 2) {
+        if (s >= L) {  // (the last one)
+#pragma unroll
+            for (int t0 = 0; t0 < NR - s; t0 += 8) {
+                double c[8];
+                hold();
+#pragma unroll
+                for (int t = 0; t < 8; ++t) c[t] = other_half<true>(y[t0 + t + s - L], 0.0);
+#pragma unroll
+                for (int t = 0; t < 8; ++t) y[t0 + t] = __builtin_fma(q[t0 + t], c[t], y[t0 + t]);
+            }
+            break;
+        }
+        double c[L];
+        hold();
+#pragma unroll
+        for (int t = L - s; t < L; ++t) c[t] = other_half<true>(y[t + s - L], 0.0);
+#pragma unroll
+        for (int t = 0; t + s < L; ++t) y[t] = __builtin_fma(q[t], y[t + s], y[t]);
+#pragma unroll
+        for (int t = L - s; t < L; ++t) y[t] = __builtin_fma(q[t], c[t], y[t]);
+        hold();
+#pragma unroll
+        for (int t = 0; t < L; ++t)
+            if (t + s >= L) c[t] = other_half<true>(q[t + s - L], 1.0);
+#pragma unroll
+        for (int t = 0; t + s < L; ++t) q[t] *= q[t + s];
+#pragma unroll
+        for (int t = 0; t < L; ++t)
+            if (t + s >= L) q[t] *= c[t];
+    }
+    WaveFft<256>::wave_sync();
+    {
+        const double in = other_half<true>(y[0], 0.0);
+#pragma unroll
+        for (int t = 0; t < L; ++t)
+            x[t] = __builtin_fma(-pc[t], t + 1 < L ? y[t + 1 < L ? t + 1 : 0] : in, x[t]);
+    }
+    if (kind == 0 && m0 == 0) {  // zero volume mean of the pressure-type solution
+        double(&v)[2][64] = s_v[wave];
+        if (pin) {
+#pragma unroll
+            for (int t = 0; t < L; ++t) v[lane & 1][r0 + t] = x[t];
+        }
+        WaveFft<256>::wave_sync();
+        const bool in = lane < M;
+        double vol = in ? tb.dn[lane] : 0.0, sx = in ? v[0][lane] * vol : 0.0, sy = in ? v[1][lane] * vol : 0.0;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            sx += __shfl_xor(sx, o, 64);
+            sy += __shfl_xor(sy, o, 64);
+            vol += __shfl_xor(vol, o, 64);
+        }
+        const double mean = ((lane & 1) ? sy : sx) / vol;
+        if (pin) {
+#pragma unroll
+            for (int t = 0; t < L; ++t) x[t] -= mean;
+        }
+    }
+    if (cm >= nc) return;
+#pragma unroll
+    for (int t = 0; t < L; ++t)
+        if (r0 + t < M) *(double *)(base + (size_t)t * row + at) = x[t];
+}
+
 // Solve of one tile of tm consecutive modes of one problem: the tile's rows
 // are staged in LDS with coalesced loads; each group of W lanes then solves
 // one mode at a time with its rows split into W contiguous lane segments of R
@@ -1917,6 +2115,17 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
             else if (L == 12) NSPNP_MR(12);
             else NSPNP_MR(16);
 #undef NSPNP_MR
+        } else if (d.M <= kColRows && nmem >= 4 && (nmodes + kColModes - 1) / kColModes * b.nprob * nmem >= 2048) {
+            // (members that share the pivots, and two waves for every SIMD: fewer
+            // waves would leave the chip waiting for single columns)
+            ProfScope prof_(s, K_THOMAS);
+            const dim3 gm((unsigned)((nmodes + kColModes - 1) / kColModes), (unsigned)b.nprob, (unsigned)((nmem + 3) / 4));
+#define NSPNP_MC(LL) k_mode_columns<LL><<<gm, 256, 0, s->stream>>>(d, s->tb, b, s->spec, s->fac, nspec, nmem)
+            if (d.M <= 16) NSPNP_MC(8);
+            else if (d.M <= 32) NSPNP_MC(16);
+            else if (d.M <= 48) NSPNP_MC(24);
+            else NSPNP_MC(32);
+#undef NSPNP_MC
         } else {
             ProfScope prof_(s, K_THOMAS);
             const int lanes = d.M <= 16 ? 16 : (d.M <= 32 ? 32 : 64);

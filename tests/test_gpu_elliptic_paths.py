@@ -63,3 +63,23 @@ def test_runs_across_the_row_limits(oracle_mod, rows, precision):
         a, b = s.get_field(k).cpu().numpy(), o.field(k)
         err = np.max(np.abs(a - b)) / max(np.max(np.abs(b)), 1e-300)
         assert err < (1e-10 if precision == "fp64" else 1e-5), (k, err)
+
+
+# Members of an ensemble large enough for the columns in registers (up to 64
+# rows, a partial group of members and of modes) against runs of their own,
+# which stay lane-split: the same operations in the same order.
+@pytest.mark.parametrize("rows", [4, 7, 8, 9, 15, 16, 17, 32, 33, 48, 49, 63, 64, 65])
+def test_columns_of_an_ensemble(rows):
+    import numpy as np
+    import paper_1701_02005_amd as P
+    base = config(P, 96, rows + 1, 54)  # 2646 modes: 165 tiles of 16 and a part
+    cfgs = [dataclasses.replace(base, seed=3 + m, re=300.0 + 50.0 * m, u_noise=0.05) for m in range(7)]
+    e = P.Ensemble(cfgs)
+    e.step(2)
+    e.sync()
+    for m in (0, 3, 4, 6):
+        s = P.Solver(cfgs[m])
+        s.step(2)
+        for k in ("u", "v", "w", "cp", "cm", "phi", "p"):
+            a, b = e.get_field(m, k).cpu().numpy(), s.get_field(k).cpu().numpy()
+            assert np.array_equal(a, b), (m, k, np.max(np.abs(a - b)))
