@@ -542,10 +542,13 @@ hipError_t launch_shift_conc(nspnp_state *s, double mp, double mm) {
 hipError_t launch_dt(nspnp_state *s) {
     ProfScope prof_(s, K_DT);
     // columns in chunks of one block; rows split into slabs so that the
-    // partials fit kDtMaxBlocks per member
+    // partials fit kDtMaxBlocks per member and the members together have about
+    // 4096 blocks (a slab reads one row of v and phi beyond its own and loads
+    // kDtRows at a time: 32 members of 64 x 65 x 64 with single rows 92 us, with
+    // 8 rows 39; of 48 x 49 x 48 43 and 25)
     static_assert(kDtThreads == kRedThreads, "dt block size");
     const int chunks = dt_chunks(s->d.plane);
-    const int slabs = std::max(1, std::min(s->d.M, kDtMaxBlocks / chunks));
+    const int slabs = std::max(1, std::min({s->d.M, kDtMaxBlocks / chunks, 4096 / (chunks * s->nmem)}));
     const int slab_rows = (s->d.M + slabs - 1) / slabs;
     const unsigned nb = (unsigned)(chunks * ((s->d.M + slab_rows - 1) / slab_rows));
     if ((int64_t)nb * kDtParts > s->nred) return hipErrorInvalidValue;  // the layout sized red for this
