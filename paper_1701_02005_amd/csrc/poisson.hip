@@ -1579,11 +1579,13 @@ __global__ void __launch_bounds__(256, 2) k_mode_columns(Dims d, Tables tb, Pois
 // coalesced stores.  The members of a batch share one grid, so all of them
 // read member 0's pivots, which then stay in the caches: 32 instead of 48
 // bytes of memory traffic per mode and row.
-constexpr int kThBatch = 12;  // a whole 16-mode tile of 192 rows in one batch
+// Loads per thread and wait of the staging: a whole 16-mode tile up to 192 rows.
+constexpr int thomas_batch(int R) { return R == 1 ? 4 : 12; }
 
 template <int R, int W>
 __global__ void __launch_bounds__(256) k_thomas_tile(Dims d, Tables tb, PoissonBatch b, double2 *spec_all,
                                                      const double2 *fac_all, int64_t nspec, int tm) {
+    constexpr int kThBatch = thomas_batch(R);
     extern __shared__ double2 s_x[];
     const uint3 blk = xcd_block3();
     const int prob = (int)blk.y;
@@ -1595,6 +1597,21 @@ __global__ void __launch_bounds__(256) k_thomas_tile(Dims d, Tables tb, PoissonB
     const int64_t m0 = (int64_t)blk.x * tm;
     const int ncol = (int)((nmodes - m0) < tm ? (nmodes - m0) : tm);
     const int LD = tm + 1;
+    const int lane = (int)threadIdx.x % W, wave = (int)threadIdx.x / W, nwave = (int)blockDim.x / W;  // (groups)
+    const int js = lane * R;
+    // Pivots (1/den, c') of a column: unconditional loads (padding rows read
+    // the last row and ignore it); the next column's are fetched while the
+    // current one is solved, unconditionally (the wave's last column re-reads
+    // its own) so that the wait for the current pivots stays partial
+    double2 fnext[R];
+    auto load_pivots = [&](int c, double2 *f) {
+        const double2 *fm = fac + (m0 + c) * M;
+#pragma unroll
+        for (int t = 0; t < R; ++t) f[t] = fm[(js + t < M) ? js + t : M - 1];
+    };
+    // one row per lane: with the tile's loads (latency; with more rows their
+    // registers cost more: 256 x 193 x 256 111 against 115 us)
+    if (R == 1 && wave < ncol) load_pivots(wave, fnext);
     // Staging in batches of kThBatch unconditional loads per thread (lanes
     // past the tile read its first mode and discard it): one wait per batch.
     // Offsets within one spectrum: rows * modes < 2^32 for every supported grid.
@@ -1619,9 +1636,7 @@ __global__ void __launch_bounds__(256) k_thomas_tile(Dims d, Tables tb, PoissonB
         }
     }
     __syncthreads();
-    const int lane = (int)threadIdx.x % W, wave = (int)threadIdx.x / W, nwave = (int)blockDim.x / W;  // (groups)
     constexpr int kSteps = W == 64 ? 6 : (W == 32 ? 5 : 4);
-    const int js = lane * R;
     const double scale = 1.0 / ((double)d.nx * (double)d.nz);
     double lo[R];
 #pragma unroll
@@ -1629,17 +1644,7 @@ __global__ void __launch_bounds__(256) k_thomas_tile(Dims d, Tables tb, PoissonB
         const int j = js + t;
         lo[t] = (j > 0 && j < M) ? tb.lyc_lo[j] : 0.0;
     }
-    // pivots (1/den, c') of a column: unconditional loads (padding rows read
-    // the last row and ignore it); the next column's are fetched while the
-    // current one is solved, unconditionally (the wave's last column re-reads
-    // its own) so that the wait for the current pivots stays partial
-    double2 fnext[R];
-    auto load_pivots = [&](int c, double2 *f) {
-        const double2 *fm = fac + (m0 + c) * M;
-#pragma unroll
-        for (int t = 0; t < R; ++t) f[t] = fm[(js + t < M) ? js + t : M - 1];
-    };
-    if (wave < ncol) load_pivots(wave, fnext);
+    if (R > 1 && wave < ncol) load_pivots(wave, fnext);
     for (int c = wave; c < ncol; c += nwave) {
         const int64_t m = m0 + c;
         const bool pin = (kind == 0 && m == 0);
@@ -2136,7 +2141,7 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
             while (tm > 256 / lanes && (nmodes + tm - 1) / tm * b.nprob * nmem < 512) tm = std::max(tm / 2, 256 / lanes);
             const dim3 gt((unsigned)((nmodes + tm - 1) / tm), (unsigned)b.nprob, (unsigned)nmem);
             const size_t ldst = (size_t)d.M * (tm + 1) * sizeof(double2);
-            const int rpl = (d.M + 63) / 64;  // rows per lane (M <= 512: at most 8)
+            const int rpl = (d.M + 63) / 64;  // rows per lane (up to kLaneRows: at most 5)
 #define NSPNP_TH(RR, WW) k_thomas_tile<RR, WW><<<gt, 256, ldst, s->stream>>>(d, s->tb, b, s->spec, s->fac, nspec, tm)
 #define NSPNP_TH_CASE(RR)                                                                                \
         case RR:                                                                                             \
@@ -2152,9 +2157,6 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
                 NSPNP_TH_CASE(3)
                 NSPNP_TH_CASE(4)
                 NSPNP_TH_CASE(5)
-                NSPNP_TH_CASE(6)
-                NSPNP_TH_CASE(7)
-                NSPNP_TH_CASE(8)
                 default:
                     return hipErrorInvalidValue;
             }

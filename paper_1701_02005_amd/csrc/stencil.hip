@@ -498,10 +498,11 @@ inline int cn_tile_cols(int threads) { return threads > 256 ? 32 : 16; }
 // Bound by memory: 0.273 ms at 256 x 193 x 256 (5.5 TB/s).
 constexpr int kCnLaneRows = 320;
 
-template <int kCnTx, int kCnMaxR>
+template <int kCnTx, int kCnMaxR, int W>
 __global__ void __launch_bounds__(512) k_cn_scan(CnArgs a) {
     using T = double;
-    constexpr int kCnBatch = kCnMaxR == 1 ? 4 : 6;
+    constexpr int kCnBatch = kCnMaxR == 1 ? 4 : 6, kSteps = W == 64 ? 6 : (W == 32 ? 5 : 4);
+    constexpr bool kAhead = kCnMaxR == 1;
     extern __shared__ double s_r[];
     const uint3 blk = xcd_block3();  // adjacent column tiles share an L2
     const int f = (int)blk.y;
@@ -520,6 +521,24 @@ __global__ void __launch_bounds__(512) k_cn_scan(CnArgs a) {
     constexpr int LD = kCnTx + 1;
     const int nrow = M - j0;
     const int ntile = nrow * kCnTx, bd = (int)blockDim.x;
+    const int lane = threadIdx.x % W, wave = threadIdx.x / W, nwave = blockDim.x / W;  // (groups of W lanes)
+    const int R = kCnMaxR;  // rows per lane (the launcher picks ceil(rows / 64))
+    const int js = j0 + lane * R;
+    // this lane's recurrence coefficients (the same for every column)
+    double g[kCnMaxR], mm[kCnMaxR], nn[kCnMaxR];
+    auto load_coef = [&] {
+#pragma unroll
+        for (int t = 0; t < kCnMaxR; ++t) {
+            const int j = js + t < M ? js + t : M - 1;
+            g[t] = cg[j];
+            mm[t] = cm[j];
+            nn[t] = cn[j];
+        }
+    };
+    // One row per lane: the coefficients, and below the first values of q, go
+    // out with the loads of r (latency; with more rows their registers cost
+    // more: 256 x 193 x 256 279 against 287 us)
+    if (kAhead) load_coef();
     // Staging in batches of kCnBatch unconditional loads per thread (lanes
     // past the tile read its first element, which exists, and discard it), so
     // that a thread waits for memory once per batch, not once per element.
@@ -539,34 +558,38 @@ __global__ void __launch_bounds__(512) k_cn_scan(CnArgs a) {
             if (e < ntile) s_r[jj * LD + c] = (c < ncol) ? (double)v[u] : 0.0;
         }
     }
+    T qv[kCnBatch];
+    auto load_q = [&](int e0) {
+#pragma unroll
+        for (int u = 0; u < kCnBatch; ++u) {
+            const int e = e0 + u * bd, jj = j0 + e / kCnTx, c = e % kCnTx;
+            qv[u] = ld_once(q + ((e < ntile && c < ncol) ? (unsigned)jj * upl + uc0 + (unsigned)c : o_safe));
+        }
+    };
+    if (kAhead && !a.out_r) load_q((int)threadIdx.x);
     __syncthreads();
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = blockDim.x >> 6;
-    const int R = kCnMaxR;  // rows per lane (the launcher picks ceil(rows / 64))
-    const int js = j0 + lane * R;
-    // this lane's recurrence coefficients (the same for every column)
-    double g[kCnMaxR], mm[kCnMaxR], nn[kCnMaxR];
+    if (!kAhead) load_coef();
     double Qs = 1.0, Ss = 1.0;
 #pragma unroll
     for (int t = 0; t < kCnMaxR; ++t) {
-        const int j = js + t;
-        const bool in = (t < R) && (j < M);
-        g[t] = in ? cg[j] : 0.0;
-        mm[t] = in ? cm[j] : 1.0;
-        nn[t] = in ? cn[j] : 1.0;
+        const bool in = js + t < M;
+        g[t] = in ? g[t] : 0.0;
+        mm[t] = in ? mm[t] : 1.0;
+        nn[t] = in ? nn[t] : 1.0;
         Qs *= mm[t];
         Ss *= nn[t];
     }
     // multipliers of the scans of the affine maps x -> T + Q x across lanes
     // (forward, from lane 0 up) and x -> U + S x (backward, from lane 63 down)
-    double qm[6], sm[6];
+    double qm[kSteps], sm[kSteps];
 #pragma unroll
-    for (int st = 0; st < 6; ++st) {
+    for (int st = 0; st < kSteps; ++st) {
         const int sft = 1 << st;
         qm[st] = Qs;
         sm[st] = Ss;
-        const double Qp = __shfl_up(Qs, sft, 64), Sp = __shfl_down(Ss, sft, 64);
+        const double Qp = __shfl_up(Qs, sft, W), Sp = __shfl_down(Ss, sft, W);
         if (lane >= sft) Qs *= Qp;
-        if (lane + sft < 64) Ss *= Sp;
+        if (lane + sft < W) Ss *= Sp;
     }
     for (int c = wave; c < ncol; c += nwave) {
         double *col = s_r + c;
@@ -581,11 +604,11 @@ __global__ void __launch_bounds__(512) k_cn_scan(CnArgs a) {
 #pragma unroll
         for (int t = 0; t < kCnMaxR; ++t) Tf = g[t] * x[t] + mm[t] * Tf;
 #pragma unroll
-        for (int st = 0; st < 6; ++st) {
-            const double Tp = __shfl_up(Tf, 1 << st, 64);
+        for (int st = 0; st < kSteps; ++st) {
+            const double Tp = __shfl_up(Tf, 1 << st, W);
             if (lane >= (1 << st)) Tf += qm[st] * Tp;
         }
-        double din = __shfl_up(Tf, 1, 64);
+        double din = __shfl_up(Tf, 1, W);
         if (lane == 0) din = 0.0;
 #pragma unroll
         for (int t = 0; t < kCnMaxR; ++t) {
@@ -597,12 +620,12 @@ __global__ void __launch_bounds__(512) k_cn_scan(CnArgs a) {
 #pragma unroll
         for (int t = kCnMaxR - 1; t >= 0; --t) U = (g[t] != 0.0 ? x[t] : 0.0) + nn[t] * U;
 #pragma unroll
-        for (int st = 0; st < 6; ++st) {
-            const double Up = __shfl_down(U, 1 << st, 64);
-            if (lane + (1 << st) < 64) U += sm[st] * Up;
+        for (int st = 0; st < kSteps; ++st) {
+            const double Up = __shfl_down(U, 1 << st, W);
+            if (lane + (1 << st) < W) U += sm[st] * Up;
         }
-        double xin = __shfl_down(U, 1, 64);
-        if (lane == 63) xin = 0.0;
+        double xin = __shfl_down(U, 1, W);
+        if (lane == W - 1) xin = 0.0;
 #pragma unroll
         for (int t = kCnMaxR - 1; t >= 0; --t) {
             xin = (g[t] != 0.0 ? x[t] : 0.0) + nn[t] * xin;
@@ -624,16 +647,11 @@ __global__ void __launch_bounds__(512) k_cn_scan(CnArgs a) {
         return;
     }
     for (int e0 = threadIdx.x; e0 < ntile; e0 += kCnBatch * bd) {
-        T v[kCnBatch];
+        if (!kAhead || e0 != (int)threadIdx.x) load_q(e0);
 #pragma unroll
         for (int u = 0; u < kCnBatch; ++u) {
             const int e = e0 + u * bd, jj = j0 + e / kCnTx, c = e % kCnTx;
-            v[u] = ld_once(q + ((e < ntile && c < ncol) ? (unsigned)jj * upl + uc0 + (unsigned)c : o_safe));
-        }
-#pragma unroll
-        for (int u = 0; u < kCnBatch; ++u) {
-            const int e = e0 + u * bd, jj = j0 + e / kCnTx, c = e % kCnTx;
-            if (e < ntile && c < ncol) st_once(q + ((unsigned)jj * upl + uc0 + (unsigned)c), (T)((double)v[u] + s_r[jj * LD + c]));
+            if (e < ntile && c < ncol) st_once(q + ((unsigned)jj * upl + uc0 + (unsigned)c), (T)((double)qv[u] + s_r[jj * LD + c]));
         }
     }
 }
@@ -1450,11 +1468,13 @@ static hipError_t launch_cyc(nspnp_state *s, const Stage &st, int dir, int out_r
 
 // Lane-scan Crank-Nicolson solve of the five fields (tiles of 16 or 32 columns).
 static hipError_t launch_cn_lane(nspnp_state *s, const CnArgs &a) {
-    // up to two blocks per CU: 8 waves on 16 columns, so that a wave solves two
-    // columns one after the other instead of four (the result is the same;
-    // 16 x 17 x 12 7 to 8 -> 5.8 us, latency)
+    // up to 32 rows: groups of 16 or 32 lanes a column, which hold all of its
+    // rows (a whole wave's idle lanes would only pass values through: the result
+    // is the same); up to two blocks per CU: 8 waves on 16 columns (32 x 33 x 32
+    // 8.6 us with one column a wave, 6.5 so; latency)
+    const int lanes = s->d.M <= 16 ? 16 : (s->d.M <= 32 ? 32 : 64);
     const bool small = (s->d.plane + 15) / 16 * 5 * s->nmem <= 512;
-    const int tb = small ? 512 : s->tiles.cn;
+    const int tb = small ? (lanes == 16 ? 256 : 512) : s->tiles.cn;
     const int tcols = small ? 16 : cn_tile_cols(tb);
     const dim3 g((unsigned)((s->d.plane + tcols - 1) / tcols), 5, (unsigned)s->nmem);
     const size_t lds = (size_t)s->d.M * (tcols + 1) * sizeof(double);
@@ -1467,19 +1487,19 @@ static hipError_t launch_cn_lane(nspnp_state *s, const CnArgs &a) {
         kernel<<<g, tb, lds, s->stream>>>(a);
         return hipGetLastError();
     };
-#define NSPNP_CN_CASE(RR)                                                                              \
-    case RR:                                                                                           \
-        if (tcols == 32)                                                                               \
-            return launch((const void *)k_cn_scan<32, RR>, k_cn_scan<32, RR>);                         \
-        return launch((const void *)k_cn_scan<16, RR>, k_cn_scan<16, RR>);
+#define NSPNP_CN_CASE(RR, WW)                                                                          \
+    if (tcols == 32) return launch((const void *)k_cn_scan<32, RR, WW>, k_cn_scan<32, RR, WW>);        \
+    return launch((const void *)k_cn_scan<16, RR, WW>, k_cn_scan<16, RR, WW>);
     switch (rpl) {
-        NSPNP_CN_CASE(1)
-        NSPNP_CN_CASE(2)
-        NSPNP_CN_CASE(3)
-        NSPNP_CN_CASE(4)
-        NSPNP_CN_CASE(5)
-        default:
-            return hipErrorInvalidValue;
+        case 1:
+            if (lanes == 16) { NSPNP_CN_CASE(1, 16) }
+            if (lanes == 32) { NSPNP_CN_CASE(1, 32) }
+            NSPNP_CN_CASE(1, 64)
+        case 2: NSPNP_CN_CASE(2, 64)
+        case 3: NSPNP_CN_CASE(3, 64)
+        case 4: NSPNP_CN_CASE(4, 64)
+        case 5: NSPNP_CN_CASE(5, 64)
+        default: return hipErrorInvalidValue;
     }
 #undef NSPNP_CN_CASE
 }
