@@ -488,18 +488,20 @@ __global__ void __launch_bounds__(256) k_fft_x_c2r(Dims d, Tables tb, FftPlan pl
     }
 }
 
-// ---- x lines of 256 and 512 points: one wave per line pair, in registers ----
-// A block of 4 waves owns 8 consecutive lines; a wave transforms one pair with
-// N / 64 values per lane, all passes in registers (radix 4 for 256 points,
-// radix 8 for 512, as make_plan has them) and exchanges within the wave
-// through its own piece of LDS, without block barriers.  Each exchange has an
-// index map that keeps its writes and reads free of bank conflicts.  The 8
-// lines make whole 128-byte lines of the [j][kx][kz] spectrum.  Butterflies
+// ---- x lines of 64, 128, 256 and 512 points: a wave per line pair, in registers ----
+// A block of 4 waves owns 8 consecutive lines (16 of 128 points, 32 of 64); a
+// wave transforms one pair (2, 4) with 4 or 8 values per lane, all passes in
+// registers (radix 4, for 128 points a last pass of radix 2; radix 8 for 512;
+// as make_plan has them) and exchanges within the wave through its own piece
+// of LDS, without block barriers.  Each exchange has an index map that keeps
+// its writes and reads free of bank conflicts.  The 8 lines make whole
+// 128-byte lines of the [j][kx][kz] spectrum.  Butterflies
 // and their order are those of the general kernels: the same bit for bit.
 // Bound by memory; many independent waves with every load of a line in flight
 // beat tiles behind block barriers: 512 x 385 x 512 FP64 forward 1.49 -> 1.03
 // ms (5.4 TB/s), inverse 0.95 -> 0.56 ms (5.7 TB/s), mixed 1.14 -> 0.66 and
-// 0.93 -> 0.50 ms; 256 x 193 x 256 FP64 165 -> 130 and 106 -> 62 us.
+// 0.93 -> 0.50 ms; 256 x 193 x 256 FP64 165 -> 130 and 106 -> 62 us, 128 x 129
+// x 128 36 -> 29 and 30 -> 15 us, 64 x 129 x 256 34 -> 28 and 29 -> 15 us.
 // Which product of a complex multiplication is rounded before the fused
 // multiply-add is written out, as the general kernels' compilation has it.
 __device__ __forceinline__ double2 twiddle(double2 a, double2 w, bool inv) {
@@ -541,35 +543,48 @@ __device__ __forceinline__ void wave_dft(double2 *v, bool inv) {
 
 template <int N, bool kZ = false>
 struct WaveFft {
-    static constexpr int R = N / 64;                 // values per lane and radix
-    static constexpr int kSlots = N == 256 ? 328 : 568;  // LDS slots of one pair (8 mod 16)
+    static constexpr int R = N == 512 ? 8 : 4;   // values per lane and radix
+    static constexpr int kLanes = N / R;         // lanes of a line or pair
+    static constexpr int kPer = 64 / kLanes;     // lines or pairs per wave
+    // LDS slots of one pair (64, 128 points: the pairs of a block in different banks)
+    static constexpr int kSlots = N == 512 ? 568 : (N == 256 ? 328 : (N == 128 ? 162 : 81));
     // slot of element i on the way from the pass with input stride Ns
     static __device__ __forceinline__ int slot(int i, int Ns) {
         if (Ns == 1) return i + (i >> 4);
-        if (N == 256) return Ns == 4 ? i + 4 * (i >> 4) : i;
+        if (R == 4) return Ns == 4 ? i + 4 * (i >> 4) : i;
         return i + 8 * (i >> 6);
     }
-    // v[r] holds element lane + 64 r before and after; z: the pair's slots
+    // v[r] holds element lane + kLanes r before and after; z: the pair's slots
     static __device__ __forceinline__ void run(double2 *v, double2 *z, const double2 *__restrict__ tw, int lane,
                                                bool inv) {
         wave_dft<R, kZ>(v, inv);  // (the first pass's twiddles are 1)
         int off = R - 1;
 #pragma unroll
         for (int Ns = R; Ns < N; Ns *= R) {
+            const bool two = Ns * R > N;  // 128 points: a last pass of radix 2, two butterflies a lane
             const int pNs = Ns / R, blk = lane / pNs, pk = lane % pNs, k = lane % Ns;
             double2 w[R];
 #pragma unroll
-            for (int r = 1; r < R; ++r) w[r] = tw[off + (r - 1) * Ns + k];
+            for (int r = 1; r < R; ++r) w[r] = two ? tw[off + lane + (r & 1) * kLanes] : tw[off + (r - 1) * Ns + k];
             off += Ns * (R - 1);
 #pragma unroll
             for (int r = 0; r < R; ++r) z[slot(blk * Ns + pk + r * pNs, pNs)] = v[r];
             wave_sync();
 #pragma unroll
-            for (int r = 0; r < R; ++r) v[r] = z[slot(lane + 64 * r, pNs)];
+            for (int r = 0; r < R; ++r) v[r] = z[slot(lane + kLanes * r, pNs)];
             wave_sync();
+            if (two) {
 #pragma unroll
-            for (int r = 1; r < R; ++r) v[r] = twiddle(v[r], w[r], inv);
-            wave_dft<R, kZ>(v, inv);
+                for (int r = 0; r < 2; ++r) {
+                    const double2 c = twiddle(v[r + 2], w[r + 2], inv);
+                    v[r + 2] = csub(v[r], c);
+                    v[r] = cadd(v[r], c);
+                }
+            } else {
+#pragma unroll
+                for (int r = 1; r < R; ++r) v[r] = twiddle(v[r], w[r], inv);
+                wave_dft<R, kZ>(v, inv);
+            }
         }
     }
     // orders the wave's LDS accesses (they execute in order; this keeps the
@@ -664,8 +679,8 @@ template <typename T, int N>
 __global__ void __launch_bounds__(256) k_lines_r2c(Dims d, Tables tb, PoissonBatch b, const double *clock,
                                                    double2 *spec, int64_t nspec) {
     using F = WaveFft<N>;
-    constexpr int nxh = N / 2 + 1;
-    __shared__ double2 s_z[4 * F::kSlots];
+    constexpr int nxh = N / 2 + 1, kLines = 8 * F::kPer, B = F::kPer == 1 ? 4 : N / 64;
+    __shared__ double2 s_z[4 * F::kPer * F::kSlots];
     const int prob = blockIdx.y;
     PoissonSrc src = b.src[prob];
     src.a = member_ptr(src.a, b.ms);
@@ -676,37 +691,52 @@ __global__ void __launch_bounds__(256) k_lines_r2c(Dims d, Tables tb, PoissonBat
     const double ch = member_ptr(b.phys, b.ms)->ch;
     double2 *out = member_ptr(spec, b.ms) + prob * nspec;
     const int nz = d.nz, nlines = d.M * nz;
-    const int line0 = (int)xcd_tile(blockIdx.x, gridDim.x) * 8;
+    const int line0 = (int)xcd_tile(blockIdx.x, gridDim.x) * kLines;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const double sc = (src.type == SRC_DIV) ? ((src.alp > 0.0) ? 1.0 / (src.alp * clock[1]) : src.fixed) : 0.0;
     const double idx = 1.0 / d.dx, idz = 1.0 / d.dz;
-    {
+    // right-hand side of the wave's pair h, elements lane + 64 r
+    auto rhs = [&](int h, int r0, double2 *v) {
         // (a pair past the last line repeats the last one and is not stored)
-        const int line = line0 + 2 * wave < nlines ? line0 + 2 * wave : nlines - 2;
+        const int first = line0 + 2 * (wave * F::kPer + h), line = first < nlines ? first : nlines - 2;
         const int j = line / nz, k = line - j * nz;
+        if (src.type == SRC_DIV) line_rhs<T, SRC_DIV, N, B>(src, d, tb, ch, sc, idx, idz, j, k, lane, r0, v);
+        else if (src.type == SRC_CHARGE) line_rhs<T, SRC_CHARGE, N, B>(src, d, tb, ch, sc, idx, idz, j, k, lane, r0, v);
+        else line_rhs<T, SRC_REAL, N, B>(src, d, tb, ch, sc, idx, idz, j, k, lane, r0, v);
+    };
+    {
+        const int l = lane % F::kLanes;
+        double2 *zw = s_z + wave * F::kPer * F::kSlots, *z = zw + lane / F::kLanes * F::kSlots;
         double2 v[F::R];
-        double2 *z = s_z + wave * F::kSlots;
-        constexpr int B = 4;
+        if constexpr (F::kPer == 1) {
 #pragma unroll
-        for (int r0 = 0; r0 < F::R; r0 += B) {
-            if (src.type == SRC_DIV) line_rhs<T, SRC_DIV, N, B>(src, d, tb, ch, sc, idx, idz, j, k, lane, r0, v);
-            else if (src.type == SRC_CHARGE) line_rhs<T, SRC_CHARGE, N, B>(src, d, tb, ch, sc, idx, idz, j, k, lane, r0, v);
-            else line_rhs<T, SRC_REAL, N, B>(src, d, tb, ch, sc, idx, idz, j, k, lane, r0, v);
+            for (int r0 = 0; r0 < F::R; r0 += B) rhs(0, r0, v);
+        } else {  // by the whole wave, pair by pair, and through LDS to each pair's lanes
+#pragma unroll
+            for (int h = 0; h < F::kPer; ++h) rhs(h, 0, v + h * B);
+#pragma unroll
+            for (int h = 0; h < F::kPer; ++h)
+#pragma unroll
+                for (int t = 0; t < B; ++t) zw[h * F::kSlots + lane + 64 * t] = v[h * B + t];
+            F::wave_sync();
+#pragma unroll
+            for (int r = 0; r < F::R; ++r) v[r] = z[l + F::kLanes * r];
+            F::wave_sync();
         }
-        F::run(v, z, tb.twx, lane, false);
+        F::run(v, z, tb.twx, l, false);
 #pragma unroll
-        for (int r = 0; r < F::R; ++r) z[lane + 64 * r] = v[r];
+        for (int r = 0; r < F::R; ++r) z[l + F::kLanes * r] = v[r];
     }
     __syncthreads();
     // A = (Z_k + conj(Z_{N-k}))/2 for the even lines, B = (Z_k - conj(Z_{N-k}))/(2i)
     // for the odd ones; a thread keeps its line
-    const int l = threadIdx.x & 7, line = line0 + l;
+    const int l = threadIdx.x % kLines, line = line0 + l;
     if (line >= nlines) return;
     const int j = line / nz, k = line - j * nz;
     const double2 *z = s_z + (l >> 1) * F::kSlots;
     double2 *o = out + (int64_t)j * nxh * nz + k;
 #pragma unroll 4
-    for (int kk = threadIdx.x >> 3; kk < nxh; kk += 32) {
+    for (int kk = threadIdx.x / kLines; kk < nxh; kk += 256 / kLines) {
         const double2 zk = z[kk], zc = z[kk == 0 ? 0 : N - kk];
         o[(int64_t)kk * nz] = (l & 1) ? make_double2(0.5 * (zk.y + zc.y), -0.5 * (zk.x - zc.x))
                                       : make_double2(0.5 * (zk.x + zc.x), 0.5 * (zk.y - zc.y));
@@ -717,32 +747,34 @@ template <typename T, int N>
 __global__ void __launch_bounds__(256) k_lines_c2r(Dims d, Tables tb, PoissonBatch b, const double2 *spec,
                                                    int64_t nspec) {
     using F = WaveFft<N>;
-    constexpr int nxh = N / 2 + 1, kIt = (nxh + 31) / 32, kLine = N / 2 + 2;  // (2 mod 16)
-    __shared__ double2 s_z[4 * F::kSlots];
+    constexpr int nxh = N / 2 + 1, kLines = 8 * F::kPer, kRows = 256 / kLines, kIt = (nxh + kRows - 1) / kRows;
+    constexpr int kLine = N == 128 ? 65 : (N == 64 ? 40 : N / 2 + 2);  // (the lines of a pair in different banks)
+    __shared__ double2 s_z[4 * F::kPer * F::kSlots];
     const int prob = blockIdx.y;
     const double2 *in = member_ptr(spec, b.ms) + prob * nspec;
     const int nz = d.nz, nlines = d.M * nz;
-    const int line0 = (int)xcd_tile(blockIdx.x, gridDim.x) * 8;
+    const int line0 = (int)xcd_tile(blockIdx.x, gridDim.x) * kLines;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     {
-        const int l = threadIdx.x & 7, line = line0 + l < nlines ? line0 + l : nlines - 1;
-        const int j = line / nz, k = line - j * nz, k0 = threadIdx.x >> 3;
+        const int l = threadIdx.x % kLines, line = line0 + l < nlines ? line0 + l : nlines - 1;
+        const int j = line / nz, k = line - j * nz, k0 = threadIdx.x / kLines;
         const double2 *p = in + (int64_t)j * nxh * nz + k;
         double2 v[kIt];
 #pragma unroll
-        for (int t = 0; t < kIt; ++t) v[t] = ld_once(p + (int64_t)(k0 + 32 * t < nxh ? k0 + 32 * t : nxh - 1) * nz);
+        for (int t = 0; t < kIt; ++t) v[t] = ld_once(p + (int64_t)(k0 + kRows * t < nxh ? k0 + kRows * t : nxh - 1) * nz);
         double2 *o = s_z + (l >> 1) * F::kSlots + (l & 1) * kLine;
 #pragma unroll
         for (int t = 0; t < kIt; ++t)
-            if (k0 + 32 * t < nxh) o[k0 + 32 * t] = v[t];
+            if (k0 + kRows * t < nxh) o[k0 + kRows * t] = v[t];
     }
     __syncthreads();
-    if (line0 + 2 * wave >= nlines) return;
-    double2 *z = s_z + wave * F::kSlots;
+    const int pair = wave * F::kPer + lane / F::kLanes, l = lane % F::kLanes;
+    if (line0 + 2 * wave * F::kPer >= nlines) return;
+    double2 *z = s_z + pair * F::kSlots;
     double2 v[F::R];
 #pragma unroll
     for (int r = 0; r < F::R; ++r) {
-        const int kk = lane + 64 * r;
+        const int kk = l + F::kLanes * r;
         const bool lower = kk < nxh;
         const int src = lower ? kk : N - kk;
         double2 A = z[src], B = z[kLine + src];
@@ -753,14 +785,15 @@ __global__ void __launch_bounds__(256) k_lines_c2r(Dims d, Tables tb, PoissonBat
         v[r] = make_double2(A.x - B.y, A.y + B.x);  // Z = A + i B
     }
     F::wave_sync();
-    F::run(v, z, tb.twx, lane, true);
-    const int64_t la = (int64_t)(line0 + 2 * wave) * N;
+    F::run(v, z, tb.twx, l, true);
+    if (line0 + 2 * pair >= nlines) return;
+    const int64_t la = (int64_t)(line0 + 2 * pair) * N;
     const bool as_state = b.out_state[prob] != 0;
     double *o64 = (double *)member_ptr(b.out[prob], b.ms) + la;
     T *ot = (T *)member_ptr(b.out[prob], b.ms) + la;
 #pragma unroll
     for (int r = 0; r < F::R; ++r) {
-        const int i = lane + 64 * r;
+        const int i = l + F::kLanes * r;
         if (as_state) {
             st_once(ot + i, (T)v[r].x);
             st_once(ot + N + i, (T)v[r].y);
@@ -772,24 +805,29 @@ __global__ void __launch_bounds__(256) k_lines_c2r(Dims d, Tables tb, PoissonBat
 }
 
 // ---- z direction: contiguous complex lines, tiles of tk lines ----
-// Lines of 256 and 512 points: a wave per line, in registers (WaveFft).
+// Lines of 64 to 512 points, powers of two: a wave per line (2, 4 lines of 128,
+// 64 points), in registers (WaveFft).
 // 256 x 193 x 256 75 -> 62 us (6.5 TB/s, the spectra partly in the last-level
-// cache), 512 x 385 x 512 0.69 -> 0.60 ms forward, 0.66 -> 0.59 ms inverse.
+// cache), 512 x 385 x 512 0.69 -> 0.60 ms forward, 0.66 -> 0.59 ms inverse,
+// 128 x 129 x 128 20 -> 14 us, 256 x 129 x 64 18 -> 14 us.
 template <int N, bool kInv>
 __global__ void __launch_bounds__(256) k_lines_z(Dims d, const double2 *__restrict__ tw, double2 *spec, int64_t nspec,
                                                  size_t ms) {
     using F = WaveFft<N, true>;
-    __shared__ double2 s_z[4 * F::kSlots];
+    __shared__ double2 s_z[4 * F::kPer * F::kSlots];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int64_t line = (int64_t)blockIdx.x * 4 + wave;  // (j, kx)
-    if (line >= (int64_t)d.M * d.nxh) return;
-    double2 *p = member_ptr(spec, ms) + blockIdx.y * nspec + line * N + lane;
+    const int mine = wave * F::kPer + lane / F::kLanes, l = lane % F::kLanes;
+    const int64_t nlines = (int64_t)d.M * d.nxh, line0 = (int64_t)blockIdx.x * (4 * F::kPer);  // (j, kx)
+    if (line0 + wave * F::kPer >= nlines) return;
+    const bool in = F::kPer == 1 || line0 + mine < nlines;
+    double2 *p = member_ptr(spec, ms) + blockIdx.y * nspec + (in ? line0 + mine : nlines - 1) * N + l;
     double2 v[F::R];
 #pragma unroll
-    for (int r = 0; r < F::R; ++r) v[r] = p[64 * r];
-    F::run(v, s_z + wave * F::kSlots, tw, lane, kInv);
+    for (int r = 0; r < F::R; ++r) v[r] = p[F::kLanes * r];
+    F::run(v, s_z + mine * F::kSlots, tw, l, kInv);
+    if (!in) return;
 #pragma unroll
-    for (int r = 0; r < F::R; ++r) p[64 * r] = v[r];
+    for (int r = 0; r < F::R; ++r) p[F::kLanes * r] = v[r];
 }
 
 // Other lengths.
@@ -2022,17 +2060,23 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
     const dim3 gp((unsigned)d.M, (unsigned)b.nprob, (unsigned)nmem);
     const size_t ldsp = plane_lds(d.nx, d.nz);
     const unsigned tp = plane_threads(s);
-    // 256 and 512 points: a wave per line pair
-    const bool lines = !planes && (d.nx == 256 || d.nx == 512);
-    const dim3 gl((unsigned)((nlines + 7) / 8), (unsigned)b.nprob, (unsigned)nmem);
+    // 64 to 512 points, powers of two: a wave per line pair, or per 2 or 4
+    auto wave_line = [](int n) { return n == 64 || n == 128 || n == 256 || n == 512; };
+    const bool lines = !planes && wave_line(d.nx);
+    const int lpb = d.nx == 64 ? 32 : (d.nx == 128 ? 16 : 8);  // lines per block
+    const dim3 gl((unsigned)((nlines + lpb - 1) / lpb), (unsigned)b.nprob, (unsigned)nmem);
     if (lines) {
         ProfScope prof_(s, K_FFTX_FWD);
 #define NSPNP_LR(TT, NN) k_lines_r2c<TT, NN><<<gl, 256, 0, s->stream>>>(d, s->tb, b, s->clock, s->spec, nspec)
         if (s->fp64) {
-            if (d.nx == 256) NSPNP_LR(double, 256);
+            if (d.nx == 64) NSPNP_LR(double, 64);
+            else if (d.nx == 128) NSPNP_LR(double, 128);
+            else if (d.nx == 256) NSPNP_LR(double, 256);
             else NSPNP_LR(double, 512);
         } else {
-            if (d.nx == 256) NSPNP_LR(float, 256);
+            if (d.nx == 64) NSPNP_LR(float, 64);
+            else if (d.nx == 128) NSPNP_LR(float, 128);
+            else if (d.nx == 256) NSPNP_LR(float, 256);
             else NSPNP_LR(float, 512);
         }
 #undef NSPNP_LR
@@ -2090,12 +2134,17 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
         const int zblocks = std::max(1, std::min(ztiles, 2048 / std::max(1, b.nprob * nmem)));
         const dim3 gz((unsigned)zblocks, (unsigned)b.nprob, (unsigned)nmem);
         const size_t ldsz = (2 * (size_t)tk * d.nz + d.nz) * sizeof(double2);
-        const bool zlines = !planes && (d.nz == 256 || d.nz == 512);
+        const bool zlines = !planes && wave_line(d.nz);
         auto z_lines = [&](auto inv) {
             constexpr bool kInv = decltype(inv)::value;
-            const dim3 g((unsigned)(((int64_t)d.M * d.nxh + 3) / 4), (unsigned)b.nprob, (unsigned)nmem);
-            if (d.nz == 256) k_lines_z<256, kInv><<<g, 256, 0, s->stream>>>(d, s->tb.twz, s->spec, nspec, b.ms);
-            else k_lines_z<512, kInv><<<g, 256, 0, s->stream>>>(d, s->tb.twz, s->spec, nspec, b.ms);
+            const int lb = d.nz == 64 ? 16 : (d.nz == 128 ? 8 : 4);  // lines per block
+            const dim3 g((unsigned)(((int64_t)d.M * d.nxh + lb - 1) / lb), (unsigned)b.nprob, (unsigned)nmem);
+#define NSPNP_LZ(NN) k_lines_z<NN, kInv><<<g, 256, 0, s->stream>>>(d, s->tb.twz, s->spec, nspec, b.ms)
+            if (d.nz == 64) NSPNP_LZ(64);
+            else if (d.nz == 128) NSPNP_LZ(128);
+            else if (d.nz == 256) NSPNP_LZ(256);
+            else NSPNP_LZ(512);
+#undef NSPNP_LZ
         };
         if (zlines) {
             ProfScope prof_(s, K_FFTZ_FWD);
@@ -2176,10 +2225,14 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
         ProfScope prof_(s, K_FFTX_INV);
 #define NSPNP_LC(TT, NN) k_lines_c2r<TT, NN><<<gl, 256, 0, s->stream>>>(d, s->tb, b, s->spec, nspec)
         if (s->fp64) {
-            if (d.nx == 256) NSPNP_LC(double, 256);
+            if (d.nx == 64) NSPNP_LC(double, 64);
+            else if (d.nx == 128) NSPNP_LC(double, 128);
+            else if (d.nx == 256) NSPNP_LC(double, 256);
             else NSPNP_LC(double, 512);
         } else {
-            if (d.nx == 256) NSPNP_LC(float, 256);
+            if (d.nx == 64) NSPNP_LC(float, 64);
+            else if (d.nx == 128) NSPNP_LC(float, 128);
+            else if (d.nx == 256) NSPNP_LC(float, 256);
             else NSPNP_LC(float, 512);
         }
 #undef NSPNP_LC

@@ -1,6 +1,6 @@
 """The elliptic solve on the paths that its sizes choose: whole-plane
 transforms (planes of up to two blocks per CU's LDS) and their limit, radices
-2, 3, 4 and 8 in either direction, lines of 256 and 512 points (a wave each),
+2, 3, 4 and 8 in either direction, lines of 64 to 512 points (1, 2 or 4 a wave),
 groups of 16, 32 and 64 lanes per mode, and,
 for caller-owned right-hand sides and above 320 rows, slabs of rows in
 registers at the edges of every slab height.  Against the oracle.  Bar: the
@@ -37,7 +37,8 @@ def check_solve(P, O, cfg):
 
 
 @pytest.mark.parametrize("nx,nz", [(4, 4), (6, 4), (4, 54), (16, 12), (48, 48), (64, 64), (36, 108), (64, 72), (128, 32), (256, 18), (512, 4),
-                                   (4, 512), (768, 4), (256, 54), (512, 54), (54, 256), (36, 512), (1024, 6)])
+                                   (4, 512), (768, 4), (256, 54), (512, 54), (54, 256), (36, 512), (1024, 6),
+                                   (64, 162), (162, 64), (64, 256), (256, 64), (128, 108), (108, 128), (128, 128)])
 def test_plane_transforms(oracle_mod, nx, nz):
     import paper_1701_02005_amd as P
     check_solve(P, oracle_mod, config(P, nx, 9, nz))
