@@ -798,8 +798,7 @@ struct CycArgs {
     void *q[5];
     void *r[5];
     const double *cyc;
-    int dir;    // 0: x-lines (contiguous), 1: z-lines (stride nx)
-    int out_r;  // 1: the solution replaces r; 0: q += solution
+    int lines;  // x-lines: lines per wave
 };
 
 // One block per stage, diffusivity and direction; one thread runs the serial
@@ -854,100 +853,52 @@ __global__ void __launch_bounds__(64) k_cyc_coef(Dims d, const Phys *phys, const
         for (int q = 0; q < 4; ++q) blk[q * Nmax + i] = s_t[q][i];
 }
 
-// One tile of kCycTx periodic lines of one field per block, staged in LDS
-// (x-lines: each line contiguous; z-lines: kCycTx neighbouring columns per
-// element, 128-byte runs in FP64); each wave solves one line with its N points
-// split into 64 contiguous lane segments (affine-map scans across the wave),
-// then applies the periodic correction (the line's end values y_0, y_{N-1}
-// broadcast from their lanes).
-constexpr int kCycTx = 16;
-
-constexpr int kCycBatch = 8;  // loads per thread per wait in the periodic line solves
-
-template <typename T, int R>
-__global__ void __launch_bounds__(256) k_cyc_scan(CycArgs a) {
-    extern __shared__ double s_l[];
-    const uint3 blk = xcd_block3();
-    const int f = (int)blk.y, ty = f < 3 ? 0 : 1;
-    const int dir = a.dir, nx = a.d.nx, nz = a.d.nz;
-    const int N = dir == 0 ? nx : nz, L = dir == 0 ? nz : nx;  // points per line, lines per row
-    const int ntl = (L + kCycTx - 1) / kCycTx;
-    const int j = (int)blk.x / ntl, l0 = ((int)blk.x - j * ntl) * kCycTx;
-    const int nl = (L - l0) < kCycTx ? (L - l0) : kCycTx;
-    const unsigned upl = (unsigned)a.d.plane, row = (unsigned)j * upl;
-    T *rr = (T *)member_ptr_at(a.r[f], a.ms, blk.z);
-    T *qq = (T *)member_ptr_at(a.q[f], a.ms, blk.z);
-    const int64_t nb = cyc_block_doubles(nx, nz), Nmax = (nb - 4) / 4;
-    const double *cb = member_ptr_at(a.cyc, a.ms, blk.z) + ((int64_t)(a.st.k * 2 + ty) * 2 + dir) * nb;
-    const double *cg = cb, *cm = cb + Nmax, *cn = cb + 2 * Nmax, *cz = cb + 3 * Nmax;
-    const double vf = cb[4 * Nmax], sf = cb[4 * Nmax + 1];
-    constexpr int LD = kCycTx + 1;
-    const int ntile = N * kCycTx, bd = (int)blockDim.x;
-    // element (point i, line c) of the tile: x-lines (l0 + c) nx + i, z-lines i nx + l0 + c
-    auto addr = [&](int i, int c) -> unsigned {
-        return row + (dir == 0 ? (unsigned)(l0 + c) * (unsigned)nx + (unsigned)i : (unsigned)i * (unsigned)nx + (unsigned)(l0 + c));
-    };
-    // staging order: along the contiguous direction of memory (point i, line c of element e)
-    struct IC {
-        int i, c;
-    };
-    auto split = [&](int e) -> IC {
-        if (dir == 0) {
-            const int c = e / N;
-            return IC{e - c * N, c};
-        }
-        const int i = e / kCycTx;
-        return IC{i, e - i * kCycTx};
-    };
-    for (int e0 = threadIdx.x; e0 < ntile; e0 += kCycBatch * bd) {
-        T v[kCycBatch];
+// One line over the lanes of a wave, R contiguous points per lane: affine-map
+// scans across the wave, then the periodic correction (the line's end values
+// y_0, y_{N-1} broadcast from their lanes).  The recurrences' coefficients and
+// the scans' multipliers are the same for every line.
+template <int R>
+struct CycWave {
+    double g[R], mm[R], nn[R], zz[R], qm[6], sm[6], vf, sf;
+    int lane, last_lane, last_t;
+    __device__ __forceinline__ void load(const CycArgs &a, int ty, int dir, unsigned mem, int N) {
+        const int64_t nb = cyc_block_doubles(a.d.nx, a.d.nz), Nmax = (nb - 4) / 4;
+        const double *cb = member_ptr_at(a.cyc, a.ms, mem) + ((int64_t)(a.st.k * 2 + ty) * 2 + dir) * nb;
+        const double *cg = cb, *cm = cb + Nmax, *cn = cb + 2 * Nmax, *cz = cb + 3 * Nmax;
+        vf = cb[4 * Nmax];
+        sf = cb[4 * Nmax + 1];
+        lane = threadIdx.x & 63;
+        last_lane = (N - 1) / R;
+        last_t = (N - 1) - last_lane * R;
 #pragma unroll
-        for (int u = 0; u < kCycBatch; ++u) {
-            const int e = e0 + u * bd;
-            const IC p = split(e < ntile ? e : 0);
-            v[u] = ld_once(rr + ((e < ntile && p.c < nl) ? addr(p.i, p.c) : row));
-        }
-#pragma unroll
-        for (int u = 0; u < kCycBatch; ++u) {
-            const int e = e0 + u * bd;
-            if (e < ntile) {
-                const IC p = split(e);
-                s_l[p.i * LD + p.c] = (p.c < nl) ? (double)v[u] : 0.0;
-            }
+        for (int t = 0; t < R; ++t) {
+            const int i = lane * R + t;
+            const bool in = i < N;
+            g[t] = in ? cg[i] : 0.0;
+            mm[t] = in ? cm[i] : 1.0;
+            nn[t] = in ? cn[i] : 1.0;
+            zz[t] = in ? cz[i] : 0.0;
         }
     }
-    __syncthreads();
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = blockDim.x >> 6;
-    const int js = lane * R;
-    double g[R], mm[R], nn[R], zz[R];
-    double Qs = 1.0, Ss = 1.0;
+    __device__ __forceinline__ void products() {
+        double Qs = 1.0, Ss = 1.0;
 #pragma unroll
-    for (int t = 0; t < R; ++t) {
-        const int i = js + t;
-        const bool in = i < N;
-        g[t] = in ? cg[i] : 0.0;
-        mm[t] = in ? cm[i] : 1.0;
-        nn[t] = in ? cn[i] : 1.0;
-        zz[t] = in ? cz[i] : 0.0;
-        Qs *= mm[t];
-        Ss *= nn[t];
+        for (int t = 0; t < R; ++t) {
+            Qs *= mm[t];
+            Ss *= nn[t];
+        }
+#pragma unroll
+        for (int st = 0; st < 6; ++st) {
+            const int sft = 1 << st;
+            qm[st] = Qs;
+            sm[st] = Ss;
+            const double Qp = __shfl_up(Qs, sft, 64), Sp = __shfl_down(Ss, sft, 64);
+            if (lane >= sft) Qs *= Qp;
+            if (lane + sft < 64) Ss *= Sp;
+        }
     }
-    double qm[6], sm[6];
-#pragma unroll
-    for (int st = 0; st < 6; ++st) {
-        const int sft = 1 << st;
-        qm[st] = Qs;
-        sm[st] = Ss;
-        const double Qp = __shfl_up(Qs, sft, 64), Sp = __shfl_down(Ss, sft, 64);
-        if (lane >= sft) Qs *= Qp;
-        if (lane + sft < 64) Ss *= Sp;
-    }
-    const int last_lane = (N - 1) / R, last_t = (N - 1) - last_lane * R;
-    for (int c = wave; c < nl; c += nwave) {
-        double *col = s_l + c;
-        double x[R];
-#pragma unroll
-        for (int t = 0; t < R; ++t) x[t] = (js + t < N) ? col[(js + t) * LD] : 0.0;
+    // the solution of a line (points past its end: 0 in)
+    __device__ __forceinline__ void solve(double *x) const {
         double Tf = 0.0;
 #pragma unroll
         for (int t = 0; t < R; ++t) Tf = g[t] * x[t] + mm[t] * Tf;
@@ -987,31 +938,122 @@ __global__ void __launch_bounds__(256) k_cyc_scan(CycArgs a) {
         const double yl = __shfl(ylast, last_lane, 64);
         const double wcor = (y0 + vf * yl) * sf;
 #pragma unroll
-        for (int t = 0; t < R; ++t)
-            if (js + t < N) col[(js + t) * LD] = x[t] - wcor * zz[t];
+        for (int t = 0; t < R; ++t) x[t] = x[t] - wcor * zz[t];
     }
-    __syncthreads();
+};
+
+// x-lines, the solution in place of r: contiguous, so each wave takes its
+// lines straight from memory into its lanes, kCycLines at a time with all of
+// their loads in flight, without LDS tiles or barriers.  Bound by the scans'
+// moves between lanes: 128 x 129 x 128 FP64 45 us (3.7 TB/s); through tiles in
+// LDS, as the z-lines, 57 us (two passes more through LDS, and an integer
+// division per element).
+constexpr int cyc_lines(int R) { return R <= 2 ? 4 : (R <= 4 ? 2 : 1); }
+
+template <typename T, int R>
+__global__ void __launch_bounds__(256) k_cyc_x(CycArgs a) {
+    constexpr int kB = cyc_lines(R);
+    const int f = (int)blockIdx.y, N = a.d.nx;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), nlines = a.d.M * a.d.nz;
+    T *rr = (T *)member_ptr_at(a.r[f], a.ms, blockIdx.z);
+    CycWave<R> s;
+    s.load(a, f < 3 ? 0 : 1, 0, blockIdx.z, N);
+    const int js = s.lane * R;
+    const int l0 = ((int)blockIdx.x * 4 + wave) * a.lines, l1 = l0 + a.lines < nlines ? l0 + a.lines : nlines;
+    if (l0 >= l1) return;
+    T v[kB][R];
+    // points past the line and lines past the last one read what exists
+    auto load = [&](int l) {
+#pragma unroll
+        for (int b = 0; b < kB; ++b) {
+            const T *p = rr + (int64_t)(l + b < l1 ? l + b : l1 - 1) * N;
+#pragma unroll
+            for (int t = 0; t < R; ++t) v[b][t] = ld_once(p + (js + t < N ? js + t : 0));
+        }
+    };
+    load(l0);
+    s.products();
+    for (int l = l0; l < l1; l += kB) {
+        double x[kB][R];
+#pragma unroll
+        for (int b = 0; b < kB; ++b)
+#pragma unroll
+            for (int t = 0; t < R; ++t) x[b][t] = js + t < N ? (double)v[b][t] : 0.0;
+        if (l + kB < l1) load(l + kB);  // lands while these are solved
+#pragma unroll
+        for (int b = 0; b < kB; ++b) s.solve(x[b]);
+#pragma unroll
+        for (int b = 0; b < kB; ++b) {
+            T *p = rr + (int64_t)(l + b) * N;
+#pragma unroll
+            for (int t = 0; t < R; ++t)
+                if (l + b < l1 && js + t < N) st_once(p + js + t, (T)x[b][t]);
+        }
+    }
+}
+
+// z-lines, added to the fields: one tile of kCycTx neighbouring columns of one
+// field per block, staged in LDS in 128-byte runs (FP64), a wave per line.
+constexpr int kCycTx = 16;
+
+constexpr int kCycBatch = 8;  // loads per thread per wait
+
+template <typename T, int R>
+__global__ void __launch_bounds__(256) k_cyc_z(CycArgs a) {
+    extern __shared__ double s_l[];
+    const uint3 blk = xcd_block3();
+    const int f = (int)blk.y;
+    const int nx = a.d.nx, N = a.d.nz;
+    const int ntl = (nx + kCycTx - 1) / kCycTx;
+    const int j = (int)blk.x / ntl, l0 = ((int)blk.x - j * ntl) * kCycTx;
+    const int nl = (nx - l0) < kCycTx ? (nx - l0) : kCycTx;
+    const unsigned row = (unsigned)j * (unsigned)a.d.plane;
+    const T *rr = (const T *)member_ptr_at(a.r[f], a.ms, blk.z);
+    T *qq = (T *)member_ptr_at(a.q[f], a.ms, blk.z);
+    constexpr int LD = kCycTx + 1;
+    const int ntile = N * kCycTx, bd = (int)blockDim.x;
+    // element e of the tile: point i = e / kCycTx of line c = e % kCycTx
+    auto addr = [&](int e) -> unsigned { return row + (unsigned)(e / kCycTx) * (unsigned)nx + (unsigned)(l0 + e % kCycTx); };
     for (int e0 = threadIdx.x; e0 < ntile; e0 += kCycBatch * bd) {
         T v[kCycBatch];
-        if (!a.out_r) {
 #pragma unroll
-            for (int u = 0; u < kCycBatch; ++u) {
-                const int e = e0 + u * bd;
-                const IC p = split(e < ntile ? e : 0);
-                v[u] = ld_once(qq + ((e < ntile && p.c < nl) ? addr(p.i, p.c) : row));
-            }
+        for (int u = 0; u < kCycBatch; ++u) {
+            const int e = e0 + u * bd;
+            v[u] = ld_once(rr + ((e < ntile && e % kCycTx < nl) ? addr(e) : row));
         }
 #pragma unroll
         for (int u = 0; u < kCycBatch; ++u) {
             const int e = e0 + u * bd;
-            if (e < ntile) {
-                const IC p = split(e);
-                if (p.c < nl) {
-                    const double xs = s_l[p.i * LD + p.c];
-                    if (a.out_r) st_once(rr + addr(p.i, p.c), (T)xs);
-                    else st_once(qq + addr(p.i, p.c), (T)((double)v[u] + xs));
-                }
-            }
+            if (e < ntile) s_l[e / kCycTx * LD + e % kCycTx] = (e % kCycTx < nl) ? (double)v[u] : 0.0;
+        }
+    }
+    __syncthreads();
+    CycWave<R> s;
+    s.load(a, f < 3 ? 0 : 1, 1, blk.z, N);
+    s.products();
+    const int js = s.lane * R, wave = threadIdx.x >> 6, nwave = blockDim.x >> 6;
+    for (int c = wave; c < nl; c += nwave) {
+        double *col = s_l + c;
+        double x[R];
+#pragma unroll
+        for (int t = 0; t < R; ++t) x[t] = (js + t < N) ? col[(js + t) * LD] : 0.0;
+        s.solve(x);
+#pragma unroll
+        for (int t = 0; t < R; ++t)
+            if (js + t < N) col[(js + t) * LD] = x[t];
+    }
+    __syncthreads();
+    for (int e0 = threadIdx.x; e0 < ntile; e0 += kCycBatch * bd) {
+        T v[kCycBatch];
+#pragma unroll
+        for (int u = 0; u < kCycBatch; ++u) {
+            const int e = e0 + u * bd;
+            v[u] = ld_once(qq + ((e < ntile && e % kCycTx < nl) ? addr(e) : row));
+        }
+#pragma unroll
+        for (int u = 0; u < kCycBatch; ++u) {
+            const int e = e0 + u * bd;
+            if (e < ntile && e % kCycTx < nl) st_once(qq + addr(e), (T)((double)v[u] + s_l[e / kCycTx * LD + e % kCycTx]));
         }
     }
 }
@@ -1421,36 +1463,45 @@ hipError_t launch_explicit_debug(nspnp_state *s, double *const out[5]) {
     return launch_adv_limit(s, a.st, out);
 }
 
-// Periodic-line solves of the five fields along x (dir 0) or z (dir 1).
-static hipError_t launch_cyc(nspnp_state *s, const Stage &st, int dir, int out_r) {
+// Periodic-line solves of the five fields along x (into r) or z (added to q).
+static hipError_t launch_cyc(nspnp_state *s, const Stage &st, bool along_z) {
     CycArgs c{};
     c.d = s->d;
     c.ms = s->mstride;
     c.st = st;
     for (int q = 0; q < 5; ++q) { c.q[q] = s->f[q]; c.r[q] = s->r[q]; }
     c.cyc = s->cyc;
-    c.dir = dir;
-    c.out_r = out_r;
-    const int N = dir == 0 ? s->d.nx : s->d.nz, L = dir == 0 ? s->d.nz : s->d.nx;
-    const dim3 g((unsigned)(s->d.M * ((L + kCycTx - 1) / kCycTx)), 5, (unsigned)s->nmem);
-    const size_t lds = (size_t)N * (kCycTx + 1) * sizeof(double);
-    if (lds > (size_t)s->lds_max) return hipErrorInvalidValue;
+    const int N = along_z ? s->d.nz : s->d.nx;
     int rpl = (N + 63) / 64;  // points per lane, rounded up to an instantiated count
     const int have[] = {1, 2, 3, 4, 6, 8, 12, 16};
     int R = 0;
     for (int h : have)
         if (!R && h >= rpl) R = h;
     if (!R) return hipErrorInvalidValue;
-    auto go = [&](const void *fn, auto kernel) -> hipError_t {
+    // x: up to 16 lines a wave, fewer while that leaves the chip with fewer
+    // than four blocks per CU
+    const int64_t nlines = (int64_t)s->d.M * s->d.nz;
+    c.lines = 16;
+    while (c.lines > 1 && (nlines + 4 * c.lines - 1) / (4 * c.lines) * 5 * s->nmem < 1024) c.lines /= 2;
+    const dim3 gx((unsigned)((nlines + 4 * c.lines - 1) / (4 * c.lines)), 5, (unsigned)s->nmem);
+    const dim3 gz((unsigned)(s->d.M * ((s->d.nx + kCycTx - 1) / kCycTx)), 5, (unsigned)s->nmem);
+    const size_t lds = (size_t)N * (kCycTx + 1) * sizeof(double);
+    if (along_z && lds > (size_t)s->lds_max) return hipErrorInvalidValue;
+    auto go_z = [&](const void *fn, auto kernel) -> hipError_t {
         const hipError_t e = lds_opt_in(fn, lds, s->lds_max);
         if (e != hipSuccess) return e;
-        kernel<<<g, 256, lds, s->stream>>>(c);
+        kernel<<<gz, 256, lds, s->stream>>>(c);
+        return hipGetLastError();
+    };
+    auto go_x = [&](auto kernel) -> hipError_t {
+        kernel<<<gx, 256, 0, s->stream>>>(c);
         return hipGetLastError();
     };
 #define NSPNP_CYC_CASE(RR)                                                                             \
     case RR:                                                                                           \
-        return s->fp64 ? go((const void *)k_cyc_scan<double, RR>, k_cyc_scan<double, RR>)              \
-                       : go((const void *)k_cyc_scan<float, RR>, k_cyc_scan<float, RR>);
+        if (!along_z) return s->fp64 ? go_x(k_cyc_x<double, RR>) : go_x(k_cyc_x<float, RR>);           \
+        return s->fp64 ? go_z((const void *)k_cyc_z<double, RR>, k_cyc_z<double, RR>)                  \
+                       : go_z((const void *)k_cyc_z<float, RR>, k_cyc_z<float, RR>);
     switch (R) {
         NSPNP_CYC_CASE(1)
         NSPNP_CYC_CASE(2)
@@ -1561,9 +1612,9 @@ hipError_t launch_cn_solve(nspnp_state *s, const Stage &st) {
     if (e != hipSuccess) return e;
     if (!s->cfg.implicit_xz) return launch_cn_y(s, st, false);
     // three-direction factorisation: x-lines into r, y (this solve) into r, then z-lines with q += solution
-    if ((e = launch_cyc(s, st, 0, 1)) != hipSuccess) return e;
+    if ((e = launch_cyc(s, st, false)) != hipSuccess) return e;
     if ((e = launch_cn_y(s, st, true)) != hipSuccess) return e;
-    return launch_cyc(s, st, 1, 0);
+    return launch_cyc(s, st, true);
 }
 
 hipError_t launch_correct(nspnp_state *s, const Stage &st, bool update_p, double fixed, bool advance_clock) {

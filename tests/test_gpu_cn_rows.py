@@ -29,3 +29,20 @@ def test_rows(oracle_mod, rows, nx, nz, imp):
             a, b = g.get_field(k).cpu().numpy(), o.field(k)
             err = np.max(np.abs(a - b)) / max(np.max(np.abs(b)), 1e-300)
             assert err < bar, (prec, k, err)
+
+
+# The x-lines of the three-direction form: points per lane 1 to 16, whole and
+# partial lanes, lines that are no multiple of a wave's, at the same bar.
+@pytest.mark.parametrize("nx", [4, 54, 64, 72, 128, 162, 192, 216, 256, 288, 486, 512, 648, 768, 972, 1024])
+def test_periodic_x_lines(oracle_mod, nx):
+    import paper_1701_02005_amd as P
+    cfg = dataclasses.replace(P.configs.couette_small(), nx=nx, ny=10, nz=6, dt=0.0, cfl=0.5, seed=nx, u_noise=0.05,
+                              implicit_xz=1)
+    o = oracle_mod.Oracle(**cfg.oracle_kwargs())
+    o.init(cfg.seed, cfg.u_noise, cfg.c_noise)
+    o.run(3)
+    g = P.Solver(cfg)
+    g.step(3)
+    for k in ("u", "v", "w", "cp", "cm", "phi", "p"):
+        a, b = g.get_field(k).cpu().numpy(), o.field(k)
+        assert np.max(np.abs(a - b)) / max(np.max(np.abs(b)), 1e-300) < 1e-10, k
