@@ -18,7 +18,7 @@ def close(got, ref):
 
 
 @pytest.mark.parametrize("rows", [1, 15, 16, 17, 33, 64])
-@pytest.mark.parametrize("sizes", [(3, 5), (3, 16, 17, 7), (40, 288, 31), (3, 256, 256, 579), (5, 1000, 9)],
+@pytest.mark.parametrize("sizes", [(3, 5), (3, 16, 17, 7), (40, 288, 31), (3, 256, 256, 579), (4, 768, 7), (4, 800, 7), (5, 1000, 9)],
                          ids=lambda s: "x".join(map(str, s)))
 def test_edges(rows, sizes):
     import torch
