@@ -81,6 +81,29 @@ __device__ __forceinline__ void shift_explicit(ExplicitArgs &a, unsigned mem) {
 // needs are carried in registers from the previous row.
 constexpr int kNF = 7;  // u v w c+ c- phi p
 
+// Minus the divergence of (limited face value - mean) times the face velocity
+// of one species: x and z faces right, left, front, back, y faces top and
+// bottom.  q: c at x +1 -1 +2 -2, z +1 -1 +2 -2; col: rows j - 2 .. j + 2 of the
+// cell's column (rows outside the grid are not used).
+template <typename T>
+__device__ __forceinline__ T limit_delta(const T *q, const T *col, T uR, T uL, T wF, T wB, T vt, T vb, int j, int M,
+                                         T idx, T idz, T idn) {
+    const T half = T(0.5);
+    const bool ur = uR >= T(0), ul = uL >= T(0), wf = wF >= T(0), wb = wB >= T(0);
+    const bool upt = vt >= T(0), upb = vb >= T(0);
+    const bool have_t = upt ? (j > 0) : (j + 2 < M), have_b = upb ? (j > 1) : (j + 1 < M);
+    const T cc = col[2], cyp = col[3], cym = col[1];
+    const T cxp = q[0], cxm = q[1], czp = q[4], czm = q[5];
+    const T dR = adv_face(cc, cxp, ur ? cxm : q[2], ur, true) - half * (cxp + cc);
+    const T dL = adv_face(cxm, cc, ul ? q[3] : cxp, ul, true) - half * (cc + cxm);
+    const T dF = adv_face(cc, czp, wf ? czm : q[6], wf, true) - half * (czp + cc);
+    const T dB = adv_face(czm, cc, wb ? q[7] : czp, wb, true) - half * (cc + czm);
+    // top face (rows j, j + 1) and bottom face (rows j - 1, j)
+    const T dT = (j + 1 < M) ? adv_face(cc, cyp, upt ? cym : col[4], upt, have_t) - half * (cyp + cc) : T(0);
+    const T dD = (j > 0) ? adv_face(cym, cc, upb ? col[0] : cyp, upb, have_b) - half * (cc + cym) : T(0);
+    return -((uR * dR - uL * dL) * idx + (wF * dF - wB * dB) * idz + (vt * dT - vb * dD) * idn);
+}
+
 template <typename T, int kHalo>
 struct HaloRegs {
     T v[kNF][kHalo];
@@ -90,7 +113,13 @@ struct HaloRegs {
 // is its own instantiation, so the substep kernel carries none of its state.
 // kTx > 0: the tile is kTx columns by kTz z-lines (a.tx, a.tz ignored), so
 // every LDS neighbour offset is a compile-time constant.
-template <typename T, int kHalo, int kWaves, int kMode, int kTx = 0, int kTz = 0>
+// kLim (the mixed form): the limited advective flux of migration_face 2 is
+// formed here instead of in a pass of its own, which reads u, v, w, c+- and
+// the ions' H and r again and rewrites those: 256 x 193 x 256 277 us against 222
+// and 157, bound by arithmetic (12 divisions a species and cell).  The values two
+// columns away come from the caches (the row's own tile loads them), those two
+// rows up from memory one row early.  FP64 keeps the pass (registers).
+template <typename T, int kHalo, int kWaves, int kMode, int kTx = 0, int kTz = 0, bool kLim = false>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves))) k_explicit(ExplicitArgs a) {
     extern __shared__ unsigned char s_raw[];
     T *sm = (T *)s_raw;  // [slot 0..1][field 0..6][halo tile]
@@ -165,6 +194,16 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves
     const int ip = (i + 1 >= nx) ? 0 : i + 1;
     const int kp = (k + 1 >= nz) ? 0 : k + 1;
     const int e_xp = k * nx + ip, e_zp = kp * nx + i;
+    unsigned two_off[4] = {0, 0, 0, 0};  // x + 2, x - 2, z + 2, z - 2, bytes in the plane
+    if constexpr (kLim) {
+        if (active) {
+            auto wrap = [](int q, int n) { return q < 0 ? q + n : (q >= n ? q - n : q); };  // n >= 4
+            two_off[0] = (unsigned)(k * nx + wrap(i + 2, nx)) * (unsigned)sizeof(T);
+            two_off[1] = (unsigned)(k * nx + wrap(i - 2, nx)) * (unsigned)sizeof(T);
+            two_off[2] = (unsigned)(wrap(k + 2, nz) * nx + i) * (unsigned)sizeof(T);
+            two_off[3] = (unsigned)(wrap(k - 2, nz) * nx + i) * (unsigned)sizeof(T);
+        }
+    }
 
     const int j0 = (int)slab * a.slab_rows;
     const int j1 = (j0 + a.slab_rows < M) ? j0 + a.slab_rows : M;
@@ -179,6 +218,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves
         fm = F[5][q + e]; pm = F[6][q + e];
         u_xp_m = F[0][q + e_xp];
         w_zp_m = F[2][q + e_zp];
+    }
+    T c_mm[2] = {zero, zero};  // c+- of row j - 2
+    if constexpr (kLim) {
+        if (j0 > 1)
+#pragma unroll
+            for (int sp = 0; sp < 2; ++sp) c_mm[sp] = *byte_at(F[3 + sp], (unsigned)(j0 - 2) * plb + ueb);
     }
     T hold_c[5], hold_n[5];
 #pragma unroll
@@ -209,6 +254,16 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves
             for (int f = 0; f < 5; ++f) hold_n[f] = ld_once(byte_at((const T *)a.h[f], (unsigned)(j + 1) * plb + ueb));
         }
         if constexpr (sizeof(T) == 8) __builtin_amdgcn_s_setprio(0);
+        T far[2][5];  // c+- of row j at the four, and of row j + 2
+        if constexpr (kLim) {
+            const unsigned row = (unsigned)j * plb, up2 = (unsigned)(j + 2 < M ? j + 2 : M - 1) * plb + ueb;
+#pragma unroll
+            for (int sp = 0; sp < 2; ++sp) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) far[sp][q] = *byte_at(F[3 + sp], row + two_off[q]);
+                far[sp][4] = *byte_at(F[3 + sp], up2);
+            }
+        }
         const bool has_up = (j + 1 < M), has_dn = (j > 0);
         const unsigned qb = (unsigned)j * plb + ueb;  // this cell, bytes
         if (active) {
@@ -222,12 +277,22 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves
             const T rho0 = ac - bc;
             const T uxp = X(sc, 0, 1, 0), wzp = X(sc, 2, 0, 1);
 
-            auto emit = [&](int f, T hval, T gp, T nu_ly) {
+            // (delta: added to H, and dt gam times it to r, each rounded as a pass
+            // over the stored values rounds them)
+            auto emit = [&](int f, T hval, T gp, T nu_ly, T delta) {
                 if constexpr (mode == 1) {
                     a.dbg[f][(size_t)j * (size_t)pl + (unsigned)e] = (double)hval;
                     return;
                 }
-                const T rv = dt * (gam * hval + zet * hold_c[f] - alp * gp + alp * nu_ly);
+                T rv = dt * (gam * hval + zet * hold_c[f] - alp * gp + alp * nu_ly);
+                if constexpr (kLim) {
+                    if (f >= 3) {
+                        asm("" : "+v"(rv));  // (not merged into the sums below)
+                        asm("" : "+v"(hval));
+                        rv = __builtin_fmaf(dt * gam, delta, rv);
+                        hval = hval + delta;
+                    }
+                }
                 st_once(byte_at((T *)a.r[f], qb), rv);
                 if (keep) st_once(byte_at((T *)a.h[f], qb), hval);
             };
@@ -255,7 +320,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves
                 const T f = kf * half * (rho0 + rhox) * (ph0 - X(sc, 5, -1, 0)) * idx_;
                 const T ly = ((ut - uc) * idct - (uc - ub) * idcb) * idn;
                 const T lapH = imp ? zero : lap, lapI = imp ? lap : zero;
-                emit(0, -(cx + cy + cz) + ire * lapH + f, (pc - X(sc, 6, -1, 0)) * idx_, ire * (ly + lapI));
+                emit(0, -(cx + cy + cz) + ire * lapH + f, (pc - X(sc, 6, -1, 0)) * idx_, ire * (ly + lapI), zero);
             }
             __builtin_amdgcn_sched_barrier(0);
             // ---------------- w on the z-face ----------------
@@ -281,7 +346,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves
                 const T f = kf * half * (rho0 + rhoz) * (ph0 - X(sc, 5, 0, -1)) * idz_;
                 const T ly = ((wt - wc) * idct - (wc - wb) * idcb) * idn;
                 const T lapH = imp ? zero : lap, lapI = imp ? lap : zero;
-                emit(2, -(cx + cy + cz) + ire * lapH + f, (pc - X(sc, 6, 0, -1)) * idz_, ire * (ly + lapI));
+                emit(2, -(cx + cy + cz) + ire * lapH + f, (pc - X(sc, 6, 0, -1)) * idz_, ire * (ly + lapI), zero);
             }
             __builtin_amdgcn_sched_barrier(0);
             // ---------------- v on the bottom y-face of row j ----------------
@@ -305,9 +370,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves
                 const T f = kf * half * (rho0 + rhoy) * ey;
                 const T ly = ((vtop - vc) * idn - (vc - vbot) * idn_lo) * idcb;
                 const T lapH = imp ? zero : lap, lapI = imp ? lap : zero;
-                emit(1, -(cx + cy + cz) + ire * lapH + f, (pc - pm) * idcb, ire * (ly + lapI));
+                emit(1, -(cx + cy + cz) + ire * lapH + f, (pc - pm) * idcb, ire * (ly + lapI), zero);
             } else {
-                emit(1, T(0), T(0), T(0));
+                emit(1, T(0), T(0), T(0), zero);
                 if constexpr (mode == 0) st_once(byte_at((T *)a.r[1], qb), T(0));
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -362,10 +427,20 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves
                     const T dxx = (cxp - two * cc + cxm) * ix2 + (czp - two * cc + czm) * iz2;
                     const T dxxH = imp ? zero : dxx;
                     const T diffI = imp ? kd * ((dft - dfb) * idn + dxx) : kd * (dft - dfb) * idn;
-                    emit(fi, -(ax + ay + az) + kd * (dxxH + zs * (mx + my + mz)), T(0), diffI);
+                    T delta = zero;
+                    if constexpr (kLim) {
+                        const T q[8] = {cxp, cxm, far[sp][0], far[sp][1], czp, czm, far[sp][2], far[sp][3]};
+                        const T col[5] = {c_mm[sp], cd, cc, cu, far[sp][4]};
+                        delta = limit_delta(q, col, uxp, uc, wzp, wc, vt, has_dn ? vc : zero, j, M, idx_, idz_, idn);
+                    }
+                    emit(fi, -(ax + ay + az) + kd * (dxxH + zs * (mx + my + mz)), T(0), diffI, delta);
                 }
             }
             // carry row j as row j - 1 of the next step
+            if constexpr (kLim) {
+                c_mm[0] = am;
+                c_mm[1] = bm;
+            }
             um = uc; vm = vc; wm = wc; am = ac; bm = bc; fm = ph0; pm = pc;
             u_xp_m = uxp;
             w_zp_m = wzp;
@@ -1216,10 +1291,20 @@ static void explicit_tiling(const Dims &d, bool fp64, int &threads, int slab_row
 
 // Launch of the explicit kernel with its halo-tile LDS ring; kHalo halo
 // positions per thread cover the tile plus halo ((tx+2)(tz+2) <= kHalo * threads).
+// The limited advective flux where that is a form of this kernel.
+static bool explicit_limits(const nspnp_state *s, const ExplicitArgs &a, int threads) {
+    return s->cfg.migration_face == 2 && !s->fp64 && a.mode == 0 && (a.tx + 2) * (a.tz + 2) <= 2 * threads;
+}
 static hipError_t explicit_launch(nspnp_state *s, const ExplicitArgs &a, int threads, unsigned blocks) {
     const int hs = (a.tx + 2) * (a.tz + 2);
     const size_t lds = 2 * (size_t)kNF * hs * s->wsize;
     const bool dbg = a.mode == 1;
+    if (explicit_limits(s, a, threads)) {
+        if (threads == 256 && a.tx == 64 && a.tz == 4) k_explicit<float, 2, 3, 0, 64, 4, true><<<blocks, threads, lds, s->stream>>>(a);
+        else if (threads == 192 && a.tx == 48 && a.tz == 4) k_explicit<float, 2, 3, 0, 48, 4, true><<<blocks, threads, lds, s->stream>>>(a);
+        else k_explicit<float, 2, 3, 0, 0, 0, true><<<blocks, threads, lds, s->stream>>>(a);
+        return hipGetLastError();
+    }
     if (!dbg && threads == 256 && s->fp64 && a.tx == 32 && a.tz == 8) {  // the common tiles
         // three waves per SIMD (at most 168 VGPRs; 12 bytes per lane spill):
         // with the fused Crank-Nicolson first pass the compiler's own choice
@@ -1325,7 +1410,6 @@ __global__ void __launch_bounds__(256) k_adv_limit(AdvArgs a) {
     const T *cf[2] = {member_ptr_at((const T *)a.c[0], ms, mem), member_ptr_at((const T *)a.c[1], ms, mem)};
     T *hf[2] = {member_ptr_at((T *)a.h[0], ms, mem), member_ptr_at((T *)a.h[1], ms, mem)};
     T *rf[2] = {member_ptr_at((T *)a.r[0], ms, mem), member_ptr_at((T *)a.r[1], ms, mem)};
-    const T half = T(0.5);
     const T idx_ = T(1.0 / a.d.dx), idz_ = T(1.0 / a.d.dz);
     const T dtg = T(member_ptr_at(a.clock, ms, mem)[1]) * T(a.st.gam);
     const bool keep = a.st.k < 2;
@@ -1362,23 +1446,9 @@ __global__ void __launch_bounds__(256) k_adv_limit(AdvArgs a) {
         for (int sp = 0; sp < 2; ++sp) nxt[sp] = *byte_at(cf[sp], rowb(j + 3) + ex);
         const T vb = (j > 0) ? vj : T(0), vt = (j + 1 < M) ? vn : T(0);
         const T idn = T(uniform_load(a.tb.idn, j));
-        const bool ur = uR >= T(0), ul = uL >= T(0), wf = wF >= T(0), wb = wB >= T(0);
-        const bool upt = vt >= T(0), upb = vb >= T(0);
-        const bool have_t = upt ? (j > 0) : (j + 2 < M), have_b = upb ? (j > 1) : (j + 1 < M);
 #pragma unroll
         for (int sp = 0; sp < 2; ++sp) {
-            const T *q = nb[sp];
-            const T cc = win[sp][2], cyp = win[sp][3], cym = win[sp][1];
-            const T cxp = q[0], cxm = q[1], czp = q[4], czm = q[5];
-            const T dR = adv_face(cc, cxp, ur ? cxm : q[2], ur, true) - half * (cxp + cc);
-            const T dL = adv_face(cxm, cc, ul ? q[3] : cxp, ul, true) - half * (cc + cxm);
-            const T dF = adv_face(cc, czp, wf ? czm : q[6], wf, true) - half * (czp + cc);
-            const T dB = adv_face(czm, cc, wb ? q[7] : czp, wb, true) - half * (cc + czm);
-            // top face (rows j, j + 1) and bottom face (rows j - 1, j)
-            const T dT = (j + 1 < M) ? adv_face(cc, cyp, upt ? cym : win[sp][4], upt, have_t) - half * (cyp + cc)
-                                     : T(0);
-            const T dD = (j > 0) ? adv_face(cym, cc, upb ? win[sp][0] : cyp, upb, have_b) - half * (cc + cym) : T(0);
-            const T delta = -((uR * dR - uL * dL) * idx_ + (wF * dF - wB * dB) * idz_ + (vt * dT - vb * dD) * idn);
+            const T delta = limit_delta(nb[sp], win[sp], uR, uL, wF, wB, vt, vb, j, M, idx_, idz_, idn);
             if (a.mode == 1) {
                 a.dbg[sp][(size_t)j * (size_t)pl + (size_t)e] += (double)delta;
             } else {
@@ -1440,7 +1510,7 @@ hipError_t launch_explicit(nspnp_state *s, const Stage &st, bool /*write_r*/) {
     int tb = s->tiles.expl;
     explicit_tiling(s->d, s->fp64, tb, s->tiles.slab, s->nmem, a);
     const hipError_t e2 = explicit_launch(s, a, tb, (unsigned)((int64_t)a.chunks * a.slabs * s->nmem));
-    if (e2 != hipSuccess || s->cfg.migration_face != 2) return e2;
+    if (e2 != hipSuccess || s->cfg.migration_face != 2 || explicit_limits(s, a, tb)) return e2;
     return launch_adv_limit(s, st, nullptr);
 }
 
