@@ -47,6 +47,16 @@ CN_ROWS_KERNELS = ("k_cn_coef", "k_cn_rows")
 CN_SLAB_KERNELS = ("k_cn_coef", "k_cn_slab_scan", "k_cn_slab_apply")
 
 
+# the elliptic chain's other forms: lines a wave each, whole planes (their
+# kernels carry the z transforms too), modes in registers
+ELLIPTIC_KERNELS = {
+    "fft_x_r2c": (("k_lines_r2c",), ("k_plane_fwd",)),
+    "fft_z_fwd": (("k_lines_z",),),
+    "thomas_modes": (("k_mode_rows",), ("k_mode_columns",)),
+    "fft_z_inv": (("k_lines_z",),),
+    "fft_x_c2r": (("k_lines_c2r",), ("k_plane_inv",)),
+}
+
 # the z transforms under the fused y-march method (mode-solve tile 0): the
 # forward march (z transform + forward elimination) and the backward march
 # (back-substitution + inverse z transform); no separate mode-solve kernel
@@ -116,6 +126,9 @@ def main(argv=None):
             kernels = CN_ROWS_KERNELS
         if cls in Z_FUSED_KERNELS and all(k in per_kernel for k in Z_FUSED_KERNELS[cls]):
             kernels = Z_FUSED_KERNELS[cls]
+        for other in ELLIPTIC_KERNELS.get(cls, ()):
+            if not all(k in per_kernel for k in kernels) and all(k in per_kernel for k in other):
+                kernels = other
         if not all(k in per_kernel for k in kernels):
             continue
         fb = sum(per_kernel[k][0] for k in kernels)
