@@ -410,7 +410,12 @@ int step_handle(nspnp_state *s, int n) {
     for (int it = 0; it < n; ++it) {
         const int k = (int)(s->substeps % 3);
         const Stage st{kRkGam[k], kRkZet[k], kRkAlp[k], k};
-        if (k == 0) HIP_TRY(launch_dt(s));  // dt rule (adaptive runs) and health check
+        if (k == 0) {  // dt rule (adaptive runs) and health check
+            ProfScope prof_(s, K_DT);
+            int nparts = 0;
+            HIP_TRY(launch_dt(s, &nparts));
+            HIP_TRY(launch_step_coef(s, nparts));
+        }
         HIP_TRY(launch_explicit(s, st, true));
         HIP_TRY(launch_cn_solve(s, st));
         // pressure projection and potential depend only on the updated

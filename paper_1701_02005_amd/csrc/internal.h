@@ -437,7 +437,8 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b);
 hipError_t lds_opt_in(const void *fn, size_t bytes, int lds_max);
 hipError_t launch_thomas_factors(nspnp_state *s);
 hipError_t prime_x_transform_lds(int lds_max);
-hipError_t launch_dt(nspnp_state *s);
+hipError_t launch_dt(nspnp_state *s, int *nparts);  // partial reductions, for launch_step_coef
+hipError_t launch_step_coef(nspnp_state *s, int nparts);  // dt, clock and the coefficients of a step
 hipError_t launch_init_fields(nspnp_state *s);
 hipError_t launch_plane_sums(nspnp_state *s, int what, double *dev_out);
 hipError_t launch_energy_sums(nspnp_state *s, double *dev_out);  // 4 doubles per row

@@ -159,55 +159,6 @@ __global__ void __launch_bounds__(kRedThreads) k_dt_partial(Dims d, Tables tb, c
     if (threadIdx.x < kDtParts) part[kDtParts * blockIdx.x + threadIdx.x] = s[threadIdx.x][0];
 }
 
-// Combines the partials: the step dt (adaptive runs only, Sec. II time
-// stepping with the limits of include/nspnp.h) and the sticky health word.
-__global__ void __launch_bounds__(kRedThreads) k_dt_final(int nparts, const double *part, const Phys *phys,
-                                                          Dims d, double *clock, size_t ms) {
-    __shared__ double s[kDtParts][kRedThreads];
-    part = member_ptr(part, ms);
-    clock = member_ptr(clock, ms);
-    const Phys ph = *member_ptr(phys, ms);
-    double acc[kDtParts] = {0.0, 0.0, 1e300, 0.0, 0.0};
-    for (int b = threadIdx.x; b < nparts; b += blockDim.x) {
-        acc[0] = fmax(acc[0], part[kDtParts * b + 0]);
-        acc[1] = fmax(acc[1], part[kDtParts * b + 1]);
-        acc[2] = fmin(acc[2], part[kDtParts * b + 2]);
-        acc[3] = fmax(acc[3], part[kDtParts * b + 3]);
-        acc[4] = fmax(acc[4], part[kDtParts * b + 4]);
-    }
-#pragma unroll
-    for (int q = 0; q < kDtParts; ++q) s[q][threadIdx.x] = acc[q];
-    __syncthreads();
-    for (int o = kRedThreads / 2; o > 0; o >>= 1) {
-        if (threadIdx.x < o) {
-            s[0][threadIdx.x] = fmax(s[0][threadIdx.x], s[0][threadIdx.x + o]);
-            s[1][threadIdx.x] = fmax(s[1][threadIdx.x], s[1][threadIdx.x + o]);
-            s[2][threadIdx.x] = fmin(s[2][threadIdx.x], s[2][threadIdx.x + o]);
-            s[3][threadIdx.x] = fmax(s[3][threadIdx.x], s[3][threadIdx.x + o]);
-            s[4][threadIdx.x] = fmax(s[4][threadIdx.x], s[4][threadIdx.x + o]);
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        const double re = ph.re, rs = 1.0 / ph.kd;
-        double dt = 1e30;
-        if (s[0][0] > 0.0) dt = ph.cfl / s[0][0];
-        if (s[1][0] > 0.0) dt = fmin(dt, 2.0 * ph.debye * ph.debye * rs / s[1][0]);
-        const double nu_min = re < rs ? re : rs;
-        if (ph.implicit_xz == 0.0)  // explicit x/z diffusion limit
-            dt = fmin(dt, nu_min / (4.0 / (d.dx * d.dx) + 4.0 / (d.dz * d.dz)));
-        int bits = (int)clock[2];
-        if (s[3][0] != 0.0) bits |= kHealthNonFinite;
-        if (s[2][0] < 0.0) bits |= kHealthNegative;
-        if (ph.adaptive != 0.0) {
-            if (!(dt > 0.0) || !__builtin_isfinite(dt)) bits |= kHealthNonFinite;
-            else clock[1] = dt;
-        }
-        clock[2] = (double)bits;
-        clock[3] = s[4][0];
-    }
-}
-
 // ---- per-plane sums for diagnostics ----
 // out[j * kPlaneQ + q], q as in PlaneQ: sums of u, c+, c-; total ion fluxes
 // at node j; kinetic energy of row j; max |div u|; min c+, min c-,
@@ -539,8 +490,7 @@ hipError_t launch_shift_conc(nspnp_state *s, double mp, double mm) {
     return hipGetLastError();
 }
 
-hipError_t launch_dt(nspnp_state *s) {
-    ProfScope prof_(s, K_DT);
+hipError_t launch_dt(nspnp_state *s, int *nparts) {
     // columns in chunks of one block; rows split into slabs so that the
     // partials fit kDtMaxBlocks per member and the members together have about
     // 4096 blocks (a slab reads one row of v and phi beyond its own and loads
@@ -563,8 +513,7 @@ hipError_t launch_dt(nspnp_state *s) {
             s->d, s->tb, s->d_phys, (const float *)s->f[0], (const float *)s->f[1], (const float *)s->f[2],
             (const float *)s->f[3], (const float *)s->f[4], (const float *)s->f[5], s->red, chunks, slab_rows,
             s->mstride);
-    k_dt_final<<<dim3(1, 1, (unsigned)s->nmem), kRedThreads, 0, s->stream>>>((int)nb, s->red, s->d_phys, s->d,
-                                                                             s->clock, s->mstride);
+    *nparts = (int)nb;
     return hipGetLastError();
 }
 

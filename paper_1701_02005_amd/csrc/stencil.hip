@@ -500,12 +500,66 @@ __device__ __forceinline__ void cn_row(const double *lo_tab, const double *up_ta
 // 3 cn_rows(M) coefficients with coalesced writes, zeros past the last row
 // and, for the nodes, in row 0 (the wall: no unknown).  Launched once per
 // Runge-Kutta step (dt changes only at the first stage).
+// It first combines the partials of the step's reductions (nparts of them, 0: dt
+// stays): the step dt (adaptive runs only, Sec. II time stepping with the limits
+// of include/nspnp.h) and the sticky health word.  Every block forms them, the
+// first of a member stores them, without a launch of its own (32 x 33 x 32: 6.3
+// us against 3.2 and 4.3; 128 x 129 x 128 14.9 against 4.8 and 11.5).
+__device__ __forceinline__ double dt_close(int nparts, const double *part, const Phys &ph, const Dims &d, double *clock,
+                                           bool store, double (*s)[4]) {
+    double acc[kDtParts] = {0.0, 0.0, 1e300, 0.0, 0.0};
+    for (int b = threadIdx.x; b < nparts; b += blockDim.x) {
+        acc[0] = fmax(acc[0], part[kDtParts * b + 0]);
+        acc[1] = fmax(acc[1], part[kDtParts * b + 1]);
+        acc[2] = fmin(acc[2], part[kDtParts * b + 2]);
+        acc[3] = fmax(acc[3], part[kDtParts * b + 3]);
+        acc[4] = fmax(acc[4], part[kDtParts * b + 4]);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int q = 0; q < kDtParts; ++q) {
+            const double v = __shfl_xor(acc[q], o, 64);
+            acc[q] = q == 2 ? fmin(acc[q], v) : fmax(acc[q], v);
+        }
+    if ((threadIdx.x & 63) == 0)
+        for (int q = 0; q < kDtParts; ++q) s[q][threadIdx.x >> 6] = acc[q];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kDtParts; ++q) {
+        acc[q] = s[q][0];
+        for (int w = 1; w < 4; ++w) acc[q] = q == 2 ? fmin(acc[q], s[q][w]) : fmax(acc[q], s[q][w]);
+    }
+    const double re = ph.re, rs = 1.0 / ph.kd;
+    double dt = 1e30;
+    if (acc[0] > 0.0) dt = ph.cfl / acc[0];
+    if (acc[1] > 0.0) dt = fmin(dt, 2.0 * ph.debye * ph.debye * rs / acc[1]);
+    const double nu_min = re < rs ? re : rs;
+    if (ph.implicit_xz == 0.0)  // explicit x/z diffusion limit
+        dt = fmin(dt, nu_min / (4.0 / (d.dx * d.dx) + 4.0 / (d.dz * d.dz)));
+    const bool adaptive = ph.adaptive != 0.0, good = dt > 0.0 && __builtin_isfinite(dt);
+    if (store && threadIdx.x == 0) {
+        int bits = (int)clock[2];
+        if (acc[3] != 0.0) bits |= kHealthNonFinite;
+        if (acc[2] < 0.0) bits |= kHealthNegative;
+        if (adaptive) {
+            if (!good) bits |= kHealthNonFinite;
+            else clock[1] = dt;
+        }
+        clock[2] = (double)bits;
+        clock[3] = acc[4];
+    }
+    // (clock[1] is not stored to in the cases in which it is read)
+    return adaptive && good ? dt : clock[1];
+}
+
 struct CnStages {
     double alp[3];
 };
 
-__global__ void __launch_bounds__(256) k_cn_coef(Dims d, Tables tb, const Phys *phys, const double *clock,
-                                                 double *coef, CnStages stages, size_t ms) {
+__global__ void __launch_bounds__(256) k_cn_coef(Dims d, Tables tb, const Phys *phys, double *clock, double *coef,
+                                                 CnStages stages, int nparts, const double *part, size_t ms) {
+    __shared__ double s_dt[kDtParts][4];
     __shared__ double s_a[kMaxRows + kCnPad], s_b[kMaxRows + kCnPad], s_c[kMaxRows + kCnPad];
     phys = member_ptr(phys, ms);
     clock = member_ptr(clock, ms);
@@ -513,7 +567,9 @@ __global__ void __launch_bounds__(256) k_cn_coef(Dims d, Tables tb, const Phys *
     const int stage = blockIdx.y, sys = blockIdx.x;
     coef = member_ptr(coef, ms) + (size_t)stage * cn_stage_stride(M) + (size_t)sys * 3 * Mp;
     const double nu = (sys == 2) ? phys->kd : phys->ire;
-    const double beta = 0.5 * stages.alp[stage] * clock[1] * nu;
+    const double dt =
+        nparts ? dt_close(nparts, member_ptr(part, ms), *phys, d, clock, stage == 0 && sys == 0, s_dt) : clock[1];
+    const double beta = 0.5 * stages.alp[stage] * dt * nu;
     const double *lo_tab = sys == 1 ? tb.lyn_lo : tb.lyc_lo, *up_tab = sys == 1 ? tb.lyn_up : tb.lyc_up;
     const int j0 = (sys == 1) ? 1 : 0;
     for (int j = threadIdx.x; j < Mp; j += blockDim.x) {
@@ -1340,12 +1396,11 @@ static hipError_t explicit_launch(nspnp_state *s, const ExplicitArgs &a, int thr
 
 // Crank-Nicolson recurrence coefficients of the three stages: computed on
 // the device once per Runge-Kutta step, after the step's dt.
-static hipError_t launch_cn_coef(nspnp_state *s, const Stage &st) {
-    if (st.k != 0 && s->cn_fresh) return hipSuccess;
+hipError_t launch_step_coef(nspnp_state *s, int nparts) {
     CnStages cs;
     for (int q = 0; q < 3; ++q) cs.alp[q] = kRkAlp[q];
     k_cn_coef<<<dim3(3, 3, (unsigned)s->nmem), 256, 0, s->stream>>>(s->d, s->tb, s->d_phys, s->clock, s->cn_coef, cs,
-                                                                   s->mstride);
+                                                                   nparts, s->red, s->mstride);
     if (s->cfg.implicit_xz)
         k_cyc_coef<<<dim3(4, 3, (unsigned)s->nmem), 64, 0, s->stream>>>(s->d, s->d_phys, s->clock, s->cyc, cs,
                                                                         s->mstride);
@@ -1678,8 +1733,9 @@ static hipError_t launch_cn_y(nspnp_state *s, const Stage &st, bool out_r) {
 
 hipError_t launch_cn_solve(nspnp_state *s, const Stage &st) {
     ProfScope prof_(s, K_CN);
-    hipError_t e = launch_cn_coef(s, st);
-    if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
+    // (a step's first stage has made them; after a restart within a step, or a new dt)
+    if (!s->cn_fresh && (e = launch_step_coef(s, 0)) != hipSuccess) return e;
     if (!s->cfg.implicit_xz) return launch_cn_y(s, st, false);
     // three-direction factorisation: x-lines into r, y (this solve) into r, then z-lines with q += solution
     if ((e = launch_cyc(s, st, false)) != hipSuccess) return e;

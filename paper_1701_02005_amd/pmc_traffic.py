@@ -30,7 +30,7 @@ CSRC = "paper_1701_02005_amd/csrc"
 
 # profiler class -> (HIP kernels launched per class launch, source file)
 CLASSES = {
-    "dt": (("k_dt_partial", "k_dt_final"), "reduce.hip"),
+    "dt": (("k_dt_partial",), "reduce.hip"),
     "explicit_rhs": (("k_explicit",), "stencil.hip"),
     "cn_tridiag": (("k_cn_coef", "k_cn_scan"), "stencil.hip"),
     "fft_x_r2c": (("k_fft_x_r2c",), "poisson.hip"),
