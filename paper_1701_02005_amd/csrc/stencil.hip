@@ -116,7 +116,8 @@ struct HaloRegs {
 // kLim (the mixed form): the limited advective flux of migration_face 2 is
 // formed here instead of in a pass of its own, which reads u, v, w, c+- and
 // the ions' H and r again and rewrites those: 256 x 193 x 256 277 us against 222
-// and 157, bound by arithmetic (12 divisions a species and cell).  The values two
+// and 157 (carrying the y faces' values from row to row, a sixth of its
+// arithmetic less, changes nothing).  The values two
 // columns away come from the caches (the row's own tile loads them), those two
 // rows up from memory one row early.  FP64 keeps the pass (registers).
 template <typename T, int kHalo, int kWaves, int kMode, int kTx = 0, int kTz = 0, bool kLim = false>
