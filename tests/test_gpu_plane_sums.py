@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("face", [0, 2])
-@pytest.mark.parametrize("nx,ny,nz", [(4, 5, 6), (16, 17, 32), (36, 9, 32), (54, 40, 96), (12, 513, 6)])
+@pytest.mark.parametrize("nx,ny,nz", [(4, 5, 6), (16, 17, 32), (36, 9, 32), (54, 40, 96), (12, 513, 6), (288, 9, 12), (1024, 6, 4)])
 def test_against_oracle(oracle_mod, nx, ny, nz, face):
     import paper_1701_02005_amd as P
     cfg = dataclasses.replace(P.configs.couette_small(), nx=nx, ny=ny, nz=nz, dt=0.0, cfl=0.5, u_noise=0.05, seed=8,
