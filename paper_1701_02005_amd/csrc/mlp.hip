@@ -786,7 +786,17 @@ int nspnp_mlp_get_params(nspnp_mlp *h, float *host_params, float *host_grads) {
 
 int nspnp_mlp_forward(nspnp_mlp *h, const float *dev_x, int32_t rows, float *dev_y) {
     if (!h || !dev_x || !dev_y || rows < 1 || rows > h->Bmax) return fail_code(NSPNP_ERR_INVALID, "mlp_forward: bad rows");
-    if (h->fused) return run_net(h, dev_x, nullptr, rows, dev_y);
+    if (h->fused) {
+        // blocks write their rows of dev_y while others still read theirs of
+        // dev_x: an output that overlaps the input goes through the workspace
+        const uintptr_t x0 = (uintptr_t)dev_x, y0 = (uintptr_t)dev_y;
+        const size_t nx = (size_t)rows * h->sizes[0] * 4, ny = (size_t)rows * h->sizes[h->nl] * 4;
+        const bool over = x0 < y0 + ny && y0 < x0 + nx;
+        const int rn = run_net(h, dev_x, nullptr, rows, over ? h->yhat : dev_y);
+        if (rn || !over) return rn;
+        M_TRY(hipMemcpyAsync(dev_y, h->yhat, ny, hipMemcpyDeviceToDevice, h->stream));
+        return NSPNP_OK;
+    }
     int rc = pack_input(h, dev_x, rows);
     if (rc || (rc = forward(h))) return rc;
     const int n = rows * h->sizes[h->nl];
