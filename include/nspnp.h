@@ -319,7 +319,8 @@ NSPNP_API int nspnp_profile_read(nspnp_state *s, int32_t *count, const char **na
  * An ensemble advances n independent runs together, each with its own
  * configuration (Re, Sc, beta, Debye length, voltage, walls, seed, noise, dt
  * rule).  Runs with the same grid (nx, ny, nz, lx, lz, stretch, precision,
- * fixed-or-adaptive dt) share every kernel launch; each run keeps its own
+ * fixed-or-adaptive dt), the same implicit_xz and migration_face 2 in all or
+ * none of them share every kernel launch; each run keeps its own
  * adaptive dt and clock, and gives the same result as a single run of the
  * same configuration.  The caller owns one device workspace of
  * nspnp_ensemble_workspace_bytes(); members are numbered as in cfgs.

@@ -1,7 +1,8 @@
 // ensemble.hip -- many independent NS-PNP runs advanced together.
 //
 // Members with the same grid (nx, ny, nz, lx, lz, stretch, precision, dt
-// mode) form a size class.  A class is one batched handle: member m's
+// mode), the same implicit directions and the advective flux of the ions
+// limited in all or none of them form a size class.  A class is one batched handle: member m's
 // workspace has the single-run layout and starts m * stride bytes after
 // member 0, and every kernel takes the member from blockIdx.z, so one launch
 // covers all members of a class (per-member Re, Sc, beta, Debye length,
@@ -41,7 +42,8 @@ namespace {
 
 bool same_class(const nspnp_config &a, const nspnp_config &b) {
     return a.nx == b.nx && a.ny == b.ny && a.nz == b.nz && a.lx == b.lx && a.lz == b.lz && a.stretch == b.stretch &&
-           a.precision == b.precision && ((a.dt > 0.0) == (b.dt > 0.0)) && a.implicit_xz == b.implicit_xz;
+           a.precision == b.precision && ((a.dt > 0.0) == (b.dt > 0.0)) && a.implicit_xz == b.implicit_xz &&
+           (a.migration_face == 2) == (b.migration_face == 2);  // (a class launches the limiter for all or none)
 }
 
 // classes in order of first appearance; returns per-member class ids
