@@ -148,6 +148,14 @@ __device__ __forceinline__ double uniform_load(const double *p, int i) {
     return ((cdouble *)p)[__builtin_amdgcn_readfirstlane(i)];
 }
 
+// Orders a wave's LDS accesses for exchanges within the wave (they execute in
+// order; this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Accesses to data that a kernel touches once (no neighbouring thread or
 // block reads the same element) and that is not handed straight to the next
 // kernel through the last-level cache: the non-temporal hint streams these

@@ -587,13 +587,6 @@ struct WaveFft {
             }
         }
     }
-    // orders the wave's LDS accesses (they execute in order; this keeps the
-    // compiler from moving them)
-    static __device__ __forceinline__ void wave_sync() {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
 };
 
 // The right-hand side of lines (j, k) and (j, k + 1) at x = lane + 64 r, r in
@@ -718,10 +711,10 @@ __global__ void __launch_bounds__(256) k_lines_r2c(Dims d, Tables tb, PoissonBat
             for (int h = 0; h < F::kPer; ++h)
 #pragma unroll
                 for (int t = 0; t < B; ++t) zw[h * F::kSlots + lane + 64 * t] = v[h * B + t];
-            F::wave_sync();
+            wave_sync();
 #pragma unroll
             for (int r = 0; r < F::R; ++r) v[r] = z[l + F::kLanes * r];
-            F::wave_sync();
+            wave_sync();
         }
         F::run(v, z, tb.twx, l, false);
 #pragma unroll
@@ -784,7 +777,7 @@ __global__ void __launch_bounds__(256) k_lines_c2r(Dims d, Tables tb, PoissonBat
         }
         v[r] = make_double2(A.x - B.y, A.y + B.x);  // Z = A + i B
     }
-    F::wave_sync();
+    wave_sync();
     F::run(v, z, tb.twx, l, true);
     if (line0 + 2 * pair >= nlines) return;
     const int64_t la = (int64_t)(line0 + 2 * pair) * N;
@@ -1525,7 +1518,7 @@ __global__ void __launch_bounds__(256, 2) k_mode_columns(Dims d, Tables tb, Pois
         for (int t = 0; t < L; ++t)
             if (t < s) q[t] *= c[t];
     }
-    WaveFft<256>::wave_sync();  // (the pivots are read again, not kept)
+    wave_sync();  // (the pivots are read again, not kept)
     {
         const double in = other_half<false>(y[L - 1], 0.0);
 #pragma unroll
@@ -1572,7 +1565,7 @@ __global__ void __launch_bounds__(256, 2) k_mode_columns(Dims d, Tables tb, Pois
         for (int t = 0; t < L; ++t)
             if (t + s >= L) q[t] *= c[t];
     }
-    WaveFft<256>::wave_sync();
+    wave_sync();
     {
         const double in = other_half<true>(y[0], 0.0);
 #pragma unroll
@@ -1585,7 +1578,7 @@ __global__ void __launch_bounds__(256, 2) k_mode_columns(Dims d, Tables tb, Pois
 #pragma unroll
             for (int t = 0; t < L; ++t) v[lane & 1][r0 + t] = x[t];
         }
-        WaveFft<256>::wave_sync();
+        wave_sync();
         const bool in = lane < M;
         double vol = in ? tb.dn[lane] : 0.0, sx = in ? v[0][lane] * vol : 0.0, sy = in ? v[1][lane] * vol : 0.0;
 #pragma unroll

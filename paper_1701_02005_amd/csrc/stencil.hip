@@ -1075,16 +1075,28 @@ struct CycWave {
 };
 
 // x-lines, the solution in place of r: contiguous, so each wave takes its
-// lines straight from memory into its lanes, kCycLines at a time with all of
-// their loads in flight, without LDS tiles or barriers.  Bound by the scans'
-// moves between lanes: 128 x 129 x 128 FP64 45 us (3.7 TB/s); through tiles in
-// LDS, as the z-lines, 57 us (two passes more through LDS, and an integer
-// division per element).
+// lines straight from memory, cyc_lines(R) at a time, the next ones' loads in
+// flight while these are solved, without block barriers.  Lines whose lanes
+// hold more than 16 bytes apiece (R > 2 in FP64, R > 3 in FP32) are loaded and
+// stored along the line, whole runs of memory, and turned into the lanes'
+// contiguous points in the wave's own piece of LDS: a lane's points taken from
+// memory one by one are a part of each 128-byte line R times over.  The three
+// solves of the implicit form together (k_cyc_x, the wall-normal solve,
+// k_cyc_z), points one by one, turned, and through tiles of 16 lines in LDS:
+//   128 x 129 x 128 FP64 (R 2)       149 / -   / 162 us (this kernel 45, 57 in tiles)
+//   192 x 129 x 128 FP64 (R 3)       248 / 202 / 221
+//   256 x 129 x 128 FP64, mixed      385, 225 / 252, 171 / 284, 248
+//   1024 x 129 x 128 FP64, mixed     5705, 2101 / 956, 657 / 1651, 1604
+//   144 x 129 x 128 mixed (R 3)      114 / 125 / 164
+// Bound by the scans' moves between lanes on short lines (128 points 3.7 TB/s).
 constexpr int cyc_lines(int R) { return R <= 2 ? 4 : (R <= 4 ? 2 : 1); }
 
 template <typename T, int R>
 __global__ void __launch_bounds__(256) k_cyc_x(CycArgs a) {
     constexpr int kB = cyc_lines(R);
+    constexpr bool kTurn = R > (sizeof(T) == 8 ? 2 : 3);
+    // (R + 1 slots for each lane's R points: reads along t are free of bank conflicts)
+    __shared__ double s_z[kTurn ? 4 * kB * 64 * (R + 1) : 1];
     const int f = (int)blockIdx.y, N = a.d.nx;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), nlines = a.d.M * a.d.nz;
     T *rr = (T *)member_ptr_at(a.r[f], a.ms, blockIdx.z);
@@ -1093,6 +1105,10 @@ __global__ void __launch_bounds__(256) k_cyc_x(CycArgs a) {
     const int js = s.lane * R;
     const int l0 = ((int)blockIdx.x * 4 + wave) * a.lines, l1 = l0 + a.lines < nlines ? l0 + a.lines : nlines;
     if (l0 >= l1) return;
+    // point of the line that this lane moves as its t-th
+    auto pt = [&](int t) { return kTurn ? s.lane + 64 * t : js + t; };
+    double *z = s_z + (kTurn ? wave * kB * 64 * (R + 1) : 0);
+    auto slot = [](int b, int i) { return b * 64 * (R + 1) + i + i / R; };
     T v[kB][R];
     // points past the line and lines past the last one read what exists
     auto load = [&](int l) {
@@ -1100,26 +1116,50 @@ __global__ void __launch_bounds__(256) k_cyc_x(CycArgs a) {
         for (int b = 0; b < kB; ++b) {
             const T *p = rr + (int64_t)(l + b < l1 ? l + b : l1 - 1) * N;
 #pragma unroll
-            for (int t = 0; t < R; ++t) v[b][t] = ld_once(p + (js + t < N ? js + t : 0));
+            for (int t = 0; t < R; ++t) v[b][t] = ld_once(p + (pt(t) < N ? pt(t) : 0));
         }
     };
     load(l0);
     s.products();
     for (int l = l0; l < l1; l += kB) {
         double x[kB][R];
+        if constexpr (kTurn) {
 #pragma unroll
-        for (int b = 0; b < kB; ++b)
+            for (int b = 0; b < kB; ++b)
 #pragma unroll
-            for (int t = 0; t < R; ++t) x[b][t] = js + t < N ? (double)v[b][t] : 0.0;
+                for (int t = 0; t < R; ++t) z[slot(b, pt(t))] = pt(t) < N ? (double)v[b][t] : 0.0;
+            wave_sync();
+#pragma unroll
+            for (int b = 0; b < kB; ++b)
+#pragma unroll
+                for (int t = 0; t < R; ++t) x[b][t] = z[slot(b, js) + t];
+        } else {
+#pragma unroll
+            for (int b = 0; b < kB; ++b)
+#pragma unroll
+                for (int t = 0; t < R; ++t) x[b][t] = js + t < N ? (double)v[b][t] : 0.0;
+        }
         if (l + kB < l1) load(l + kB);  // lands while these are solved
 #pragma unroll
         for (int b = 0; b < kB; ++b) s.solve(x[b]);
+        if constexpr (kTurn) {
+#pragma unroll
+            for (int b = 0; b < kB; ++b)
+#pragma unroll
+                for (int t = 0; t < R; ++t) z[slot(b, js) + t] = x[b][t];
+            wave_sync();
+#pragma unroll
+            for (int b = 0; b < kB; ++b)
+#pragma unroll
+                for (int t = 0; t < R; ++t) x[b][t] = z[slot(b, pt(t))];
+            wave_sync();  // (the slots are written again for the next lines)
+        }
 #pragma unroll
         for (int b = 0; b < kB; ++b) {
             T *p = rr + (int64_t)(l + b) * N;
 #pragma unroll
             for (int t = 0; t < R; ++t)
-                if (l + b < l1 && js + t < N) st_once(p + js + t, (T)x[b][t]);
+                if (l + b < l1 && pt(t) < N) st_once(p + pt(t), (T)x[b][t]);
         }
     }
 }
