@@ -50,21 +50,24 @@ struct GemmArgs {
     float *C;            // OUTPUT: [M x N] FP32 output; DW: [M x N] gradient
 };
 
-// One wave per 16 x 16 output tile; 4 waves per block.
+// One wave per 16 x 16 output tile; 4 waves per block.  kTiled: Bt in tile
+// order (tile_at), and the tiles that share columns of it on one XCD, so that
+// each XCD's L2 takes its part of the weights.
+template <bool kTiled>
 __global__ void __launch_bounds__(256) k_gemm_nt(GemmArgs g) {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    const int tiles_n = g.N / 16;
-    const int tile = blockIdx.x * 4 + wave;
-    if (tile >= (g.M / 16) * tiles_n) return;
-    const int m0 = (tile / tiles_n) * 16, n0 = (tile % tiles_n) * 16;
+    const int tiles_m = g.M / 16, tiles_n = g.N / 16;
+    const int tile = (int)(kTiled ? xcd_tile(blockIdx.x, gridDim.x) : blockIdx.x) * 4 + wave;
+    if (tile >= tiles_m * tiles_n) return;
+    const int m0 = (kTiled ? tile % tiles_m : tile / tiles_n) * 16, n0 = (kTiled ? tile / tiles_m : tile % tiles_n) * 16;
     const int r = lane & 15, kc = (lane >> 4) * 8;
     const bf16 *pa = g.A + (size_t)(m0 + r) * g.K + kc;
-    const bf16 *pb = g.Bt + (size_t)(n0 + r) * g.K + kc;
+    const bf16 *pb = kTiled ? g.Bt + (size_t)n0 * g.K + lane * 8 : g.Bt + (size_t)(n0 + r) * g.K + kc;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     for (int k0 = 0; k0 < g.K; k0 += 32) {
         const bf16x8 a = *(const bf16x8 *)(pa + k0);
-        const bf16x8 b = *(const bf16x8 *)(pb + k0);
+        const bf16x8 b = *(const bf16x8 *)(pb + (kTiled ? 16 * k0 : k0));
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
     }
     // lane holds rows m0 + 4 (lane / 16) + q, column n0 + lane % 16
@@ -503,8 +506,10 @@ struct nspnp_mlp {
 namespace {
 
 // Two row-major LDS buffers of 16 rows (8 values of padding a row spread the
-// banks), for layers of up to 768: a forward pass of 64 rows through 3 layers
-// of 768 34 us, layer by layer 37; 5 of 992 (which fit 64 KB too) 95 and 58.
+// banks), for layers of up to 768: training steps through 8 layers of 768 take
+// 0.85 (1 row), 0.64 (64) and 0.13 (1024) of their time layer by layer.  Wider
+// networks run layer by layer: forward passes through 5 layers of 992 (which
+// fit 64 KB too) 95 and 58 us.
 size_t net_lds(int widest) { return 2 * 16 * (size_t)(widest + 8) * sizeof(bf16); }
 bool net_fits(int widest) { return widest <= 768; }
 
@@ -567,26 +572,28 @@ int check_mlp(int nl, const int *sizes, int batch) {
         if (e_ != hipSuccess) return fail_code(NSPNP_ERR_HIP, std::string(#expr) + ": " + hipGetErrorString(e_)); \
     } while (0)
 
-hipError_t gemm(nspnp_mlp *h, const GemmArgs &g) {
+hipError_t gemm(nspnp_mlp *h, const GemmArgs &g, bool tiled = false) {
     const int tiles = (g.M / 16) * (g.N / 16);
-    k_gemm_nt<<<(tiles + 3) / 4, 256, 0, h->stream>>>(g);
+    if (tiled) k_gemm_nt<true><<<(tiles + 3) / 4, 256, 0, h->stream>>>(g);
+    else k_gemm_nt<false><<<(tiles + 3) / 4, 256, 0, h->stream>>>(g);
     return hipGetLastError();
 }
 
-int pack_input(nspnp_mlp *h, const float *x, int rows) {
-    const int n = h->Bp * h->padded[0];
-    k_pack_input<<<(n + 255) / 256, 256, 0, h->stream>>>(x, rows, h->sizes[0], h->Bp, h->padded[0], h->act[0],
+// Bp: batch rows packed and run, a multiple of 32
+int pack_input(nspnp_mlp *h, const float *x, int rows, int Bp) {
+    const int n = Bp * h->padded[0];
+    k_pack_input<<<(n + 255) / 256, 256, 0, h->stream>>>(x, rows, h->sizes[0], Bp, h->padded[0], h->act[0],
                                                          h->actt[0]);
     M_TRY(hipGetLastError());
     return NSPNP_OK;
 }
 
-int forward(nspnp_mlp *h) {
+int forward(nspnp_mlp *h, int Bp) {
     for (int l = 0; l < h->nl; ++l) {
         GemmArgs g{};
         g.A = h->act[l];
         g.Bt = h->wtb[l];
-        g.M = h->Bp;
+        g.M = Bp;
         g.N = h->padded[l + 1];
         g.K = h->padded[l];
         g.bias = h->w[l] + (size_t)h->padded[l] * h->padded[l + 1];
@@ -599,7 +606,7 @@ int forward(nspnp_mlp *h) {
             g.epi = EPI_OUTPUT;
             g.C = h->yhat;
         }
-        M_TRY(gemm(h, g));
+        M_TRY(gemm(h, g, h->fused));
     }
     return NSPNP_OK;
 }
@@ -639,6 +646,27 @@ int backward(nspnp_mlp *h, const float *y, int rows) {
         }
     }
     return NSPNP_OK;
+}
+
+// Forward passes of up to 384 rows go layer by layer, from the weights in tile
+// order, where k_net's 16 waves wait longer for weights than its launches
+// save: a wave loads a layer's weights in ceil(N / 256) tiles of ceil(K / 256)
+// pieces, one after the other, and nearly all layers have 3 x 3 of them; or the
+// weights (BF16) don't fit an XCD's 4 MB of L2, each of which reads them all.
+// 64 rows: 1 layer of 768 12 us (k_net 18), 3 of 704 29 (34), 5 of 640 44 (62),
+// 8 of 768 75 (126), 8 of 512 58 (59); k_net stays ahead on 3 layers of 512 (21
+// against 24), 8-768-768-8 (17, 23) and 5 layers of 8-640-..-8 (29, 38).  More
+// rows give k_net more blocks: 4 layers of 576, 256 rows 36 (35), 384 rows 37
+// (35), 512 rows 43 (35); 8 of 640, 384 rows 78 (98), 512 rows 85 (97).
+constexpr int kLayerRows = 384;
+bool forward_by_layers(const nspnp_mlp *h, int rows) {
+    int64_t weights = 0;
+    int pieces = 0;
+    for (int l = 0; l < h->nl; ++l) {
+        weights += (int64_t)h->padded[l] * h->padded[l + 1];
+        pieces += ((h->padded[l] + 255) / 256) * ((h->padded[l + 1] + 255) / 256);
+    }
+    return rows <= kLayerRows && (2 * weights > 3800000 || pieces > 7 * h->nl);
 }
 
 // k_net on the handle's weights: forward into out, or (out NULL) forward and
@@ -786,7 +814,7 @@ int nspnp_mlp_get_params(nspnp_mlp *h, float *host_params, float *host_grads) {
 
 int nspnp_mlp_forward(nspnp_mlp *h, const float *dev_x, int32_t rows, float *dev_y) {
     if (!h || !dev_x || !dev_y || rows < 1 || rows > h->Bmax) return fail_code(NSPNP_ERR_INVALID, "mlp_forward: bad rows");
-    if (h->fused) {
+    if (h->fused && !forward_by_layers(h, rows)) {
         // blocks write their rows of dev_y while others still read theirs of
         // dev_x: an output that overlaps the input goes through the workspace
         const uintptr_t x0 = (uintptr_t)dev_x, y0 = (uintptr_t)dev_y;
@@ -797,8 +825,9 @@ int nspnp_mlp_forward(nspnp_mlp *h, const float *dev_x, int32_t rows, float *dev
         M_TRY(hipMemcpyAsync(dev_y, h->yhat, ny, hipMemcpyDeviceToDevice, h->stream));
         return NSPNP_OK;
     }
-    int rc = pack_input(h, dev_x, rows);
-    if (rc || (rc = forward(h))) return rc;
+    const int Bp = h->fused ? pad32(rows) : h->Bp;
+    int rc = pack_input(h, dev_x, rows, Bp);
+    if (rc || (rc = forward(h, Bp))) return rc;
     const int n = rows * h->sizes[h->nl];
     k_unpack_output<<<(n + 255) / 256, 256, 0, h->stream>>>(h->yhat, rows, h->sizes[h->nl], h->padded[h->nl], dev_y);
     M_TRY(hipGetLastError());
@@ -809,7 +838,7 @@ int nspnp_mlp_gradients(nspnp_mlp *h, const float *dev_x, const float *dev_y, in
     if (!h || !dev_x || !dev_y || rows < 1 || rows > h->Bmax) return fail_code(NSPNP_ERR_INVALID, "mlp_gradients: bad rows");
     int rc;
     if (h->fused) rc = run_net(h, dev_x, dev_y, rows, nullptr), rc = rc ? rc : run_update(h, rows, nullptr, nullptr);
-    else rc = pack_input(h, dev_x, rows), rc = rc ? rc : forward(h), rc = rc ? rc : backward(h, dev_y, rows);
+    else rc = pack_input(h, dev_x, rows, h->Bp), rc = rc ? rc : forward(h, h->Bp), rc = rc ? rc : backward(h, dev_y, rows);
     if (rc) return rc;
     if (loss) {
         M_TRY(hipMemcpyAsync(loss, h->loss, 4, hipMemcpyDeviceToHost, h->stream));
@@ -829,7 +858,7 @@ int nspnp_mlp_train_step(nspnp_mlp *h, const float *dev_x, const float *dev_y, i
         h->t += 1;
         return run_update(h, rows, &step, dev_loss);
     }
-    if ((rc = pack_input(h, dev_x, rows)) || (rc = forward(h)) || (rc = backward(h, dev_y, rows))) return rc;
+    if ((rc = pack_input(h, dev_x, rows, h->Bp)) || (rc = forward(h, h->Bp)) || (rc = backward(h, dev_y, rows))) return rc;
     h->t += 1;
     AdamArgs a{};
     a.s = step;
