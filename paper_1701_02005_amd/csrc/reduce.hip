@@ -311,7 +311,8 @@ __global__ void __launch_bounds__(kRedThreads) k_plane(Dims d, const Phys *phys,
 }
 
 // A row's block sums combined in order: one thread per (row, quantity).  The
-// rows and quantities that `what` does not form become 0.
+// rows and quantities that `what` does not form become 0.  (One block per row:
+// its sums are the result, and this is not launched.)
 __global__ void __launch_bounds__(kRedThreads) k_plane_close(int M, int what, const double *part, double *out,
                                                              int chunks, size_t ms) {
     part = member_ptr(part, ms);
@@ -354,7 +355,7 @@ __global__ void __launch_bounds__(kRedThreads) k_plane_close(int M, int what, co
 template <typename T>
 __global__ void __launch_bounds__(kRedThreads) k_energy(Dims d, const Phys *phys, Tables tb, const T *u, const T *v,
                                                         const T *w, const T *cp, const T *cm, const T *phi,
-                                                        double *part, int chunks, size_t ms) {
+                                                        double *part, int chunks, int stride, size_t ms) {
     __shared__ double s_wave[kRedThreads / 64];
     u = member_ptr(u, ms); v = member_ptr(v, ms); w = member_ptr(w, ms);
     cp = member_ptr(cp, ms); cm = member_ptr(cm, ms); phi = member_ptr(phi, ms); part = member_ptr(part, ms);
@@ -422,7 +423,7 @@ __global__ void __launch_bounds__(kRedThreads) k_energy(Dims d, const Phys *phys
     const double r[kEnergyQ] = {block_reduce<OP_SUM>(dis, s_wave), block_reduce<OP_SUM>(fwk, s_wave),
                                 block_reduce<OP_SUM>(wall, s_wave)};
     if (threadIdx.x == 0)
-        for (int q = 0; q < kEnergyQ; ++q) part[((size_t)j * chunks + chunk) * kEnergyQ + q] = r[q];
+        for (int q = 0; q < kEnergyQ; ++q) part[((size_t)j * chunks + chunk) * stride + q] = r[q];
 }
 
 __global__ void __launch_bounds__(kRedThreads) k_energy_close(int M, const double *part, double *out, int chunks,
@@ -541,12 +542,13 @@ static int plane_chunks(const nspnp_state *s) {
 }
 
 // per-plane sums of every member (results in each member's dev_out copy, the
-// block sums behind them in the reduction scratch)
+// block sums behind them in the reduction scratch; those that `what` does not
+// form are not defined)
 hipError_t launch_plane_sums(nspnp_state *s, int what, double *dev_out) {
     const int chunks = plane_chunks(s);
     const int M = s->d.M;
     if (dev_out != s->red || (int64_t)M * kPlaneQ * (chunks + 1) > s->nred) return hipErrorInvalidValue;
-    double *part = dev_out + (size_t)M * kPlaneQ;
+    double *part = chunks > 1 ? dev_out + (size_t)M * kPlaneQ : dev_out;
     const dim3 g((unsigned)chunks * (what == PLANE_WALL ? 2u : (unsigned)M), 1, (unsigned)s->nmem);
     auto go = [&](auto zero) {
         using T = decltype(zero);
@@ -562,6 +564,7 @@ hipError_t launch_plane_sums(nspnp_state *s, int what, double *dev_out) {
     };
     if (s->fp64) go(double{});
     else go(float{});
+    if (chunks == 1) return hipGetLastError();
     k_plane_close<<<dim3((unsigned)((M * kPlaneQ + kRedThreads - 1) / kRedThreads), 1, (unsigned)s->nmem), kRedThreads,
                     0, s->stream>>>(M, what, part, dev_out, chunks, s->mstride);
     return hipGetLastError();
@@ -572,16 +575,18 @@ hipError_t launch_energy_sums(nspnp_state *s, double *dev_out) {
     const int chunks = plane_chunks(s);
     const int M = s->d.M;
     if (dev_out != s->red || (int64_t)M * (4 + kEnergyQ * chunks) > s->nred) return hipErrorInvalidValue;
-    double *part = dev_out + 4 * (size_t)M;
+    double *part = chunks > 1 ? dev_out + 4 * (size_t)M : dev_out;
+    const int stride = chunks > 1 ? kEnergyQ : 4;
     const dim3 g((unsigned)(chunks * M), 1, (unsigned)s->nmem);
     auto go = [&](auto zero) {
         using T = decltype(zero);
         k_energy<T><<<g, kRedThreads, 0, s->stream>>>(s->d, s->d_phys, s->tb, (const T *)s->f[0], (const T *)s->f[1],
                                                       (const T *)s->f[2], (const T *)s->f[3], (const T *)s->f[4],
-                                                      (const T *)s->f[5], part, chunks, s->mstride);
+                                                      (const T *)s->f[5], part, chunks, stride, s->mstride);
     };
     if (s->fp64) go(double{});
     else go(float{});
+    if (chunks == 1) return hipGetLastError();
     k_energy_close<<<dim3((unsigned)((4 * M + kRedThreads - 1) / kRedThreads), 1, (unsigned)s->nmem), kRedThreads, 0,
                      s->stream>>>(M, part, dev_out, chunks, s->mstride);
     return hipGetLastError();
