@@ -293,8 +293,8 @@ NSPNP_API int nspnp_load(nspnp_state *s, const char *path);
 /* Choose this run's launch shapes as nspnp_ensemble_autotune does for a
  * size class (same candidates, cache format and key, with member count 1).
  * Trials advance the run by trial_substeps (a multiple of 3) per candidate;
- * the shapes never change a result beyond the rounding order of the CN
- * method.  tiles_out (NULL or 8 ints) receives the choice.  Synchronises. */
+ * the shapes never change a result beyond the rounding order of two methods
+ * (tiles_out[4] = 0 and tiles_out[7], see there).  tiles_out (NULL or 8 ints) receives the choice.  Synchronises. */
 NSPNP_API int nspnp_autotune(nspnp_state *s, const char *cache_path, int32_t trial_substeps, int32_t *tiles_out);
 
 /* Read / set this run's launch shapes (8 ints in the order of
@@ -369,16 +369,19 @@ NSPNP_API int nspnp_ensemble_clock(nspnp_ensemble *e, int32_t member, double *t,
  * multiple of 3) per candidate, coordinate by coordinate; also the rows
  * one block of the stencil kernel marches.  Results are read from /
  * appended to the text cache at cache_path (NULL: no cache), one line per
- * (arch, grid, precision, members) key.  Trials advance the members (the
- * launch shape does not change any result); on return every member has
- * advanced by the same number of substeps.  tiles_out (NULL or 8 ints per
- * class) receives the choice: explicit-kernel threads, threads of the CN lane
- * scans (64 to 256: tiles of 16 columns; 512: tiles of 32 columns), x and z
- * transform points, modes per tile of the mode solves, correction threads,
- * explicit-kernel and correction slab rows, and the CN method (0: lane scans
- * in FP64 up to 320 rows, else slabs of rows in registers, their height by
- * the number of rows; 16: slabs of 16 rows; 32: of 24 up to 384 rows, else
- * of 16).
+ * (arch, grid, precision, members) key.  Shapes that no kernel reads at these
+ * sizes are not tried.  Trials advance the members; on return every member has
+ * advanced by the same number of substeps.  The shapes change no result but
+ * for its rounding under two methods, mode solves 0 and the CN method, which
+ * sum in another order: runs tuned apart can differ in their last bits, unless
+ * they take their shapes from one cache or from nspnp_set_tiles.  tiles_out
+ * (NULL or 8 ints per class) receives the choice: explicit-kernel threads,
+ * threads of the CN lane scans (64 to 256: tiles of 16 columns; 512: tiles of
+ * 32 columns), x and z transform points, modes per tile of the mode solves (0:
+ * fused with the z transforms), correction threads, explicit-kernel and
+ * correction slab rows, and the CN method (0: lane scans in FP64 up to 320
+ * rows, else slabs of rows in registers, their height by the number of rows;
+ * 16: slabs of 16 rows; 32: of 24 up to 384 rows, else of 16).
  * Synchronises. */
 NSPNP_API int nspnp_ensemble_autotune(nspnp_ensemble *e, const char *cache_path, int32_t trial_substeps,
                                       int32_t *tiles_out);

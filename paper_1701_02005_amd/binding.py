@@ -326,7 +326,8 @@ class Solver:
         _check(self.lib.nspnp_sync(self._h))
 
     def autotune(self, cache_path: str | None = None, trial_substeps: int = 6) -> Dict[str, int]:
-        """Launch shapes chosen by timing (advances the run; results unchanged)."""
+        """Launch shapes chosen by timing (advances the run; two of them, thomas 0 and cnslab, change
+        the rounding of the results, the others nothing)."""
         out = (ctypes.c_int32 * len(Ensemble.TILE_NAMES))()
         path = cache_path.encode() if cache_path else None
         _check(self.lib.nspnp_autotune(self._h, path, int(trial_substeps), out))

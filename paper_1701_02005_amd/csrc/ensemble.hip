@@ -173,8 +173,9 @@ void tiles_to_ints(const Tiles &t, int32_t *o) {
 
 // Launch shapes of one handle (a single run or a size class): from the cache
 // when its key is there, else by coordinate descent over each shape, timing
-// trial substeps per candidate (every trial advances the state; the shapes do
-// not change any result).
+// trial substeps per candidate (every trial advances the state; see Tiles for
+// the two shapes that change its rounding).  Shapes that no kernel of the
+// handle reads, and methods that come out the same, are not tried.
 int tune_handle(nspnp_state *c, const char *cache_path, int trial) {
     const std::string key = tune_key(c);
     Tiles best = c->tiles;
@@ -208,13 +209,26 @@ int tune_handle(nspnp_state *c, const char *cache_path, int trial) {
             return NSPNP_OK;
         };
         if ((rc = sweep(&c->tiles.expl, cand_expl, 3))) return rc;
-        if ((rc = sweep(&c->tiles.cn, cand_cn, 4))) return rc;
-        if ((rc = sweep(&c->tiles.fftx, cand_fft, 3))) return rc;
-        if ((rc = sweep(&c->tiles.fftz, cand_fft, 3))) return rc;
-        if ((rc = sweep(&c->tiles.thomas, cand_th, 5))) return rc;
+        if (cn_tile_read(c) && (rc = sweep(&c->tiles.cn, cand_cn, 4))) return rc;
+        const unsigned read = elliptic_tiles_read(c);
+        if ((read & kReadFftx) && (rc = sweep(&c->tiles.fftx, cand_fft, 3))) return rc;
+        if ((read & kReadFftz) && (rc = sweep(&c->tiles.fftz, cand_fft, 3))) return rc;
+        const int method_th[] = {0, c->tiles.thomas ? c->tiles.thomas : 16};
+        if ((rc = (read & kReadThomas) ? sweep(&c->tiles.thomas, cand_th, 5) : sweep(&c->tiles.thomas, method_th, 2)))
+            return rc;
         if ((rc = sweep(&c->tiles.corr, cand_corr, 2))) return rc;
         if ((rc = sweep(&c->tiles.slab, cand_slab, 4))) return rc;
-        if ((rc = sweep(&c->tiles.cnslab, cand_cnslab, 3))) return rc;
+        std::vector<int> cnslab, rows = {cn_slab_rows(c)};
+        for (const int v : cand_cnslab) {
+            const int keep = c->tiles.cnslab;
+            c->tiles.cnslab = v;
+            const int r = cn_slab_rows(c);
+            c->tiles.cnslab = keep;
+            if (std::find(rows.begin(), rows.end(), r) != rows.end()) continue;
+            rows.push_back(r);
+            cnslab.push_back(v);
+        }
+        if ((rc = sweep(&c->tiles.cnslab, cnslab.data(), (int)cnslab.size()))) return rc;
         best = c->tiles;
         cache_store(cache_path, key, best);
     }

@@ -297,9 +297,10 @@ constexpr int kCnPad = 32;
 __host__ __device__ inline int cn_rows(int M) { return (M + kCnPad - 1) / kCnPad * kCnPad + kCnPad; }
 __host__ __device__ inline size_t cn_stage_stride(int M) { return 9 * (size_t)cn_rows(M); }
 
-// Launch shapes chosen by the autotuner.  None of them changes the
-// arithmetic done per cell, column, line or mode, so results are bitwise
-// independent of the choice.
+// Launch shapes chosen by the autotuner.  Results are bitwise independent of
+// the choice but for two: cnslab (rows per thread of the Crank-Nicolson solve)
+// and thomas 0 (elimination and pivots of the fused marches) sum in another
+// order, within the rounding of the solve.
 struct Tiles {
     int expl;     // threads per block of the explicit kernel (64..256)
     int cn;       // threads per block of the Crank-Nicolson lane scans
@@ -438,6 +439,11 @@ hipError_t launch_explicit(nspnp_state *s, const Stage &st, bool write_r);
 hipError_t launch_explicit_debug(nspnp_state *s, double *const out[5]);
 hipError_t launch_adv_limit(nspnp_state *s, const Stage &st, double *const out[5]);
 hipError_t launch_cn_solve(nspnp_state *s, const Stage &st);
+int cn_slab_rows(const nspnp_state *s);   // rows per thread of the Crank-Nicolson solve, 0: lane scans
+// shapes that some kernel of this handle's substeps reads (its grid, type, members and other shapes as they are)
+bool cn_tile_read(const nspnp_state *s);  // Tiles::cn
+constexpr unsigned kReadFftx = 1, kReadFftz = 2, kReadThomas = 4;
+unsigned elliptic_tiles_read(const nspnp_state *s);  // Tiles::fftx, fftz, thomas above 0 (were thomas not 0)
 hipError_t launch_correct(nspnp_state *s, const Stage &st, bool update_p, double fixed_scale, bool advance_clock);
 hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b);
 // Raises a kernel's dynamic-LDS limit to the device maximum when bytes > 64 KB

@@ -2033,6 +2033,37 @@ hipError_t lds_opt_in(const void *fn, size_t bytes, int lds_max) {
     return e;
 }
 
+namespace {
+// The forms of the elliptic chain, by the handle's sizes and shapes.
+bool has_r8(const FftPlan &p) {
+    for (int q = 0; q < p.nstages; ++q)
+        if (p.radix[q] == 8) return true;
+    return false;
+}
+bool march_form(const nspnp_state *s) { return s->tiles.thomas == 0 && s->mu; }  // z transforms fused with the y solve
+// (the plane kernels' passes: radix 4, 2 and 3)
+bool planes_form(const nspnp_state *s) {
+    return !march_form(s) && !has_r8(s->planx) && !has_r8(s->planz) && plane_fits(s);
+}
+// 64 to 512 points, powers of two: a wave per line pair, or per 2 or 4
+bool wave_line(int n) { return n == 64 || n == 128 || n == 256 || n == 512; }
+// Members that share the pivots, and two waves for every SIMD: fewer waves
+// would leave the chip waiting for single columns.
+bool columns_form(const nspnp_state *s, int nprob, int nmem) {
+    const int64_t nmodes = (int64_t)s->d.nxh * s->d.nz;
+    return s->d.M <= kColRows && nmem >= 4 && (nmodes + kColModes - 1) / kColModes * nprob * nmem >= 2048;
+}
+}  // namespace
+
+unsigned elliptic_tiles_read(const nspnp_state *s) {
+    const bool planes = planes_form(s);
+    unsigned r = 0;
+    if (!planes && !wave_line(s->d.nx)) r |= kReadFftx;
+    if (!planes && !march_form(s) && !wave_line(s->d.nz)) r |= kReadFftz;
+    if (s->d.M <= kLaneRows && !columns_form(s, 2, s->nmem)) r |= kReadThomas;
+    return r;
+}
+
 // All members of the handle are solved when b.ms is the member stride;
 // caller-owned arrays (b.ms = 0) are solved for member 0 only.
 hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
@@ -2042,19 +2073,11 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
     const int64_t nspec = (int64_t)d.nxh * d.nz * d.M;
     const int ppb = pairs_per_block(d.nx, s->tiles.fftx);
     const int64_t npairs = (nlines + 1) / 2;
-    auto has_r8 = [](const FftPlan &p) {
-        for (int q = 0; q < p.nstages; ++q)
-            if (p.radix[q] == 8) return true;
-        return false;
-    };
     const bool r8x = has_r8(s->planx), r8z = has_r8(s->planz);
-    const bool march = s->tiles.thomas == 0 && s->mu;  // z transforms fused with the y solve
-    const bool planes = !march && !r8x && !r8z && plane_fits(s);  // (its passes: radix 4, 2 and 3)
+    const bool march = march_form(s), planes = planes_form(s);
     const dim3 gp((unsigned)d.M, (unsigned)b.nprob, (unsigned)nmem);
     const size_t ldsp = plane_lds(d.nx, d.nz);
     const unsigned tp = plane_threads(s);
-    // 64 to 512 points, powers of two: a wave per line pair, or per 2 or 4
-    auto wave_line = [](int n) { return n == 64 || n == 128 || n == 256 || n == 512; };
     const bool lines = !planes && wave_line(d.nx);
     const int lpb = d.nx == 64 ? 32 : (d.nx == 128 ? 16 : 8);  // lines per block
     const dim3 gl((unsigned)((nlines + lpb - 1) / lpb), (unsigned)b.nprob, (unsigned)nmem);
@@ -2162,9 +2185,7 @@ hipError_t launch_poisson_batch(nspnp_state *s, const PoissonBatch &b) {
             else if (L == 12) NSPNP_MR(12);
             else NSPNP_MR(16);
 #undef NSPNP_MR
-        } else if (d.M <= kColRows && nmem >= 4 && (nmodes + kColModes - 1) / kColModes * b.nprob * nmem >= 2048) {
-            // (members that share the pivots, and two waves for every SIMD: fewer
-            // waves would leave the chip waiting for single columns)
+        } else if (columns_form(s, b.nprob, nmem)) {
             ProfScope prof_(s, K_THOMAS);
             const dim3 gm((unsigned)((nmodes + kColModes - 1) / kColModes), (unsigned)b.nprob, (unsigned)((nmem + 3) / 4));
 #define NSPNP_MC(LL) k_mode_columns<LL><<<gm, 256, 0, s->stream>>>(d, s->tb, b, s->spec, s->fac, nspec, nmem)

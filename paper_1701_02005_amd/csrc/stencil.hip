@@ -1683,14 +1683,18 @@ static hipError_t launch_cyc(nspnp_state *s, const Stage &st, bool along_z) {
 #undef NSPNP_CYC_CASE
 }
 
+// Planes on which the lane scans take 8 waves on 16 columns whatever Tiles::cn:
+// up to two such blocks per CU.
+static bool cn_small(const nspnp_state *s) { return (s->d.plane + 15) / 16 * 5 * s->nmem <= 512; }
+
 // Lane-scan Crank-Nicolson solve of the five fields (tiles of 16 or 32 columns).
 static hipError_t launch_cn_lane(nspnp_state *s, const CnArgs &a) {
     // up to 32 rows: groups of 16 or 32 lanes a column, which hold all of its
     // rows (a whole wave's idle lanes would only pass values through: the result
-    // is the same); up to two blocks per CU: 8 waves on 16 columns (32 x 33 x 32
-    // 8.6 us with one column a wave, 6.5 so; latency)
+    // is the same); small planes: 8 waves on 16 columns (32 x 33 x 32 8.6 us with
+    // one column a wave, 6.5 so; latency)
     const int lanes = s->d.M <= 16 ? 16 : (s->d.M <= 32 ? 32 : 64);
-    const bool small = (s->d.plane + 15) / 16 * 5 * s->nmem <= 512;
+    const bool small = cn_small(s);
     const int tb = small ? (lanes == 16 ? 256 : 512) : s->tiles.cn;
     const int tcols = small ? 16 : cn_tile_cols(tb);
     const dim3 g((unsigned)((s->d.plane + tcols - 1) / tcols), 5, (unsigned)s->nmem);
@@ -1721,14 +1725,14 @@ static hipError_t launch_cn_lane(nspnp_state *s, const CnArgs &a) {
 #undef NSPNP_CN_CASE
 }
 
-// Rows a thread holds in the Crank-Nicolson solve (the result's rounding
-// depends on it, so it follows from the type and the rows alone); 0: lane
-// scans.  24 rows where they make
+// Rows a thread holds in the Crank-Nicolson solve; 0: lane scans.  The result's
+// rounding depends on it, so with cnslab 0, the default, it follows from the
+// type and the rows alone; cnslab 16 and 32 ask for another.  24 rows where they make
 // 8 or 16 whole slabs: 0.130 ms (mixed) against 0.145 for 12 and 0.136 for
 // 16 at 256 x 193 x 256; 16 at up to 128 (28.9 against 30.8 us for 24, 33.4
 // for 8 at 128 x 129 x 128); short columns split into at least 8 slabs, which
 // fill the chip on small planes.
-static int cn_slab_rows(const nspnp_state *s) {
+int cn_slab_rows(const nspnp_state *s) {
     const int M = s->d.M;
     if (s->fp64 && s->tiles.cnslab == 0 && M <= kCnLaneRows) return 0;
     if (s->tiles.cnslab == 16 || M > 384) return 16;
@@ -1737,6 +1741,8 @@ static int cn_slab_rows(const nspnp_state *s) {
     if (M <= 64) return 8;
     return (M <= 128 || (M > 192 && M <= 256)) ? 16 : 24;
 }
+
+bool cn_tile_read(const nspnp_state *s) { return cn_slab_rows(s) == 0 && !cn_small(s); }
 
 // out_r: the solution replaces r, else it is added to the fields
 static hipError_t launch_cn_y(nspnp_state *s, const Stage &st, bool out_r) {
