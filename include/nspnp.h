@@ -369,7 +369,8 @@ NSPNP_API int nspnp_ensemble_clock(nspnp_ensemble *e, int32_t member, double *t,
  * multiple of 3) per candidate, coordinate by coordinate; also the rows
  * one block of the stencil kernel marches.  Results are read from /
  * appended to the text cache at cache_path (NULL: no cache), one line per
- * (arch, grid, precision, members) key.  Shapes that no kernel reads at these
+ * (arch, grid, precision, members) key, also for implicit_xz and the mixed
+ * form's migration_face 2.  Shapes that no kernel reads at these
  * sizes are not tried.  Trials advance the members; on return every member has
  * advanced by the same number of substeps.  The shapes change no result but
  * for its rounding under two methods, mode solves 0 and the CN method, which

@@ -125,6 +125,8 @@ std::string tune_key(const nspnp_state *c) {
     std::ostringstream k;
     k << "gfx950v7:" << c->cfg.nx << "x" << c->cfg.ny << "x" << c->cfg.nz << ":" << (c->fp64 ? "fp64" : "mixed")
       << ":" << c->nmem << (c->cfg.implicit_xz ? ":ixz" : "");
+    // (the mixed form's limiter runs in the explicit kernel on some of its tiles only)
+    if (!c->fp64 && c->cfg.migration_face == 2) k << ":lim";
     return k.str();
 }
 

@@ -33,3 +33,16 @@ def test_trials(case):
     trials = s.clock()[3] // 3
     assert 2 * (1 + candidates) <= trials <= 2 * (1 + candidates + len(read))
     assert all(tiles[k] == default[k] for k in tiles if k not in read)
+
+
+def test_limited_runs_have_shapes_of_their_own(tmp_path):
+    """The mixed form's limited flux is formed in the explicit kernel on some
+    tiles and in a pass of its own on others: shapes tuned without it are not
+    taken over."""
+    import paper_1701_02005_amd as P
+    cache = tmp_path / "shapes.txt"
+    base = dataclasses.replace(P.configs.couette_small(precision="mixed"), nx=64, ny=9, nz=8)
+    for face, lines in ((0, 1), (1, 1), (2, 2), (2, 2)):
+        P.Solver(dataclasses.replace(base, migration_face=face)).autotune(str(cache), 3)
+        keys = [line.split()[0] for line in cache.read_text().splitlines()]
+        assert len(keys) == lines == len(set(keys)), (face, keys)
