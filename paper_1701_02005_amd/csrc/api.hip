@@ -98,7 +98,7 @@ Layout make_layout(const nspnp_config *c) {
     L.off_psi = o; o = align256(o + n * 8);
     const int64_t nspec = nxh * c->nz * M;
     L.off_spec = o; o = align256(o + 2 * nspec * 16);
-    L.off_fac = o; o = align256(o + 2 * nspec * 16);  // [kind][mode][row] pivots
+    L.off_fac = o; o = align256(o + (M <= kLaneRows ? 2 * nspec * 16 : 0));  // [kind][mode][row] pivots
     L.off_gv = o; o = align256(o + 2 * nspec * 8);    // [kind][row][mode] 1/den
     L.off_mu = o; o = align256(o + 2 * 16);           // pinned-mode volume means
     L.off_coef = o; o = align256(o + 3 * cn_stage_stride((int)M) * 8);  // 3 stages
@@ -313,7 +313,7 @@ void setup_handle(nspnp_state *s, const nspnp_config *cfg, char *base, int nmem,
     for (int q = 0; q < 5; ++q) s->r[q] = base + L.off_r[q];
     s->psi = (double *)(base + L.off_psi);
     s->spec = (double2 *)(base + L.off_spec);
-    s->fac = (double2 *)(base + L.off_fac);
+    s->fac = s->d.M <= kLaneRows ? (double2 *)(base + L.off_fac) : nullptr;
     s->gv = (double *)(base + L.off_gv);
     s->mu = (double2 *)(base + L.off_mu);
     s->cn_coef = (double *)(base + L.off_coef);
@@ -349,7 +349,7 @@ nspnp_state *member_view(const nspnp_state *cls, int m, const nspnp_config *cfg)
     for (int q = 0; q < 5; ++q) { v->h[q] = sh(cls->h[q]); v->r[q] = sh(cls->r[q]); }
     v->psi = sh(cls->psi);
     v->spec = sh(cls->spec);
-    v->fac = sh(cls->fac);
+    v->fac = cls->fac ? sh(cls->fac) : nullptr;
     v->gv = sh(cls->gv);
     v->mu = sh(cls->mu);
     v->cn_coef = sh(cls->cn_coef);

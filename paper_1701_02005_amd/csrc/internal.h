@@ -17,6 +17,9 @@ constexpr int kMaxFftStages = 12;
 // Most cell rows across the gap (ny - 1) of a supported grid: 8 rows per
 // lane of the wall-normal scans.
 constexpr int kMaxRows = 512;
+// Most rows that the lane-split mode solves take (5 per lane); taller columns
+// need no pivot pairs.
+constexpr int kLaneRows = 320;
 
 // Radix decomposition of one FFT length (radices 4, 2, 3; product = n).
 struct FftPlan {
@@ -383,8 +386,8 @@ struct nspnp_state {
     void *r[5];          // Crank-Nicolson right-hand sides, state type
     double *psi;         // pressure increment (n, FP64)
     double2 *spec;       // two half spectra, 2 * nxh * nz * M
-    double2 *fac;        // Thomas pivots (1/den, c') of both elliptic operators, [kind][mode][row] (NULL: not
-                         // kept; FP64 handles, for the lane-split solve)
+    double2 *fac;        // Thomas pivots (1/den, c') of both elliptic operators, [kind][mode][row], for the
+                         // lane-split solves and columns of two lanes (NULL: not kept, above kLaneRows rows)
     double *gv;          // 1/den alone, [kind][row][mode]
     double2 *mu;         // volume mean of the pinned pressure mode, per problem (fused y-march)
     double *cn_coef;     // Crank-Nicolson recurrence coefficients, cn_stage_stride(M) per stage

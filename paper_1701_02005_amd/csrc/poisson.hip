@@ -1275,7 +1275,6 @@ __global__ void __launch_bounds__(256) k_thomas_factors(Dims d, Tables tb, doubl
 // (0.111 against 0.087 ms at 256 x 193 x 256): it keeps their results, down
 // to plane means that are zero but for rounding, bit for bit what they were.
 constexpr int kModes = 32;
-constexpr int kLaneRows = 320;
 
 template <int L>
 __global__ void __launch_bounds__(1024) k_mode_rows(Dims d, Tables tb, PoissonBatch b, double2 *spec_all,
