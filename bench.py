@@ -179,8 +179,8 @@ def measure(cfg, args, P, torch, tiles_trial: int) -> dict:
             src = Path(ent["source"]).name if ent else None
             cn_rows = cfg.precision == "mixed" or cfg.ny > 321 or bool(tiles and tiles.get("cnslab"))
             z_fused = bool(tiles) and tiles.get("thomas") == 0
-            same_kernels = ent and tuple(ent.get("kernels", ())) == tuple(
-                pmc_traffic.class_kernels(dom, z_fused=z_fused, cn_rows=cn_rows))
+            same_kernels = ent and tuple(ent.get("kernels", ())) in pmc_traffic.class_forms(
+                dom, z_fused=z_fused, cn_rows=cn_rows)
             if same_kernels and ent.get("source_sha256") == pmc_traffic.source_hash(src):
                 traffic = ent["bytes_per_launch"]
         except (ValueError, OSError, KeyError):

@@ -42,7 +42,8 @@ CLASSES = {
 }
 
 # the same class where the solve holds slabs of rows in registers (the mixed form,
-# FP64 above 320 rows), and in counter runs of the earlier three-pass method
+# FP64 above 320 rows), and in counter runs of an earlier three-pass method, which
+# no kernel of the library takes any more
 CN_ROWS_KERNELS = ("k_cn_coef", "k_cn_rows")
 CN_SLAB_KERNELS = ("k_cn_coef", "k_cn_slab_scan", "k_cn_slab_apply")
 
@@ -70,6 +71,15 @@ def class_kernels(cls: str, cn_slab: bool = False, z_fused: bool = False, cn_row
     if z_fused and cls in Z_FUSED_KERNELS:
         return Z_FUSED_KERNELS[cls]
     return CLASSES[cls][0]
+
+
+def class_forms(cls: str, z_fused: bool = False, cn_rows: bool = False):
+    """Every set of kernels that a class may be made of under these methods; which of the elliptic
+    chain's forms a run takes follows from its sizes."""
+    forms = (class_kernels(cls, z_fused=z_fused, cn_rows=cn_rows),)
+    if z_fused and (cls in Z_FUSED_KERNELS or cls == "thomas_modes"):
+        return forms
+    return forms + ELLIPTIC_KERNELS.get(cls, ())
 
 
 def source_hash(fname: str) -> str:
