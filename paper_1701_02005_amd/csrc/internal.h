@@ -14,8 +14,8 @@
 namespace nspnp {
 
 constexpr int kMaxFftStages = 12;
-// Most cell rows across the gap (ny - 1) of a supported grid: 8 rows per
-// lane of the wall-normal scans.
+// Most cell rows across the gap (ny - 1) of a supported grid: 32 slabs of 16
+// rows, 1024 threads, in the row-slab solves.
 constexpr int kMaxRows = 512;
 // Most rows that the lane-split mode solves take (5 per lane); taller columns
 // need no pivot pairs.

@@ -503,7 +503,9 @@ __global__ void __launch_bounds__(256) k_fft_x_c2r(Dims d, Tables tb, FftPlan pl
 // 0.93 -> 0.50 ms; 256 x 193 x 256 FP64 165 -> 130 and 106 -> 62 us, 128 x 129
 // x 128 36 -> 29 and 30 -> 15 us, 64 x 129 x 256 34 -> 28 and 29 -> 15 us.
 // Which product of a complex multiplication is rounded before the fused
-// multiply-add is written out, as the general kernels' compilation has it.
+// multiply-add is written out, as the general kernels' compilation has it (the
+// general kernels leave it to the compiler: one that fuses otherwise there would
+// leave the two equal to rounding).
 __device__ __forceinline__ double2 twiddle(double2 a, double2 w, bool inv) {
     if (inv) return make_double2(__builtin_fma(a.x, w.x, a.y * w.y), __builtin_fma(a.y, w.x, -(a.x * w.y)));
     return make_double2(__builtin_fma(a.x, w.x, -(a.y * w.y)), __builtin_fma(a.y, w.x, a.x * w.y));
@@ -1271,9 +1273,11 @@ __global__ void __launch_bounds__(256) k_thomas_factors(Dims d, Tables tb, doubl
 // mode and row against 48 and two dozen shuffles per mode for the lane-split
 // solve below: bound by memory, 0.86 ms at 512 x 385 x 512 (4.7 TB/s; 1.13 ms
 // lane-split, 0.94 with tiles of 8 modes), one problem of 256 x 193 x 256 in
-// 45 us (63).  A run's own solves on up to kLaneRows rows stay lane-split
-// (0.111 against 0.087 ms at 256 x 193 x 256): it keeps their results, down
-// to plane means that are zero but for rounding, bit for bit what they were.
+// 45 us (63).  1024 threads leave 128 VGPRs: slabs of 16 rows spill 40 bytes a
+// lane (also at 193 to 256 rows, whose blocks have 512 threads at most).  A
+// run's own solves on up to kLaneRows rows stay lane-split, 0.111 against 0.087
+// ms at 256 x 193 x 256: that keeps FP64 results bit for bit, down to plane means
+// that are zero but for rounding; the mixed form shares the rule.
 constexpr int kModes = 32;
 
 template <int L>

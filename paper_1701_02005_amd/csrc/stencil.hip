@@ -119,7 +119,8 @@ struct HaloRegs {
 // and 157 (carrying the y faces' values from row to row, a sixth of its
 // arithmetic less, changes nothing).  The values two
 // columns away come from the caches (the row's own tile loads them), those two
-// rows up from memory one row early.  FP64 keeps the pass (registers).
+// rows up from memory one row early.  FP64 keeps the pass: its kernel has 147
+// of the 168 VGPRs of three waves without the limiter (in it, not measured).
 template <typename T, int kHalo, int kWaves, int kMode, int kTx = 0, int kTz = 0, bool kLim = false>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWaves))) k_explicit(ExplicitArgs a) {
     extern __shared__ unsigned char s_raw[];
@@ -804,10 +805,11 @@ __global__ void __launch_bounds__(512) k_cn_scan(CnArgs a) {
 // mixed 1.11 ms (5.4 TB/s); 256 x 193 x 256 mixed 0.130 ms.  The lane scans
 // took 3.65, 2.37 and 0.191 ms (short runs of a row, and shuffles); a
 // three-pass form, its first pass in the explicit kernel, 2.29 ms and 0.15 ms
-// more in that kernel.  Not for FP64 columns of up to kCnLaneRows rows: the
-// gain there is small (0.256 against 0.273 ms at 256 x 193 x 256, 48 against
-// 51 us at 128 x 129 x 128), and the lane scans keep such runs bit for bit
-// what they were.
+// more in that kernel.  Not by default for FP64 columns of up to kCnLaneRows
+// rows, though it is faster there too (0.256 against 0.273 ms at 256 x 193 x
+// 256, 48 against 51 us at 128 x 129 x 128): the lane scans keep the results of
+// such runs bit for bit, down to plane means that are zero but for rounding.
+// cnslab 16 or 32 asks for it.
 template <typename T, int L, int kCx, bool kOut>
 __global__ void __launch_bounds__(1024) k_cn_rows(CnArgs a) {
     extern __shared__ double s_x[];  // exits [slab][kCx], the slabs' products, (kCx 32) the coefficients
@@ -1351,8 +1353,8 @@ inline dim3 grid1(int64_t n, int b = 256) { return dim3((unsigned)((n + b - 1) /
 
 }  // namespace
 
-// Rows that one block of a row march takes: `rows`, halved (not below `least`)
-// while that leaves the chip with fewer than two blocks per CU.  A march is
+// Rows that one block of a row march takes: `rows`, halved while it is above
+// `least` and leaves the chip with fewer than two blocks per CU.  A march is
 // serial in its rows, about 2.7 us a row in the explicit kernel: with 16 rows
 // a 32 x 33 x 32 grid has 8 blocks and takes 44 us, with 1 row 128 blocks.
 // The results do not depend on it.
@@ -1403,10 +1405,9 @@ static hipError_t explicit_launch(nspnp_state *s, const ExplicitArgs &a, int thr
         return hipGetLastError();
     }
     if (!dbg && threads == 256 && s->fp64 && a.tx == 32 && a.tz == 8) {  // the common tiles
-        // three waves per SIMD (at most 168 VGPRs; 12 bytes per lane spill):
-        // with the fused Crank-Nicolson first pass the compiler's own choice
-        // (171 VGPRs, two waves) was measured 0.29 ms slower per launch at
-        // 512 x 385 x 512 (3.73 against 3.44 ms)
+        // three waves per SIMD: 147 VGPRs, no spill; asking for two gives the
+        // same registers and time (0.415 ms at 256 x 193 x 256, 3.32 ms at 512 x
+        // 385 x 512)
         k_explicit<double, 2, 3, 0, 32, 8><<<blocks, threads, lds, s->stream>>>(a);
     } else if (!dbg && threads == 256 && !s->fp64 && a.tx == 64 && a.tz == 4) {
         k_explicit<float, 2, 3, 0, 64, 4><<<blocks, threads, lds, s->stream>>>(a);
