@@ -1,6 +1,7 @@
 """Which kernels a class of the traffic table may be made of (no GPU): every
 entry of the committed table is one of its class's forms, so that bench.py can
-report it, and a form of one method is not taken for another's."""
+report it, a form of one method is not taken for another's, and the step's
+coefficient kernel counts where it is launched."""
 import json
 from pathlib import Path
 
@@ -24,3 +25,6 @@ def test_forms_of_other_methods_stay_apart():
     assert {("k_thomas_tile",), ("k_mode_rows",), ("k_mode_columns",)} == set(T.class_forms("thomas_modes"))
     assert ("k_lines_r2c",) in T.class_forms("fft_x_r2c", z_fused=True)
 
+
+def test_coefficient_kernel_in_the_step_class():
+    assert T.class_kernels("dt") == ("k_dt_partial", "k_cn_coef")
