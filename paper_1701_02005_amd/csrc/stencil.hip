@@ -897,14 +897,17 @@ __global__ void __launch_bounds__(1024) k_cn_rows(CnArgs a) {
         x[t] += v;
     }
     if (!in) return;
+    // (the wall row of the nodes is no unknown: it keeps its value, also where
+    // the rows above are not finite)
+    const int jlo = sys == 1 ? 1 : 0;
     if constexpr (kOut) {
 #pragma unroll
         for (int t = 0; t < L; ++t)
-            if (j0 + t < M) st_once(at(r, t), (T)x[t]);
+            if (j0 + t < M && (t > 0 || j0 >= jlo)) st_once(at(r, t), (T)x[t]);
     } else {
 #pragma unroll
         for (int t = 0; t < QE; ++t)
-            if (j0 + t < M) st_once(at(q, t), (T)((double)qv[t] + x[t]));
+            if (j0 + t < M && (t > 0 || j0 >= jlo)) st_once(at(q, t), (T)((double)qv[t] + x[t]));
         if constexpr (QE < L) {
 #pragma unroll
             for (int t = QE; t < L; ++t) qv[t - QE] = ld_once(at(q, t));
